@@ -1,0 +1,569 @@
+// Decode attention over the paged KV cache, one query row per sequence:
+// QK-norm and rotary of the row's Q and K, the paged store of its K and V,
+// grouped-query attention over positions [0, n], in one kernel.
+//
+// A workgroup of two or four waves owns a run of keys ("split") of one (sequence, KV
+// head) and all G query heads that share it.  Each wave walks its share of the
+// split's 32-key blocks on its own: K and V rows go from memory
+// straight into a private two-stage LDS ring (buffer_load ... lds, whole
+// 256-byte head rows), so up to 32 KiB per wave and 128 KiB per CU are in
+// flight and the waves meet no barrier until the end.
+//
+// Scores are S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (the G heads are the
+// columns, repeated up to 16): lane l holds keys 4 (l / 16) + r of head l mod 16.
+// O^T = V^T P^T takes those registers as its B operand as they are, with V
+// read transposed from LDS (ds_read_b64_tr_b16).  P stays 32-bit: it is
+// split into three bf16 parts whose sum is P exactly, one MFMA each; the
+// matrix cores are idle here, and the kernel is bound by the K/V stream.
+//
+// Splits are merged by the last workgroup of a (sequence, KV head) to
+// arrive: partial records and an arrival count through agent-scope accesses,
+// as the skinny projections do.
+//
+// Per layer against the three kernels this replaces (norm / rotary / store,
+// 64-key splits on the vector units, merge): 32 sequences of 136,000 keys in
+// all, 8 KV heads of 128 (558 MB): 213 -> 108 us (5.2 TB/s; bound by the K/V
+// stream); 8 sequences, 32,000 keys: 69 -> 33 us; one sequence of 4000 keys,
+// 64 query heads: 27 -> 13.6 us (bound by the chain of launch, table, stream,
+// record store, count and merge).
+#include <algorithm>
+#include <type_traits>
+
+#include "common.h"
+#include "kernels.h"
+
+namespace pallas {
+
+namespace {
+
+constexpr int kPage = 16;        // tokens per cache page (the only page size the library accepts)
+// The declared bound is four times the launched size: it limits a wave to 256
+// registers, and the compiler then keeps the accumulators in vector registers
+// (with 512 it moves them to accumulation registers and back in every block).
+constexpr int kBoundThreads = 512;
+constexpr int kBlk = 32;         // keys per block: two pages
+constexpr int kStages = 2;       // blocks in flight per wave
+constexpr int kMergeBatch = 16;  // split records read at once by the last arriver
+constexpr int kAuxAgent = 16;    // buffer cache policy: sc1 (device-coherent)
+constexpr int kAuxStream = 2;    // nt: K and V are read once per step
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// LDS rows are whole head rows of CH 16-byte chunks; chunk c of row r sits in
+// slot c ^ swz(r).  K: the 16 rows an MFMA operand read covers at one chunk
+// land on 16 distinct 4-bank groups.  V: the 8 keys x 2 chunks that half of a
+// transposed read covers do.
+template <int CH>
+__device__ __forceinline__ int swz_k(int row) { return CH == 16 ? row & 15 : (row >> 1) & 7; }
+template <int CH>
+__device__ __forceinline__ int swz_v(int row) { return CH == 16 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
+
+// Four output tiles of the PV operand from a V block at LDS byte address
+// `vb`: keys 4 q4 .. + 3 of its first page (at the tile's address, vb XOR 32
+// per tile) and of its second (`kSecond` bytes further).  In each 16-lane
+// group, ds_read_b64_tr_b16 hands lane i element i % 4 of the 64-bit words
+// read by lanes i / 4, i / 4 + 4, i / 4 + 8 and i / 4 + 12: four consecutive
+// keys of one dimension.  Reads and their wait are one statement: before the
+// builtin form of this read the compiler waits for every load in flight into
+// LDS, which would empty the ring at each block.
+template <int kSecond>
+__device__ __forceinline__ void read_pv4(uint32_t vb, int dt0, u32x4* a) {
+  const uint32_t x0 = vb ^ ((dt0 + 0) * 32u), x1 = vb ^ ((dt0 + 1) * 32u);
+  const uint32_t x2 = vb ^ ((dt0 + 2) * 32u), x3 = vb ^ ((dt0 + 3) * 32u);
+  u32x2 l0, l1, l2, l3, h0, h1, h2, h3;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\t"
+      "ds_read_b64_tr_b16 %3, %9 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\t"
+      "ds_read_b64_tr_b16 %5, %10 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\t"
+      "ds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(l0), "=&v"(h0), "=&v"(l1), "=&v"(h1), "=&v"(l2), "=&v"(h2), "=&v"(l3), "=&v"(h3)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "n"(kSecond)
+      : "memory");
+  a[0] = u32x4{l0.x, l0.y, h0.x, h0.y};
+  a[1] = u32x4{l1.x, l1.y, h1.x, h1.y};
+  a[2] = u32x4{l2.x, l2.y, h2.x, h2.y};
+  a[3] = u32x4{l3.x, l3.y, h3.x, h3.y};
+}
+
+// Max / sum over the four 16-lane rows of a wave (lanes l, l ^ 16, l ^ 32, l ^ 48).
+__device__ __forceinline__ float rows_max(float v) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float rows_sum(float v) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// (a, b) as packed bf16, and what is left of them.
+__device__ __forceinline__ uint32_t take_bf2(float& a, float& b) {
+  const uint32_t w = pack_bf2(a, b);
+  a -= bflo(w);
+  b -= bfhi(w);
+  return w;
+}
+
+// Splits of the call: sequence s has splits [first[s], first[s + 1]) of
+// split_keys keys each.
+struct DecodeSplits {
+  int32_t split_keys;
+  int32_t max_splits;               // records per (sequence, head): the largest split count
+  int32_t first[kMaxSeqs + 1];
+};
+
+// Loads of the split's 32-key block `blk` (of nblk) into a stage: cached
+// rows only (positions below n, `cached` of them from the split's start); the
+// others, and rows on a page outside the pool, read zeros, as do blocks past
+// the split's.  Every wave issues the loads of every step, so the compiler
+// can count the loads in flight.  koff / voff: byte offset
+// in a page of what this lane loads in instruction v of it.
+template <int D>
+__device__ __forceinline__ void issue_block(const DecodeAttnParams& p, int kh, int entry, int cached, int blk, int nblk,
+                                            uint32_t rs, const uint32_t* koff, const uint32_t* voff, u32x4* st) {
+  constexpr int CH = D / 8, IPP = kPage / (64 / CH);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int pg = blk < nblk ? __builtin_amdgcn_readlane(entry, blk * 2 + h) : -1;
+    const int nv = min(kPage, cached - (blk * kBlk + h * kPage));
+    const uint32_t range = pg >= 0 && nv > 0 ? static_cast<uint32_t>(nv - 1) * rs + D * 2 : 0;
+    const int64_t base = (static_cast<int64_t>(max(pg, 0)) * kPage * p.Hkv + kh) * D;
+    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(p.k_plane + base), 0, range, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(p.v_plane + base), 0, range, 0x00020000);
+#pragma unroll
+    for (int v = 0; v < IPP; ++v)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)(st + (h * IPP + v) * 64), 16, koff[v], 0, 0, kAuxStream);
+#pragma unroll
+    for (int v = 0; v < IPP; ++v)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(st + kBlk * CH + (h * IPP + v) * 64), 16, voff[v], 0, 0, kAuxStream);
+  }
+}
+
+template <int D, int kWaves>
+__global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnParams p, RowMap rm, DecodeSplits sp,
+                                                               float* __restrict__ part_o,
+                                                               float* __restrict__ part_ml, int* __restrict__ ctr) {
+  constexpr int kThreads = kWaves * 64;
+  constexpr int CH = D / 8;                     // 16-byte chunks per row
+  constexpr int RPI = 64 / CH;                  // rows per load instruction
+  constexpr int IPP = kPage / RPI;              // load instructions per page
+  constexpr int kStageSlots = kBlk * CH;        // 16-byte slots of a K or V block
+  constexpr int LPH = D / 8;                    // lanes per head in the norm / rotary pass
+  constexpr int HALF = D / 2;
+  constexpr int HPP = kThreads / LPH;           // heads per pass
+  constexpr int kHeadsMax = 10;                 // G <= 8 query heads, K, V
+  constexpr int NPASS = (kHeadsMax + HPP - 1) / HPP;
+  constexpr int DT = D / 16;                    // output tiles
+  // One array: with several, the compiler's alias scopes make LDS reads of a
+  // stage wait for the loads in flight into the other.
+  constexpr int kRingSlots = kWaves * kStages * 2 * kStageSlots;
+  __shared__ __attribute__((aligned(256))) u32x4 lds[kRingSlots + kHeadsMax * CH + kWaves * 4 + 1];
+  uint16_t(*heads)[D] = reinterpret_cast<uint16_t(*)[D]>(lds + kRingSlots);   // Q heads, then K and V of this row
+  float(*wave_ml)[8][2] = reinterpret_cast<float(*)[8][2]>(lds + kRingSlots + kHeadsMax * CH);
+  int* arrived = reinterpret_cast<int*>(lds + kRingSlots + kHeadsMax * CH + kWaves * 4);
+
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int q4 = lane >> 4, l16 = lane & 15;
+  const int G = p.Hq / p.Hkv;
+  const int kh = static_cast<int>(blockIdx.x) % p.Hkv, u = static_cast<int>(blockIdx.x) / p.Hkv;
+  int s = 0, hi = rm.n_seqs - 1;                // largest s with first[s] <= u
+  while (s < hi) {
+    const int mid = (s + hi + 1) >> 1;
+    if (sp.first[mid] <= u) s = mid; else hi = mid - 1;
+  }
+  const int split = u - sp.first[s], nsplit = sp.first[s + 1] - sp.first[s];
+  const int n = rm.base_pos[s], row = rm.cu[s];
+  const int j0 = split * sp.split_keys;
+  const int j1 = min(j0 + sp.split_keys, n + 1);
+  const bool last = split == nsplit - 1;        // holds position n
+  const int32_t* bt = p.bt + static_cast<int64_t>(s) * p.max_pages;
+
+  // This split's table entries, one per lane (split_keys <= 64 pages).
+  int entry = -1;
+  {
+    const int pi = j0 / kPage + lane;
+    if (pi * kPage < j1) entry = bt[pi];
+    if (entry < 0 || entry >= p.num_pages) entry = -1;
+  }
+  // The row's Q heads (and K and V heads): a lane owns rotary pairs 4 j .. 4 j + 3.
+  const int j = t % LPH, hsub = t / LPH;
+  u32x2 lov[NPASS], hiv[NPASS];
+#pragma unroll
+  for (int ps = 0; ps < NPASS; ++ps) {
+    const int hs = ps * HPP + hsub;
+    lov[ps] = hiv[ps] = u32x2{0, 0};
+    if (hs < G + (last ? 2 : 0)) {
+      const int hh = hs < G ? kh * G + hs : p.Hq + (hs - G) * p.Hkv + kh;
+      const uint16_t* src = p.qkv + static_cast<int64_t>(row) * p.qkv_ld + static_cast<int64_t>(hh) * D;
+      lov[ps] = *reinterpret_cast<const u32x2*>(src + 4 * j);
+      hiv[ps] = *reinterpret_cast<const u32x2*>(src + HALF + 4 * j);
+    }
+  }
+  // Gains of Q and K and the rotary factors: loaded, and waited for with the
+  // table entries, before the K/V stream (loads return in order).
+  u32x2 gq[2] = {}, gk[2] = {};
+  if (p.qk_norm) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      gq[e] = *reinterpret_cast<const u32x2*>(p.q_gain + e * HALF + 4 * j);
+      gk[e] = *reinterpret_cast<const u32x2*>(p.k_gain + e * HALF + 4 * j);
+    }
+  }
+  const f32x4* rope = reinterpret_cast<const f32x4*>(p.rope + (static_cast<int64_t>(row) * HALF + 4 * j) * 2);
+  f32x4 cs01 = rope[0], cs23 = rope[1];         // (cos, sin) of pairs 4j .. 4j+3
+#pragma unroll
+  for (int ps = 0; ps < NPASS; ++ps) asm volatile("" : "+v"(lov[ps]), "+v"(hiv[ps]));
+  asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry));
+
+  // Wave w walks blocks w, w + 2, ... of the split.
+  const int nblk = (j1 - j0 + kBlk - 1) / kBlk;
+  const int nb = wave < nblk ? (nblk - wave + kWaves - 1) / kWaves : 0;
+  u32x4* const myring = lds + wave * kStages * 2 * kStageSlots;   // [stage][K, V]
+  const uint32_t rs = static_cast<uint32_t>(p.Hkv) * D * 2;   // bytes between tokens of a page
+  // Byte offset in a page of what this lane loads in instruction v of it.
+  uint32_t koff[IPP], voff[IPP];
+#pragma unroll
+  for (int v = 0; v < IPP; ++v) {
+    const int r = v * RPI + lane / CH;
+    koff[v] = r * rs + static_cast<uint32_t>(((lane % CH) ^ swz_k<CH>(r)) * 16);
+    voff[v] = r * rs + static_cast<uint32_t>(((lane % CH) ^ swz_v<CH>(r)) * 16);
+  }
+  constexpr int kLoads = 4 * IPP;               // load instructions per block
+  issue_block<D>(p, kh, entry, n - j0, wave, nblk, rs, koff, voff, myring);
+  issue_block<D>(p, kh, entry, n - j0, wave + kWaves, nblk, rs, koff, voff, myring + 2 * kStageSlots);
+
+  // QK-norm and rotary of Q (and, in the last split, of K).
+#pragma unroll
+  for (int ps = 0; ps < NPASS; ++ps) {
+    const int hs = ps * HPP + hsub;
+    if (hs >= G + (last ? 2 : 0)) continue;
+    u32x2 olo = lov[ps], ohi = hiv[ps];
+    if (hs <= G) {
+      float x0[4] = {bflo(olo.x), bfhi(olo.x), bflo(olo.y), bfhi(olo.y)};
+      float x1[4] = {bflo(ohi.x), bfhi(ohi.x), bflo(ohi.y), bfhi(ohi.y)};
+      if (p.qk_norm) {
+        float ss = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
+        if constexpr (LPH == 16) {
+          ss = row16_sum(ss);
+        } else {
+#pragma unroll
+          for (int o = LPH / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, kWave);
+        }
+        const float inv = rsqrtf(ss / D + p.eps);
+        const u32x2 g0 = hs < G ? gq[0] : gk[0], g1 = hs < G ? gq[1] : gk[1];
+        const float ga[4] = {bflo(g0.x), bfhi(g0.x), bflo(g0.y), bfhi(g0.y)};
+        const float gb[4] = {bflo(g1.x), bfhi(g1.x), bflo(g1.y), bfhi(g1.y)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x0[e] = x0[e] * inv * ga[e];
+          x1[e] = x1[e] * inv * gb[e];
+        }
+      }
+      const float cs[4] = {cs01.x, cs01.z, cs23.x, cs23.z};
+      const float sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
+      float y0[4], y1[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y0[e] = x0[e] * cs[e] - x1[e] * sn[e];
+        y1[e] = x1[e] * cs[e] + x0[e] * sn[e];
+      }
+      olo = u32x2{pack_bf2(y0[0], y0[1]), pack_bf2(y0[2], y0[3])};
+      ohi = u32x2{pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3])};
+    }
+    *reinterpret_cast<u32x2*>(&heads[hs][4 * j]) = olo;
+    *reinterpret_cast<u32x2*>(&heads[hs][HALF + 4 * j]) = ohi;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  bf16x8 qf[D / 32];
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk)
+    qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&heads[l16 % G][kk * 32 + q4 * 8]));
+
+  // Slot in a K block (row l16, chunk q4) and byte offset in a V block (key
+  // 4 q4 + l16 / 4, dimensions 4 (l16 % 4) ..): substep kk is XOR 4 kk,
+  // output tile dt XOR 32 dt, the block's second page + 16 rows.
+  const uint32_t kb0 = static_cast<uint32_t>(l16 * CH + (q4 ^ swz_k<CH>(l16)));
+  const int vkey = 4 * q4 + (l16 >> 2);
+  const uint32_t vb0 = static_cast<uint32_t>(vkey * D * 2 + ((swz_v<CH>(vkey) | ((l16 & 3) >> 1)) * 16) + (l16 & 1) * 8);
+
+  f32x4 acc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x4{};
+  float m = -INFINITY, lsum = 0.f;
+
+  for (int i = 0; i < nb; ++i) {
+    u32x4* const Kst = myring + (i % kStages) * 2 * kStageSlots;
+    u32x4* const Vst = Kst + kStageSlots;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");   // this block is here, the next may not be
+    const int blk = wave + i * kWaves, jb = j0 + blk * kBlk;
+    const int pg0 = __builtin_amdgcn_readlane(entry, blk * 2), pg1 = __builtin_amdgcn_readlane(entry, blk * 2 + 1);
+    if (n - jb < kBlk) {
+      // Position n is in this block: its K and V come from this row.
+      const int r = n - jb;
+      if (lane < 2 * CH) {
+        const int c = lane % CH;
+        const bool isk = lane < CH;
+        const u32x4 x = *reinterpret_cast<const u32x4*>(&heads[isk ? G : G + 1][c * 8]);
+        if (isk) Kst[r * CH + (c ^ swz_k<CH>(r))] = x;
+        else Vst[r * CH + (c ^ swz_v<CH>(r))] = x;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    f32x4 sc[2] = {f32x4{}, f32x4{}};
+#pragma unroll
+    for (int kk = 0; kk < D / 32; ++kk)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bf16x8 a = __builtin_bit_cast(
+            bf16x8, Kst[(kb0 ^ (kk * 4u)) + h * (kPage * CH)]);
+        sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[kk], sc[h], 0, 0, 0);
+      }
+    u32x4 va[DT];
+    const uint32_t vst = vb0 + static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)Vst));
+#pragma unroll
+    for (int dt = 0; dt < DT; dt += 4) read_pv4<kPage * D * 2>(vst, dt, va + dt);
+    float pr[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pr[h * 4 + r] = sc[h][r] * p.scale_log2;
+    if (n - jb < kBlk - 1 || pg0 < 0 || pg1 < 0) {
+      // Keys past n, and keys on a page outside the pool.
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (jb + h * kPage + 4 * q4 + r > n || (h ? pg1 : pg0) < 0) pr[h * 4 + r] = -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(fmaxf(pr[0], pr[1]), fmaxf(pr[2], pr[3])), fmaxf(fmaxf(pr[4], pr[5]), fmaxf(pr[6], pr[7])));
+    mx = rows_max(mx);
+    if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+      const float m_new = fmaxf(m, mx);
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+      m = m_new;
+      lsum *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
+    }
+    const float mc = m == -INFINITY ? 0.f : m;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      pr[e] = __builtin_amdgcn_exp2f(pr[e] - mc);
+      lsum += pr[e];
+    }
+    bf16x8 pb[3];
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = take_bf2(pr[2 * e], pr[2 * e + 1]);
+      pb[part] = __builtin_bit_cast(bf16x8, w);
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int part = 2; part >= 0; --part)
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va[dt]), pb[part], acc[dt], 0, 0, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this block's LDS reads are done
+    issue_block<D>(p, kh, entry, n - j0, blk + kStages * kWaves, nblk, rs, koff, voff, Kst);
+  }
+  lsum = rows_sum(lsum);
+
+  if (last && t < 2 * CH) {
+    // K and V of position n (stored here: a store pending in the loop would
+    // make its waits drain every load).
+    const int pg = __builtin_amdgcn_readlane(entry, (n - j0) / kPage);
+    if (pg >= 0) {
+      uint16_t* dst = (t < CH ? p.k_plane : p.v_plane) +
+                      ((static_cast<int64_t>(pg) * kPage + n % kPage) * p.Hkv + kh) * D + (t % CH) * 8;
+      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&heads[t < CH ? G : G + 1][(t % CH) * 8]);
+    } else if (t % CH == 0 && p.err) {
+      atomicOr(p.err, static_cast<int32_t>(PALLAS_DEVERR_PAGE));
+    }
+  }
+
+  // Merge the waves through LDS (the first stage is free once both are here
+  // and nothing is in flight): om[wave][head][dim].
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  float* om = reinterpret_cast<float*>(lds);
+  if (l16 < G) {
+    float* dst = om + (wave * 8 + l16) * D + 4 * q4;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + dt * 16) = acc[dt];
+    if (q4 == 0) {
+      wave_ml[wave][l16][0] = m;
+      wave_ml[wave][l16][1] = lsum;
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  const int quads = G * D / 4;                  // 4-wide output groups of this KV head
+  uint16_t* orow = p.o + (static_cast<int64_t>(row) * p.Hq + kh * G) * D;
+  auto store_out = [&](int e, f32x4 v, float l) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v[x] = l > 0.f ? v[x] / l : 0.f;
+    u32x2 w;
+    w.x = pack_bf2(v[0], v[1]);
+    w.y = pack_bf2(v[2], v[3]);
+    *reinterpret_cast<u32x2*>(orow + e * 4) = w;
+  };
+  const int64_t rec0 = (static_cast<int64_t>(s) * p.Hkv + kh) * sp.max_splits;   // this (sequence, KV head)'s records
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(part_o + rec0 * G * D), 0, static_cast<uint32_t>(sp.max_splits * G * D * 4), 0x00020000);
+  float* ml = part_ml + rec0 * G * 2;           // [split][head][max, sum]
+  for (int e = t; e < quads; e += kThreads) {
+    const int g = e / (D / 4), dv = (e % (D / 4)) * 4;
+    float mm = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, wave_ml[w][g][0]);
+    f32x4 v = {};
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float ww = mm == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wave_ml[w][g][0] - mm);
+      l += ww * wave_ml[w][g][1];
+      v += ww * *reinterpret_cast<const f32x4*>(om + (w * 8 + g) * D + dv);
+    }
+    if (nsplit == 1) {
+      store_out(e, v, l);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, (split * G * D + e * 4) * 4, 0, kAuxAgent);
+      if (dv == 0) {
+        __hip_atomic_store(ml + (split * G + g) * 2, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(ml + (split * G + g) * 2 + 1, l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  if (nsplit == 1) return;
+  // Every wave's records have reached the device-coherent level (agent-scope
+  // stores write through; vmcnt 0), then the count goes up; the last of the
+  // (sequence, KV head) reads the others' past its own L2.
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  int* cnt = ctr + s * p.Hkv + kh;
+  if (t == 0) *arrived = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (*arrived != nsplit - 1) return;
+  if (t == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // All records of a batch of splits are in flight at once, for both of this
+  // thread's output groups.
+  constexpr int E = (8 * D / 4 + kThreads - 1) / kThreads, U = E == 1 ? kMergeBatch : kMergeBatch / 2;
+  const __amdgpu_buffer_rsrc_t rml = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)ml, 0, static_cast<uint32_t>(nsplit * G * 8), 0x00020000);
+  float mm[E], l[E];
+  f32x4 v[E];
+#pragma unroll
+  for (int x = 0; x < E; ++x) {
+    mm[x] = -INFINITY;
+    l[x] = 0.f;
+    v[x] = f32x4{};
+  }
+  for (int k0 = 0; k0 < nsplit; k0 += U) {
+    f32x4 o[E][U];
+    u32x2 a[E][U];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int x = 0; x < E; ++x) {
+        const int e = x * kThreads + t, g = e / (D / 4);
+        const bool in = k0 + k < nsplit && e < quads;      // else: reads zeros
+        a[x][k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+            rml, in ? ((k0 + k) * G + g) * 8 : 0xFFFFFFF0u, 0, kAuxAgent));
+        o[x][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+            ro, in ? ((k0 + k) * G * D + e * 4) * 4 : 0xFFFFFFF0u, 0, kAuxAgent));
+      }
+#pragma unroll
+    for (int x = 0; x < E; ++x) {
+      float m_new = mm[x];
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (k0 + k < nsplit) m_new = fmaxf(m_new, __uint_as_float(a[x][k].x));
+      if (m_new == -INFINITY) continue;
+      const float w0 = __builtin_amdgcn_exp2f(mm[x] - m_new);
+      mm[x] = m_new;
+      l[x] *= w0;
+      v[x] *= w0;
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (k0 + k < nsplit) {
+          const float w = __builtin_amdgcn_exp2f(__uint_as_float(a[x][k].x) - m_new);
+          l[x] += w * __uint_as_float(a[x][k].y);
+          v[x] += w * o[x][k];
+        }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < E; ++x)
+    if (x * kThreads + t < quads) store_out(x * kThreads + t, v[x], l[x]);
+}
+
+}  // namespace
+
+// Keys per split and waves per workgroup.
+//   The last arriver reads its records in batches of kMergeBatch, a memory
+// round trip each, so a sequence gets at most that many splits; below that,
+// 128 keys (at one sequence of the large model's layer: 1000 keys in 8 splits
+// take 10.7 us, in 2 14.5; 4000 keys in 16 14.1, in 32 17.5; 8000 in 16 16.6,
+// in 63 33).
+//   A call of at most one workgroup per CU runs four waves in each (200 keys
+// 8.7 against 9.4 us with two).  Larger calls run two, two workgroups to a CU
+// (their starts and merges overlap the other's stream), with the fewest keys
+// that fill a whole number of rounds: eight sequences of 32,000 keys in all
+// take 32.4 us in 472 workgroups and 36.5 in 536 (512 run at once).
+constexpr int kCus = 256;
+
+hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, float* part, int part_splits,
+                                   hipStream_t s) {
+  if (p.Hq % p.Hkv != 0 || p.page != kPage || rm.n_seqs < 1 || rm.n_seqs > kMaxSeqs) return hipErrorInvalidValue;
+  const int G = p.Hq / p.Hkv;
+  if (G > 8 || (G & (G - 1)) != 0) return hipErrorInvalidValue;
+  for (int i = 0; i < rm.n_seqs; ++i)
+    if (rm.base_pos[i] < 0) return hipErrorInvalidValue;
+  auto splits = [&](int keys) {
+    int64_t c = 0;
+    for (int i = 0; i < rm.n_seqs; ++i) c += rm.base_pos[i] / keys + 1;
+    return c;
+  };
+  DecodeSplits sp;
+  int nmax = 0;
+  for (int i = 0; i < rm.n_seqs; ++i) nmax = std::max(nmax, rm.base_pos[i]);
+  sp.split_keys = (nmax / kMergeBatch + kDecodeMinSplit) / kDecodeMinSplit * kDecodeMinSplit;
+  if (sp.split_keys > kDecodeMaxSplit) return hipErrorInvalidValue;
+  const bool wide = splits(sp.split_keys) * p.Hkv <= kCus;
+  if (!wide) {
+    const int64_t round = 2 * kCus, want = (splits(kDecodeMaxSplit) * p.Hkv + round - 1) / round * round;
+    while (sp.split_keys < kDecodeMaxSplit && splits(sp.split_keys) * p.Hkv > want) sp.split_keys += 2 * kBlk;
+  }
+  sp.first[0] = 0;
+  sp.max_splits = 1;
+  for (int i = 0; i < rm.n_seqs; ++i) {
+    const int c = rm.base_pos[i] / sp.split_keys + 1;
+    sp.first[i + 1] = sp.first[i] + c;
+    sp.max_splits = std::max(sp.max_splits, c);
+  }
+  // Records of sp.max_splits splits in a section sized for part_splits ones
+  // of 64 keys: counters, then outputs, then maxima and sums.
+  const DecodeAttnScratch sc = decode_attn_scratch(rm.n_seqs, p.Hq, p.Hkv, p.d, part_splits);
+  if (sp.max_splits > 1 && sp.max_splits > sc.max_splits) return hipErrorInvalidValue;
+  int* ctr = reinterpret_cast<int*>(part);
+  float* po = part + sc.out_floats;
+  float* pml = part + sc.ml_floats;
+  const int grid = sp.first[rm.n_seqs] * p.Hkv;
+  if (p.d == 128 && wide) attn_decode_kernel<128, 4><<<grid, 256, 0, s>>>(p, rm, sp, po, pml, ctr);
+  else if (p.d == 128) attn_decode_kernel<128, 2><<<grid, 128, 0, s>>>(p, rm, sp, po, pml, ctr);
+  else if (p.d == 64 && wide) attn_decode_kernel<64, 4><<<grid, 256, 0, s>>>(p, rm, sp, po, pml, ctr);
+  else if (p.d == 64) attn_decode_kernel<64, 2><<<grid, 128, 0, s>>>(p, rm, sp, po, pml, ctr);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace pallas

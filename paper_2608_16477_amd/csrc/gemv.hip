@@ -243,9 +243,10 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(const uint16_t* __restri
   }
 }
 
-__global__ void fill_zero_kernel(int* __restrict__ p, int n) {
+__global__ void fill_zero_kernel(int* __restrict__ a, int na, int* __restrict__ b, int nb) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+  if (i < na) a[i] = 0;
+  else if (i - na < nb) b[i - na] = 0;
 }
 
 }  // namespace
@@ -276,9 +277,9 @@ int gemv_ksplit(int epi, int N, int K) {
   return best;
 }
 
-hipError_t launch_zero_counters(int* ctr, int n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  fill_zero_kernel<<<(n + 255) / 256, 256, 0, s>>>(ctr, n);
+hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s) {
+  if (na + nb <= 0) return hipSuccess;
+  fill_zero_kernel<<<(na + nb + 255) / 256, 256, 0, s>>>(a, na, b, nb);
   return hipGetLastError();
 }
 

@@ -230,12 +230,48 @@ inline size_t attn_prefill_split_bytes(int rows, int Hq, int d) {
 // attn_prefill_split_bytes) is used when the call splits its key ranges.
 hipError_t launch_attention_prefill(const AttnParams& p, const RowMap& rm, float* part, size_t part_bytes,
                                     hipStream_t s);
-// Decode attention: one row per sequence at position base_pos[s], keys
-// [0, base_pos[s]] through the table, split in runs of 64 keys.  `partial`
-// holds [n_seqs][Hq][max_splits][d + 2] floats; needs
-// base_pos[s] / 64 < max_splits and Hq / Hkv <= 8.
-hipError_t launch_attention_decode(const AttnParams& p, const RowMap& rm, float* partial,
-                                   int max_splits, hipStream_t s);
+// Decode attention and what precedes it: QK-norm and rotary of the row's Q and
+// K, the store of its K and V into slot base_pos[s], then attention over keys
+// [0, base_pos[s]] through the table (rows on pages outside the pool masked).
+struct DecodeAttnParams {
+  const uint16_t* qkv;     // [rows][qkv_ld]: Q heads, K heads, V heads
+  int qkv_ld;
+  const uint16_t* q_gain;  // [d] or null
+  const uint16_t* k_gain;  // [d] or null
+  const float* rope;       // [rows][d/2][2]
+  float eps;
+  int qk_norm;
+  uint16_t* k_plane;       // [P][page][Hkv][d]
+  uint16_t* v_plane;
+  const int32_t* bt;
+  int max_pages, num_pages, page;
+  uint16_t* o;             // [rows][Hq * d]
+  int Hq, Hkv, d;
+  float scale_log2;        // log2(e) / sqrt(d)
+  int32_t* err;
+};
+// Splits of at least kDecodeMinSplit keys, in a section of [n_seqs][Hq]
+// [part_splits][d + 2] floats, part_splits = largest position / 64 + 1:
+// arrival counters (zero on entry, left zero), outputs [n_seqs][Hkv][split]
+// [G][d], then maxima and sums.  With fewer than two splits nothing is used;
+// otherwise half the records leave room for the counters.
+constexpr int kDecodeMinSplit = 128;
+constexpr int kDecodeMaxSplit = 1024;   // a split's table entries: one per lane
+struct DecodeAttnScratch {
+  int max_splits;          // splits per sequence that fit
+  int counters;            // ints to clear at the start of the section
+  size_t out_floats, ml_floats;
+};
+inline DecodeAttnScratch decode_attn_scratch(int n_seqs, int Hq, int Hkv, int d, int part_splits) {
+  DecodeAttnScratch s;
+  s.max_splits = (part_splits + 1) / 2;
+  s.counters = s.max_splits > 1 ? n_seqs * Hkv : 0;
+  s.out_floats = (size_t(n_seqs) * Hkv + 63) / 64 * 64;
+  s.ml_floats = s.out_floats + size_t(n_seqs) * Hq * s.max_splits * d;
+  return s;
+}
+hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, float* part,
+                                   int part_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM
 // C[m][n] (op) A[m] . B[n] for m < M <= 8 rows; epilogues as launch_gemm.
@@ -248,7 +284,7 @@ int gemv_ksplit(int epi, int N, int K);
 hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C,
                        int ldc, int M, int N, int K, float* part, size_t part_bytes, int* ctr,
                        int ctr_count, hipStream_t s);
-// ctr[0..n) = 0 (a kernel, so it can sit in a captured graph).
-hipError_t launch_zero_counters(int* ctr, int n, hipStream_t s);
+// a[0..na) = 0 and b[0..nb) = 0 (a kernel, so it can sit in a captured graph).
+hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s);
 
 }  // namespace pallas

@@ -482,7 +482,6 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   float* r = reinterpret_cast<float*>(ws + w.resid);
   uint16_t* h = reinterpret_cast<uint16_t*>(ws + w.h);
   uint16_t* qkv = reinterpret_cast<uint16_t*>(ws + w.qkv);
-  uint16_t* q = reinterpret_cast<uint16_t*>(ws + w.q);
   uint16_t* o = reinterpret_cast<uint16_t*>(ws + w.o);
   uint16_t* act = reinterpret_cast<uint16_t*>(ws + w.act);
   float* rope = reinterpret_cast<float*>(ws + w.rope);
@@ -493,49 +492,36 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
 
   const ProjScratch sc{split, sb, reinterpret_cast<float*>(ws + w.gemv_part), w.gemv_part_bytes,
                        reinterpret_cast<int*>(ws + w.gemv_ctr), w.gemv_ctr_count};
-  if (hipError_t e = pallas::launch_zero_counters(sc.gv_ctr, sc.gv_ctr_count, s); e != hipSuccess)
+  const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
+  if (hipError_t e = pallas::launch_zero_counters(sc.gv_ctr, sc.gv_ctr_count, reinterpret_cast<int*>(part), as.counters, s);
+      e != hipSuccess)
     return hip_fail(e, "counters");
   PALLAS_TRY(PALLAS_K_ROPE_TABLE, pallas::launch_rope_table(rm, B, d, c.rope_theta, rope, s), "rope table");
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(tokens, u16(m->embed), u16(m->layers[0].attn_norm), r, h, B, H,
                                           c.rms_eps, c.vocab, err, s), "embed");
-  pallas::QkvParams qp;
-  qp.rope = rope;
-  qp.q_out = q;
-  qp.bt = bt;
-  qp.max_pages = max_pages;
-  qp.num_pages = pool->num_pages;
-  qp.page = pool->page_size;
-  qp.Hq = Hq;
-  qp.Hkv = Hkv;
-  qp.d = d;
-  qp.eps = c.rms_eps;
-  qp.qk_norm = c.qk_norm;
-  qp.err = err;
-  qp.qkv = qkv;
-  qp.qkv_ld = QKV;
-  qp.kv_only = 0;
-  pallas::AttnParams ap;
-  ap.q = q;
+  pallas::DecodeAttnParams ap;
+  ap.qkv = qkv;
+  ap.qkv_ld = QKV;
+  ap.rope = rope;
+  ap.eps = c.rms_eps;
+  ap.qk_norm = c.qk_norm;
   ap.bt = bt;
   ap.max_pages = max_pages;
   ap.num_pages = pool->num_pages;
-  ap.plane_bytes = int64_t(pool->num_pages) * pool->page_size * pool->n_kv_heads * pool->head_dim * 2;
   ap.page = pool->page_size;
   ap.o = o;
   ap.Hq = Hq;
   ap.Hkv = Hkv;
   ap.d = d;
   ap.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(double(d)));
+  ap.err = err;
   for (int l = 0; l < c.n_layers; ++l) {
     const pallas_layer_weights& L = m->layers[l];
     const Planes pl = layer_planes(pool, l);
     if (l > 0) PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.attn_norm), h, B, H, c.rms_eps, s), "rmsnorm");
     PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiBf16, h, H, u16(L.w_qkv), H, qkv, QKV, B, QKV, H, sc, s), "qkv proj");
-    qp.q_gain = u16(L.q_norm);
-    qp.k_gain = u16(L.k_norm);
-    qp.k_plane = pl.k;
-    qp.v_plane = pl.v;
-    PALLAS_TRY(PALLAS_K_QKV_EPI, pallas::launch_qkv_rope(qp, rm, B, s), "qkv epilogue");
+    ap.q_gain = u16(L.q_norm);
+    ap.k_gain = u16(L.k_norm);
     ap.k_plane = pl.k;
     ap.v_plane = pl.v;
     PALLAS_TRY(PALLAS_K_DECODE_ATTN, pallas::launch_attention_decode(ap, rm, part, w.part_splits, s), "decode attention");

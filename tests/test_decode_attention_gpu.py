@@ -1,0 +1,100 @@
+"""Decode attention at the sizes where its work split changes, against the
+oracle's decode over the same random caches: 32-key blocks, 128-key splits and
+their multiples, one split (no merge) and sixteen, four-wave and two-wave
+workgroups (at most / more than 256 of them), head_dim 64 and 128, groups of
+1, 2, 4 and 8 query heads.  Unwritten slots hold NaN patterns; table entries
+outside the pool mask their keys.  Residual and logits within
+max|gpu - ref| <= 1e-2 max|ref| per row (the bf16 bound of the other decode
+tests); the K/V written within it too."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import TOL, ensure_lib, gpu_model, oracle_weights, rel_err, residual_rows, shape_of
+from oracle import model as om
+from workloads import configs, gen
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def P():
+    return ensure_lib()
+
+
+CASES = [
+    # head_dim, group, KV heads, positions
+    (128, 8, 2, [0, 1, 31, 32, 33, 127, 128, 129]),
+    (128, 4, 2, [255, 256, 257, 2047, 2048, 2049]),
+    (128, 1, 4, [63, 300, 900, 4000]),
+    (64, 2, 2, [0, 31, 64, 127, 128, 1100]),
+    (64, 8, 1, [500, 2048, 5000]),
+    (128, 8, 8, [1000 + 97 * i for i in range(10)]),     # more than 256 workgroups
+    (64, 4, 8, [700 + 131 * i for i in range(12)]),
+]
+
+
+@pytest.mark.parametrize("d,group,hkv,pos", CASES)
+def test_split_edges(P, d, group, hkv, pos):
+    cfg = configs.TINY.replace(n_layers=1, hidden=256, n_q_heads=group * hkv, n_kv_heads=hkv, head_dim=d, ffn=256,
+                               vocab=512, qk_norm=True, name="edges")
+    glob, layers = gen.model_weights(cfg, seed=61, gain_sigma=0.1)
+    model = gpu_model(P, cfg, glob, layers)
+    pages = [n // 16 + 1 for n in pos]
+    tables = gen.disjoint_block_tables(pages, sum(pages) + 3, max(pages), 61, 1)
+    pool = gen.kv_pool_normal(1, sum(pages) + 3, 16, hkv, d, 61)
+    bad = {}                              # sequence -> a page of it that is not in the pool
+    for i, n in enumerate(pos):
+        slots = torch.arange(n % 16, 16)  # unwritten: quiet NaNs
+        pool.view(torch.int16)[:, :, tables[i, n // 16], slots] = gen.SENTINEL_BITS
+        if n > 400 and i % 2:
+            bad[i] = (n // 16) // 2
+            tables[i, bad[i]] = -1 if i % 4 == 1 else sum(pages) + 3
+    d_pool = pool.to(DEV)
+    ids = gen.token_ids(len(pos), cfg.vocab, seed=61).numpy()
+    logits = torch.empty((len(pos), cfg.vocab), dtype=torch.float32, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = model.workspace(len(pos), len(pos))
+    for _ in range(2):                    # the second step finds what the first left
+        model.decode_step(torch.tensor(ids, dtype=torch.int32, device=DEV), pos,
+                          torch.tensor(tables, device=DEV), d_pool, logits, ws, err)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0           # only the store of slot n reports its page
+    resid = residual_rows(ws, len(pos), cfg.hidden).double().cpu().numpy()
+    got_pool = d_pool.cpu()
+    g, ls = oracle_weights(glob, layers)
+    shp = shape_of(cfg)
+    for i, n in enumerate(pos):
+        keep = [t for t in range(n) if t // 16 != bad.get(i)]
+        pg = tables[i][np.array(keep, dtype=int) // 16] if keep else np.zeros(0, dtype=int)
+        sl = np.array(keep, dtype=int) % 16
+        kv = pool[0][:, torch.as_tensor(pg, dtype=torch.long), torch.as_tensor(sl)].double().numpy()
+        ref, k_new, v_new = om.decode(int(ids[i]), n, [kv[0]], [kv[1]], g, ls, shp)
+        e = rel_err(logits[i].double().cpu().numpy(), ref)
+        assert e <= TOL, f"position {n}: logits rel err {e:.3g}"
+        assert np.isfinite(resid[i]).all()
+        at = got_pool[0][:, tables[i, n // 16], n % 16].double().numpy()
+        assert rel_err(at[0], k_new[0]) <= TOL and rel_err(at[1], v_new[0]) <= TOL
+
+
+def test_slot_outside_the_pool(P):
+    """The page of slot n is not in the pool: nothing is stored, the token does
+    not see its own K/V, and the error word says so."""
+    cfg = configs.TINY.replace(n_layers=1, vocab=512, name="edges")
+    glob, layers = gen.model_weights(cfg, seed=62, gain_sigma=0.1)
+    model = gpu_model(P, cfg, glob, layers)
+    n = 160
+    tables = gen.disjoint_block_tables([11], 16, 11, 62, 1)
+    tables[0, 10] = 16
+    pool = gen.kv_pool_normal(1, 16, 16, cfg.n_kv_heads, cfg.head_dim, 62)
+    d_pool = pool.to(DEV)
+    logits = torch.empty((1, cfg.vocab), dtype=torch.float32, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = model.workspace(1, 1)
+    model.decode_step(torch.tensor([5], dtype=torch.int32, device=DEV), [n], torch.tensor(tables, device=DEV),
+                      d_pool, logits, ws, err)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 1
+    assert torch.equal(d_pool.cpu().view(torch.int16), pool.view(torch.int16))
+    assert torch.isfinite(logits).all()
