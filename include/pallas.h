@@ -278,9 +278,9 @@ int pallas_assemble_kv(const pallas_kv_pool* dst, const int32_t* d_dst_block_tab
  * d_logits[i][0..V).  num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
  * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention keeps one
  * partial record per 64 keys in a workspace section of fixed size), and
- * n_i + 1 <= max_pages * page (OUT_OF_RANGE).  Up to 8 sequences run the
- * skinny projection kernel; more run the MFMA GEMM, whose 2 GiB operand
- * limit (see pallas_prefill_prefix) then also covers lm_head [V][hidden].
+ * n_i + 1 <= max_pages * page (OUT_OF_RANGE).  For more than 8
+ * sequences the 2 GiB operand limit of pallas_prefill_prefix applies, also to
+ * lm_head [V][hidden].
  * Table entries outside [0, num_pages) raise PALLAS_DEVERR_PAGE (the K/V
  * store of slot n_i is skipped; keys on such pages are masked), token ids
  * outside [0, vocab) PALLAS_DEVERR_TOKEN, in *d_err (nullable). */
@@ -398,10 +398,10 @@ double pallas_waste_bound(double t_max, double e_early, double t_avail);
 /* Per-kernel timing (tracing).  Kernel classes of the calls above: */
 typedef enum {
   PALLAS_K_EMBED = 0,      /* token embedding + first RMSNorm */
-  PALLAS_K_RMSNORM = 1,
+  PALLAS_K_RMSNORM = 1,    /* prefill only: decode folds its norms into the projections */
   PALLAS_K_ROPE_TABLE = 2,
   PALLAS_K_GEMM_QKV = 3,   /* prefill Q|K|V projection (K|V only in the last layer) */
-  PALLAS_K_QKV_EPI = 4,    /* QK-norm, rotary, paged K/V store */
+  PALLAS_K_QKV_EPI = 4,    /* prefill QK-norm, rotary, paged K/V store */
   PALLAS_K_ATTN = 5,       /* prefill causal attention */
   PALLAS_K_GEMM_O = 6,     /* prefill output projection + residual */
   PALLAS_K_GEMM_GATE_UP = 7, /* prefill gate|up projection + SwiGLU */
@@ -409,7 +409,7 @@ typedef enum {
   PALLAS_K_PACK = 9,
   PALLAS_K_ASSEMBLE = 10,
   PALLAS_K_DECODE_PROJ = 11, /* decode projections and lm_head */
-  PALLAS_K_DECODE_ATTN = 12,
+  PALLAS_K_DECODE_ATTN = 12, /* with QK-norm, rotary and the K/V store */
   PALLAS_K_COUNT = 13
 } pallas_kernel_class;
 

@@ -43,7 +43,7 @@ constexpr int kPage = 16;        // tokens per cache page (the only page size th
 constexpr int kBoundThreads = 512;
 constexpr int kBlk = 32;         // keys per block: two pages
 constexpr int kStages = 2;       // blocks in flight per wave
-constexpr int kMergeBatch = 16;  // split records read at once by the last arriver
+constexpr int kMergeBatch = kDecodeSplitsPerSeq;   // split records read at once by the last arriver
 constexpr int kAuxAgent = 16;    // buffer cache policy: sc1 (device-coherent)
 constexpr int kAuxStream = 2;    // nt: K and V are read once per step
 

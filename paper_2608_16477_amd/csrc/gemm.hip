@@ -464,13 +464,7 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
         for (int j = 0; j < JN; ++j) {
           const int col = tn * BN + wn * WN + j * 16 + l16e;
           if (col >= p.N) continue;
-          if (EPI == kEpiF32) {
-            float* C = static_cast<float*>(p.C) + static_cast<int64_t>(row) * p.ldc;
-            C[col] = acc[i][j][r];
-          } else {
-            uint16_t* C = static_cast<uint16_t*>(p.C) + static_cast<int64_t>(row) * p.ldc;
-            C[col] = f2bf(acc[i][j][r]);
-          }
+          static_cast<uint16_t*>(p.C)[static_cast<int64_t>(row) * p.ldc + col] = f2bf(acc[i][j][r]);
         }
       }
     }
@@ -526,8 +520,6 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
   if (EPI == kEpiAddF32) {
     f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(C) + static_cast<int64_t>(row) * ldc + c);
     *dst = *dst + a;
-  } else if (EPI == kEpiF32) {
-    *reinterpret_cast<f32x4*>(static_cast<float*>(C) + static_cast<int64_t>(row) * ldc + c) = a;
   } else {
     if (EPI == kEpiSwiGLU) {
 #pragma unroll
@@ -609,7 +601,6 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
     case kEpiBf16: launch_tiles<kEpiBf16>(p, bm, bn, grid, s); break;
     case kEpiAddF32: launch_tiles<kEpiAddF32>(p, bm, bn, grid, s); break;
     case kEpiSwiGLU: launch_tiles<kEpiSwiGLU>(p, bm, bn, grid, s); break;
-    case kEpiF32: launch_tiles<kEpiF32>(p, bm, bn, grid, s); break;
     default: return hipErrorInvalidValue;
   }
   if (p.ksplit > 1) {
@@ -620,7 +611,6 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
       case kEpiBf16: gemm_reduce_kernel<kEpiBf16><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
       case kEpiAddF32: gemm_reduce_kernel<kEpiAddF32><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
       case kEpiSwiGLU: gemm_reduce_kernel<kEpiSwiGLU><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
-      case kEpiF32: gemm_reduce_kernel<kEpiF32><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
     }
   }
   return hipGetLastError();

@@ -1,18 +1,33 @@
-// Skinny GEMM for decode (M <= 8 rows): C = X W^T streaming the weights once.
+// Skinny GEMM for decode (M <= 64 rows): C = X W^T streaming the weights once.
 //
-// A workgroup of 4 waves owns one 16-row weight tile (two for the gate|up
-// projection: 16 gate rows and the matching 16 up rows) and splits K four
-// ways.  Each wave streams its K range in steps of 64: one 128-byte line of
-// each weight row and the matching 64 columns of X go straight from memory
-// into a private LDS stage with buffer_load ... lds (three stages in
-// flight), each load instruction covering whole lines of 8 rows.  Inside a
-// stage the 16-byte slots are permuted so the v_mfma_f32_16x16x32_bf16
-// operand reads (16 rows at one k) hit 16 distinct bank groups.  The four
-// partial tiles are summed through LDS and the epilogue matches the prefill
-// GEMM's.  Launches with fewer than two tiles per CU (O and down) also split
-// K over up to kGemvMaxSplit workgroups per tile: each writes its partial
-// sums with agent-scope stores and counts itself in a per-tile counter, and
-// the last to arrive adds the splits in order and applies the epilogue.
+// A workgroup of 4 waves owns a tile of TN blocks of 16 weight rows (for the
+// gate|up projection half of them gate rows and half the matching up rows)
+// and splits K four ways.  Each wave streams its K range in steps of 64: one
+// 128-byte line of each weight row and the matching 64 columns of X go
+// straight from memory into a private LDS stage with buffer_load ... lds (NS
+// stages in flight), each load instruction covering whole lines of 8 rows.
+// Inside a stage the 16-byte slots are permuted so the
+// v_mfma_f32_16x16x32_bf16 operand reads (16 rows at one k) hit 16 distinct
+// bank groups.  The partial tiles of the waves are summed through LDS.
+// Launches with too few tiles to fill the chip also split K over workgroups:
+// each writes its partial sums with agent-scope stores and counts itself in a
+// per-tile counter, and the last to arrive adds the splits in order and
+// applies the epilogue (gemv_plan chooses TN and the splits).
+//
+// More than 16 rows through a wide weight (gate|up, lm_head) take a second
+// kernel (gemv_stream_kernel): X is then a large part of what a wave has in
+// flight, so four waves share each X stage and stream 128 weight rows past it.
+//
+// Weights are loaded non-temporally: they are read once per step, and the
+// stream runs 10% faster that way (M = 1: gate|up of the mid / large model 36
+// -> 31.7 / 91 -> 83.2 us, lm_head 202 -> 179 us, 6.9 TB/s).
+//
+// RMSNorm is folded into the projections on both sides of it.  The residual
+// projections (O, down) also write x g (the new residual times the next
+// norm's gain, bf16) and the sums of squares of their columns; the projection
+// that follows streams x g and scales its rows by (mean(x^2) + eps)^(-1/2).
+// bf16 rounding is relative, so x g carries the error of x g / rms, and a
+// norm launch of its own (4.6 us, twice per layer) falls away.
 #include <cmath>
 
 #include "common.h"
@@ -24,222 +39,523 @@ namespace {
 
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
-constexpr int kKStep = 64;        // k per stage: one 128-byte line per weight row
+constexpr int kKStep = 64;        // k per stage: one 128-byte line per row
 constexpr int kBlockSlots = 68;   // 8 rows x 8 slots of 16 B, plus 4 slots of padding
+constexpr int kAuxAgent = 16;     // buffer cache policy: sc1 (device-coherent)
+constexpr int kAuxStream = 2;     // nt
+constexpr uint32_t kOob = 0xFFFFFFF0u;
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-template <int TILES>
-struct GvLayout {
-  static constexpr int kStages = 3;                                   // stages in flight per wave
-  static constexpr int kWBlocks = 2 * TILES;                          // 8-row blocks per stage
-  static constexpr int kStageSlots = kWBlocks * kBlockSlots + 64;     // + one X block
-  static constexpr int kWaveSlots = kStages * kStageSlots;
-  static constexpr int kLoads = kWBlocks + 1;                         // load instructions per stage
-};
-
-// Weight block slot of (row rr in 0..7, 16-byte chunk c in 0..7).
-__device__ __forceinline__ int wslot(int rr, int c) {
+// Block slot of (row rr in 0..7, 16-byte chunk c in 0..7).
+__device__ __forceinline__ int bslot(int rr, int c) {
   return (rr & 3) + 8 * (rr >> 2) + 4 * (c & 1) + 16 * (c >> 1);
 }
-// X block slot of (row r in 0..7, chunk c in 0..7).
-__device__ __forceinline__ int xslot(int r, int c) { return r * 8 + (c ^ r); }
 
-// K split over workgroups: workgroup (tile, ks) covers K range ks of S and
-// writes float32 partial sums to part[ks][m][B row]; the last workgroup of
-// a tile to finish (an atomic count in ctr[tile], which it resets to 0)
-// adds the S partials in order and applies the epilogue.
-struct GemvSplit {
-  int S;
-  float* part;   // [S][M][B rows]
-  int* ctr;      // [tiles], zero on entry
-  int nrows;     // B rows: N, or 2N for gate|up
+struct GemvArgs {
+  const uint16_t* X;
+  const uint16_t* W;
+  void* C;
+  int ldx, ldw, ldc, M, N, K;
+  int S;          // K splits over workgroups
+  int tiles, ksteps;   // stream kernel: 128-row tiles, K / 64 rounded up
+  float* part;    // partial tiles
+  int* ctr;       // [tiles] (stream kernel: [tiles][wave]), zero on entry
+  GemvNorm nrm;
 };
 
-template <int EPI, int TILES>
-__global__ __launch_bounds__(kThreads) void gemv_kernel(const uint16_t* __restrict__ X, int ldx,
-                                                        const uint16_t* __restrict__ W, int ldw,
-                                                        void* __restrict__ C, int ldc, int M, int N,
-                                                        int K, GemvSplit sp) {
-  using L = GvLayout<TILES>;
-  __shared__ __attribute__((aligned(16))) u32x4 lds[kWaves * L::kWaveSlots];
+// Sums of squares of X's rows ([part][kMpad], four rows per thread): the first
+// loads of a thread, started early and not waited for until finish(), then
+// (mean(x^2) + eps)^(-1/2) per row.
+template <int kMpad>
+struct RowScale {
+  static constexpr int kQ = kMpad / 4;
+  static constexpr int U = 4;
+  u32x4 x[U];
+  __device__ __forceinline__ void load(const GemvNorm& n) {
+    const uint32_t bytes = n.ssq_in ? static_cast<uint32_t>(n.parts_in) * (kMpad * 4) : 0;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)n.ssq_in, 0, bytes, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < U; ++u)   // past the end: zeros
+      x[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (threadIdx.x + u * kThreads) * 16u, 0, 0));
+  }
+  // Into row_inv[kMpad] through scratch [kWaves][kQ]; every thread calls it.
+  // Read row_inv after a barrier.
+  __device__ __forceinline__ void finish(const GemvNorm& n, int K, f32x4* scratch, float* row_inv) {
+    if (!n.ssq_in) return;
+    f32x4 v = {};
+#pragma unroll
+    for (int u = 0; u < U; ++u) v += __builtin_bit_cast(f32x4, x[u]);
+    for (int i = threadIdx.x + U * kThreads; i < n.parts_in * kQ; i += kThreads)
+      v += reinterpret_cast<const f32x4*>(n.ssq_in)[i];
+#pragma unroll
+    for (int o = 32; o >= kQ; o >>= 1)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], o, kWave);
+    if ((threadIdx.x & 63) < kQ) scratch[(threadIdx.x >> 6) * kQ + (threadIdx.x & 63)] = v;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (threadIdx.x < kMpad) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) s += reinterpret_cast<const float*>(scratch + w * kQ)[threadIdx.x];
+      row_inv[threadIdx.x] = rsqrtf(s / K + n.eps);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
+};
+
+// XB: 8-row blocks of X (M <= 8 XB); NS: stages in flight per wave.
+template <int EPI, int TN, int XB, int NS>
+__global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
+  constexpr int TM = (XB + 1) / 2;                // 16-row blocks of X
+  constexpr int kBlocks = 2 * TN + XB;            // load instructions per stage
+  constexpr int kStageSlots = kBlocks * kBlockSlots;
+  constexpr int HT = TN > 1 ? TN / 2 : 1;         // gate|up: gate blocks of a tile
+  constexpr int kRing = kWaves * NS * kStageSlots;
+  constexpr int kRed = kWaves * TN * TM * 64;     // partial tiles
+  // (one array: see the decode attention kernel's note on LDS waits)
+  constexpr int kMain = kRing > kRed ? kRing : kRed;
+  constexpr int kMpad = 8 * XB;
+  using Scale = RowScale<kMpad>;
+  __shared__ __attribute__((aligned(16))) u32x4 lds[kMain + (kWaves + 1) * Scale::kQ + 1];
+  f32x4* const scratch = reinterpret_cast<f32x4*>(lds + kMain);
+  float* const row_inv = reinterpret_cast<float*>(lds + kMain + kWaves * Scale::kQ);   // [kMpad]
+  int* const arrived = reinterpret_cast<int*>(lds + kMain + (kWaves + 1) * Scale::kQ);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int li = lane & 15, kg = lane >> 4;
-  const int tile = static_cast<int>(blockIdx.x) / sp.S, ks = static_cast<int>(blockIdx.x) % sp.S;
+  const int tile = static_cast<int>(blockIdx.x) / p.S, ks = static_cast<int>(blockIdx.x) % p.S;
+  const int M = p.M, N = p.N;
 
-  // Weight tiles: first row and valid row count.
-  int trow[TILES], tvalid[TILES];
-  if (EPI == kEpiSwiGLU) {
-    const int o0 = tile * 16;
-    trow[0] = o0;
-    trow[TILES - 1] = N + o0;
-    tvalid[0] = tvalid[TILES - 1] = min(16, N - o0);
-  } else {
-#pragma unroll
-    for (int t = 0; t < TILES; ++t) {
-      trow[t] = (tile * TILES + t) * 16;
-      // The same in every lane: keeps the descriptors in scalar registers.
-      tvalid[t] = __builtin_amdgcn_readfirstlane(max(0, min(16, N - trow[t])));
-    }
-  }
-  auto tile_rsrc = [&](int t) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(W + static_cast<int64_t>(tvalid[t] > 0 ? trow[t] : 0) * ldw), 0,
-                                             static_cast<uint32_t>(tvalid[t]) * ldw * 2u, 0x00020000);
-  };
-  const __amdgpu_buffer_rsrc_t rw0 = tile_rsrc(0), rw1 = tile_rsrc(TILES - 1);
-  const __amdgpu_buffer_rsrc_t rx =
-      __builtin_amdgcn_make_buffer_rsrc((void*)X, 0, static_cast<uint32_t>(M) * ldx * 2u, 0x00020000);
-  constexpr uint32_t kOob = 0xFFFFFFF0u;
+  // First weight row of block t, and its first output column.
+  auto col0 = [&](int t) { return EPI == kEpiSwiGLU ? (tile * HT + t % HT) * 16 : (tile * TN + t) * 16; };
+  auto wrow = [&](int t) { return (EPI == kEpiSwiGLU && t >= HT ? N : 0) + col0(t); };
 
   // This workgroup's K range [kw0, kw1), then a quarter of it per wave.
-  const int kper = ((K + sp.S * kKStep - 1) / (sp.S * kKStep)) * kKStep;
-  const int kw0 = ks * kper, kw1 = min(K, kw0 + kper);
+  const int kper = ((p.K + p.S * kKStep - 1) / (p.S * kKStep)) * kKStep;
+  const int kw0 = ks * kper, kw1 = min(p.K, kw0 + kper);
   const int kslice = ((max(kw1 - kw0, 0) + kWaves * kKStep - 1) / (kWaves * kKStep)) * kKStep;
   const int kb = kw0 + wave * kslice, ke = min(kw1, kb + kslice);
   const int nst = ke > kb ? (ke - kb + kKStep - 1) / kKStep : 0;
 
-  // Per-lane load coordinates (fixed for every stage).
-  // Weight block instruction: lane -> slot lane -> (row rr, chunk c).
+  // Load coordinates: a block instruction has lane -> slot lane -> (row rr, chunk c).
   const int b = lane & 15;
-  const int w_rr = (b & 3) | ((b >> 3) << 2);
-  const int w_c = ((lane >> 4) << 1) | ((b >> 2) & 1);
-  // X block instruction: lane -> row lane/8, chunk (lane%8) ^ row.
-  const int x_r = lane >> 3;
-  const int x_c = (lane & 7) ^ x_r;
+  const int rr = (b & 3) | ((b >> 3) << 2);
+  const int lc = ((lane >> 4) << 1) | ((b >> 2) & 1);
+  const uint32_t woff = static_cast<uint32_t>(rr) * p.ldw * 2u + lc * 16u;
+  const uint32_t xoff = static_cast<uint32_t>(rr) * p.ldx * 2u + lc * 16u;
+  const __amdgpu_buffer_rsrc_t rx =
+      __builtin_amdgcn_make_buffer_rsrc((void*)p.X, 0, static_cast<uint32_t>(M) * p.ldx * 2u, 0x00020000);
 
-  u32x4* wbase = lds + wave * L::kWaveSlots;
+  u32x4* const wbase = lds + wave * NS * kStageSlots;
   auto issue = [&](int s) {
     const int k0 = kb + s * kKStep;
-    u32x4* st = wbase + (s % L::kStages) * L::kStageSlots;
+    u32x4* st = wbase + (s % NS) * kStageSlots;
+    const bool in = k0 + lc * 8 < ke;
+    const uint32_t ko = static_cast<uint32_t>(k0) * 2u;
 #pragma unroll
-    for (int blk = 0; blk < L::kWBlocks; ++blk) {
-      const int t = blk >> 1;
-      const int row = (blk & 1) * 8 + w_rr;
-      const int k = k0 + w_c * 8;
-      const uint32_t off = k < ke ? static_cast<uint32_t>(row) * ldw * 2u + static_cast<uint32_t>(k) * 2u : kOob;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(t == 0 ? rw0 : rw1, (lds_void*)(st + blk * kBlockSlots), 16, off, 0, 0, 0);
+    for (int t = 0; t < TN; ++t) {
+      // Rows past N: the buffer range ends before them (the count is the
+      // same in every lane; kept scalar, so the descriptors are).
+      const int valid = __builtin_amdgcn_readfirstlane(max(0, min(16, N - col0(t))));
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(p.W + static_cast<int64_t>(valid > 0 ? wrow(t) : 0) * p.ldw), 0,
+          static_cast<uint32_t>(valid) * p.ldw * 2u, 0x00020000);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + (2 * t + h) * kBlockSlots), 16,
+                                                 in ? woff + ko + h * 8u * p.ldw * 2u : kOob, 0, 0, kAuxStream);
     }
-    const int k = k0 + x_c * 8;
-    const uint32_t off = (x_r < M && k < ke) ? static_cast<uint32_t>(x_r) * ldx * 2u + static_cast<uint32_t>(k) * 2u : kOob;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + L::kWBlocks * kBlockSlots), 16, off, 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < XB; ++x)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + (2 * TN + x) * kBlockSlots), 16,
+                                               in ? xoff + ko + x * 8u * p.ldx * 2u : kOob, 0, 0, 0);
   };
 
-  f32x4 acc[TILES];
+  f32x4 acc[TN][TM];
 #pragma unroll
-  for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0, 0, 0, 0};
+  for (int t = 0; t < TN; ++t)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[t][i] = f32x4{0, 0, 0, 0};
   auto compute = [&](int s) {
-    const u32x4* st = wbase + (s % L::kStages) * L::kStageSlots;
+    const u32x4* st = wbase + (s % NS) * kStageSlots;
 #pragma unroll
     for (int q = 0; q < kKStep / 32; ++q) {
-      const int c = 4 * q + kg;
-      const bf16x8 a = __builtin_bit_cast(bf16x8, st[L::kWBlocks * kBlockSlots + xslot(li & 7, c)]);
+      const int sl = bslot(li & 7, 4 * q + kg);
+      bf16x8 a[TM];
 #pragma unroll
-      for (int t = 0; t < TILES; ++t) {
-        const bf16x8 w = __builtin_bit_cast(bf16x8, st[(2 * t + (li >> 3)) * kBlockSlots + wslot(li & 7, c)]);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w, acc[t], 0, 0, 0);
+      for (int i = 0; i < TM; ++i)   // XB = 1: rows 8 to 15 repeat 0 to 7
+        a[i] = __builtin_bit_cast(bf16x8, st[(2 * TN + 2 * i + (XB == 1 ? 0 : li >> 3)) * kBlockSlots + sl]);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        const bf16x8 w = __builtin_bit_cast(bf16x8, st[(2 * t + (li >> 3)) * kBlockSlots + sl]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w, acc[t][i], 0, 0, 0);
       }
     }
   };
 
-  for (int s = 0; s < L::kStages - 1 && s < nst; ++s) issue(s);
+  for (int s = 0; s < NS - 1 && s < nst; ++s) issue(s);
+  Scale scale;
+  scale.load(p.nrm);
   for (int s = 0; s < nst; ++s) {
     asm volatile("" ::: "memory");
-    if (s + L::kStages - 1 < nst) {
-      issue(s + L::kStages - 1);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((L::kStages - 1) * L::kLoads) : "memory");
+    if (s + NS - 1 < nst) {
+      issue(s + NS - 1);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * kBlocks) : "memory");
+    } else if (NS > 2 && nst - 1 - s == 1) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBlocks) : "memory");   // step s + 1 may stay in flight
     } else {
-      // Tail: stages s+1 .. nst-1 may stay in flight.
-      switch (nst - 1 - s) {
-        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-        case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::kLoads) : "memory"); break;
-        case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L::kLoads) : "memory"); break;
-        case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * L::kLoads) : "memory"); break;
-        default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * L::kLoads) : "memory"); break;
-      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     compute(s);
   }
+  static_assert(NS == 2 || NS == 3, "the tail leaves at most one step in flight");
 
-  // Sum the per-wave partial tiles.
+  // Epilogue units: block t (gate|up: the pair t, t + HT) of row block i.
+  // Wave w takes row block w % TM and every (4 / TM)-th t, so a wave's units
+  // share their rows.
+  constexpr int kT = EPI == kEpiSwiGLU ? HT : TN;     // unit columns per tile
+  constexpr int kWavesPerRow = kWaves / TM;
+  constexpr int kUnits = (kT + kWavesPerRow - 1) / kWavesPerRow;   // per wave
+  constexpr int kPer = EPI == kEpiSwiGLU ? 2 : 1;     // blocks per unit
+  const int ui = wave % TM, ut0 = wave / TM;
+  // What the residual epilogue reads, started before the reductions.
+  float old[kUnits][4], gain[kUnits];
+#pragma unroll
+  for (int u = 0; u < kUnits; ++u) {
+    const int t = ut0 + u * kWavesPerRow, col = col0(t) + li;
+    gain[u] = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = ui * 16 + kg * 4 + r;
+      old[u][r] = 0.f;
+      if (EPI == kEpiAddF32 && t < kT && col < N && m < M)
+        old[u][r] = static_cast<const float*>(p.C)[static_cast<int64_t>(m) * p.ldc + col];
+    }
+    if (EPI == kEpiAddF32 && p.nrm.gain_out && t < kT && col < N) gain[u] = bf2f(p.nrm.gain_out[col]);
+  }
   __syncthreads();
   f32x4* red = reinterpret_cast<f32x4*>(lds);
 #pragma unroll
-  for (int t = 0; t < TILES; ++t) red[(wave * TILES + t) * 64 + lane] = acc[t];
+  for (int t = 0; t < TN; ++t)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) red[((wave * TN + t) * TM + i) * 64 + lane] = acc[t][i];
   __syncthreads();
-  if (wave != 0) return;
-  f32x4 sum[TILES];
+  f32x4 sum[kUnits][kPer];
 #pragma unroll
-  for (int t = 0; t < TILES; ++t) {
-    sum[t] = red[t * 64 + lane];
+  for (int u = 0; u < kUnits; ++u) {
+    const int t0 = ut0 + u * kWavesPerRow;
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) sum[t] += red[(w * TILES + t) * 64 + lane];
+    for (int e = 0; e < kPer; ++e) {
+      const int t = t0 + e * HT;
+      sum[u][e] = f32x4{};
+      if (t0 < kT)
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum[u][e] += red[((w * TN + t) * TM + ui) * 64 + lane];
+    }
   }
-  // lane holds column li and rows kg*4 + r
-  if (sp.S > 1) {
-    const bool col_ok = (EPI == kEpiSwiGLU ? tile * 16 : trow[0]) + li < N;
+  if (p.S > 1) {
+    // Partial tiles in register layout: 16 bytes per lane, whole lines.
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.part + static_cast<int64_t>(tile) * p.S * (TN * TM * 256)), 0,
+        static_cast<uint32_t>(p.S) * (TN * TM * 1024), 0x00020000);
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int t0 = ut0 + u * kWavesPerRow, t = t0 + e * HT;
+        __builtin_amdgcn_raw_buffer_store_b128(
+            __builtin_bit_cast(u32x4, sum[u][e]), rp,
+            t0 < kT && ui * 16 + kg * 4 < M ? static_cast<uint32_t>(((ks * TN + t) * TM + ui) * 64 + lane) * 16u : kOob,
+            0, kAuxAgent);
+      }
+    // The partials are agent-scope stores, which write through this XCD's L2
+    // to the device-coherent level; once every wave's have completed (vmcnt
+    // 0, barrier), the count goes up.  The reader's agent-scope loads miss
+    // its own L2, and are issued only after the count they branch on has
+    // returned.  That is the agent-scope release/acquire sequence of the
+    // gfx950 memory model for data accessed only at agent scope: its L2
+    // write-back and invalidate act on other data only, and as fences
+    // (__ATOMIC_RELEASE / __ATOMIC_ACQUIRE at agent scope) they cost a whole
+    // L2 per workgroup: measured, a decode step of the large model took 21.6
+    // ms with them against 14.9 ms.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (threadIdx.x == 0)
+      *arrived = __hip_atomic_fetch_add(p.ctr + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (*arrived != p.S - 1) return;
+    if (threadIdx.x == 0) __hip_atomic_store(p.ctr + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Last of the tile: every split's partials at once, added in order.
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int t0 = ut0 + u * kWavesPerRow, t = t0 + e * HT;
+        f32x4 v[kGemvMaxSplit];
+#pragma unroll
+        for (int j = 0; j < kGemvMaxSplit; ++j)     // past S: reads zeros
+          v[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+              rp, j < p.S && t0 < kT ? static_cast<uint32_t>(((j * TN + t) * TM + ui) * 64 + lane) * 16u : kOob, 0,
+              kAuxAgent));
+        sum[u][e] = v[0];
+#pragma unroll
+        for (int j = 1; j < kGemvMaxSplit; ++j)
+          if (j < p.S) sum[u][e] += v[j];
+      }
+  }
+  float inv[4] = {1.f, 1.f, 1.f, 1.f};
+  if (p.nrm.ssq_in) {
+    scale.finish(p.nrm, p.K, scratch, row_inv);
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int r = 0; r < 4; ++r) inv[r] = row_inv[min(ui * 16 + kg * 4 + r, kMpad - 1)];
+  }
+  // lane holds column li and rows 16 ui + 4 kg + r
+  float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < kUnits; ++u) {
+    const int t = ut0 + u * kWavesPerRow;
+    const int col = col0(t) + li;
+    if (t >= kT || col >= N) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int m = kg * 4 + r;
-      if (m >= M || !col_ok) continue;
-#pragma unroll
-      for (int t = 0; t < TILES; ++t)
-        __hip_atomic_store(sp.part + (static_cast<int64_t>(ks) * M + m) * sp.nrows + trow[t] + li, sum[t][r],
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int m = ui * 16 + kg * 4 + r;
+      if (m >= M) continue;
+      const int64_t at = static_cast<int64_t>(m) * p.ldc + col;
+      const float v = sum[u][0][r] * inv[r];
+      if (EPI == kEpiSwiGLU) {
+        static_cast<uint16_t*>(p.C)[at] = f2bf(swiglu(v, sum[u][kPer - 1][r] * inv[r]));
+      } else if (EPI == kEpiBf16) {
+        static_cast<uint16_t*>(p.C)[at] = f2bf(v);
+      } else if (EPI == kEpiAddF32) {
+        const float x = old[u][r] + v;
+        static_cast<float*>(p.C)[at] = x;
+        if (p.nrm.gain_out) {
+          p.nrm.h_out[at] = f2bf(x * gain[u]);
+          ss[r] += x * x;
+        }
+      } else {
+        static_cast<float*>(p.C)[at] = v;
+      }
     }
-    // The partials are agent-scope atomic stores, which write through this
-    // XCD's L2 to the device-coherent level; once they have completed
-    // (vmcnt 0), the count goes up.  The reader's agent-scope atomic loads
-    // miss its own L2, and are issued only after the count they branch on
-    // has returned.  That is the agent-scope release/acquire sequence of
-    // the gfx950 memory model for data accessed only through agent-scope
-    // atomics: its L2 write-back and invalidate act on non-atomic data
-    // only, and as fences (__ATOMIC_RELEASE / __ATOMIC_ACQUIRE at agent
-    // scope) they cost a whole L2 per workgroup: measured, a decode step
-    // of the large model took 21.6 ms with them against 14.9 ms.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  if (EPI == kEpiAddF32 && p.nrm.gain_out && ut0 < kT) {
+    // One partial per row and wave of the tile that covers it.
+    f32x4 sq;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sq[r] = row16_sum(ss[r]);
+    if (li == 0 && ui * 16 + kg * 4 < kMpad)
+      *reinterpret_cast<f32x4*>(p.nrm.ssq_out +
+                                (static_cast<int64_t>(tile) * min(kT, kWavesPerRow) + ut0) * kMpad + ui * 16 + kg * 4) = sq;
+  }
+}
+
+// 8-row weight blocks per wave of the stream kernel.
+constexpr int kWBlocks = 4;
+constexpr int kStreamStages = 4;
+
+// Wide weights, more than 16 rows.  The (tile, K step) pairs of all 128-row
+// tiles form one sequence that is cut evenly over the workgroups, so every
+// CU streams the same bytes.  Each wave owns 32 rows of a tile (gate|up: 16
+// gate and 16 up rows) over all of K; the X blocks of a stage are loaded by
+// the four waves together, with one barrier per step.  A tile cut between
+// workgroups is summed, in their order, by the last of them to arrive.
+// (M = 64, large / mid model: gate|up 160 -> 123 / 66 -> 53 us against the
+// other kernel, lm_head 330 -> 237; M = 32: 126 -> 106 / 50.7 -> 44.4, 260 ->
+// 230.  Launches of a few tiles pay too much for the cut ones: Q|K|V of the
+// mid model 23.5 against 18 us.)
+template <int EPI, int TM, int NS>
+__global__ __launch_bounds__(kThreads) void gemv_stream_kernel(GemvArgs p) {
+  static_assert(EPI == kEpiSwiGLU || EPI == kEpiF32, "epilogues without loads: none may wait on the stream");
+  constexpr int XPW = TM == 4 ? 2 : 1;                   // 8-row X blocks per wave
+  constexpr int L = kWBlocks + XPW;                      // load instructions per wave and step
+  constexpr int kXSlots = kWaves * XPW * kBlockSlots;
+  constexpr int kWSlots = kWaves * kWBlocks * kBlockSlots;
+  constexpr int kStageSlots = kXSlots + kWSlots;         // X blocks, then the waves' W blocks
+  constexpr int kMpad = 16 * TM;
+  using Scale = RowScale<kMpad>;
+  __shared__ __attribute__((aligned(16))) u32x4 lds[NS * kStageSlots + (kWaves + 1) * Scale::kQ];
+  f32x4* const scratch = reinterpret_cast<f32x4*>(lds + NS * kStageSlots);
+  float* const row_inv = reinterpret_cast<float*>(lds + NS * kStageSlots + kWaves * Scale::kQ);   // [kMpad]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int li = lane & 15, kg = lane >> 4;
+  const int M = p.M, N = p.N;
+  const int G = gridDim.x, wg = blockIdx.x;
+  const int KT = p.ksteps;
+  const int64_t total = static_cast<int64_t>(p.tiles) * KT;
+  const int64_t s0 = total * wg / G, s1 = total * (wg + 1) / G;
+  const int n = static_cast<int>(s1 - s0);
+
+  const int b = lane & 15;
+  const int rr = (b & 3) | ((b >> 3) << 2);
+  const int lc = ((lane >> 4) << 1) | ((b >> 2) & 1);
+  const uint32_t woff = static_cast<uint32_t>(rr) * p.ldw * 2u + lc * 16u;
+  const uint32_t xoff = static_cast<uint32_t>(wave * XPW * 8 + rr) * p.ldx * 2u + lc * 16u;
+  const __amdgpu_buffer_rsrc_t rx =
+      __builtin_amdgcn_make_buffer_rsrc((void*)p.X, 0, static_cast<uint32_t>(M) * p.ldx * 2u, 0x00020000);
+
+  // Column (output) of this wave's 16-row block t of a tile.
+  auto col0 = [&](int tile, int t) {
+    return EPI == kEpiSwiGLU ? tile * 64 + wave * 16 : tile * 128 + wave * 32 + t * 16;
+  };
+  int it = static_cast<int>(s0 / KT), ik = static_cast<int>(s0 - static_cast<int64_t>(it) * KT), is = 0;
+  auto issue = [&]() {
+    u32x4* st = lds + (is % NS) * kStageSlots;
+    const int k0 = ik * kKStep;
+    const bool in = is < n && k0 + lc * 8 < p.K;
+    const uint32_t ko = static_cast<uint32_t>(k0) * 2u;
+#pragma unroll
+    for (int x = 0; x < XPW; ++x)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + (wave * XPW + x) * kBlockSlots), 16,
+                                               in ? xoff + ko + x * 8u * p.ldx * 2u : kOob, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < kWBlocks; ++q) {
+      const int c = col0(it, q >> 1) + (q & 1) * 8;
+      const int valid = __builtin_amdgcn_readfirstlane(max(0, min(8, N - c)));
+      const int row = valid > 0 ? (EPI == kEpiSwiGLU && q >= 2 ? N : 0) + c : 0;
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(p.W + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(row)) * p.ldw), 0, static_cast<uint32_t>(valid) * p.ldw * 2u, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + kXSlots + (wave * kWBlocks + q) * kBlockSlots), 16,
+                                               in ? woff + ko : kOob, 0, 0, kAuxStream);
+    }
+    ++is;
+    if (++ik == KT) {
+      ik = 0;
+      ++it;
+    }
+  };
+
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i) issue();
+  Scale scale;
+  scale.load(p.nrm);
+  scale.finish(p.nrm, p.K, scratch, row_inv);   // read past the first step's barrier
+
+  f32x4 acc[2][TM];
+  auto clear = [&] {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) acc[t][i] = f32x4{0, 0, 0, 0};
+  };
+
+  auto epilogue = [&](int tile) {
+    float inv[TM][4];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) inv[i][r] = p.nrm.ssq_in ? row_inv[i * 16 + kg * 4 + r] : 1.f;
+    constexpr int kT = EPI == kEpiSwiGLU ? 1 : 2;
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+      const int col = col0(tile, t) + li;
+      if (col >= N) continue;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = i * 16 + kg * 4 + r;
+          if (m >= M) continue;
+          const int64_t at = static_cast<int64_t>(m) * p.ldc + col;
+          const float v = acc[t][i][r] * inv[i][r];
+          if (EPI == kEpiSwiGLU) static_cast<uint16_t*>(p.C)[at] = f2bf(swiglu(v, acc[1][i][r] * inv[i][r]));
+          else static_cast<float*>(p.C)[at] = v;
+        }
+    }
+  };
+
+  // Partial tiles: slot 0 of a workgroup for a tile that began in an earlier
+  // one, slot 1 for the tile its run ends in.
+  constexpr uint32_t kSlotBytes = 2 * TM * 1024;
+  auto slot_rsrc = [&](int w, int slot) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(reinterpret_cast<char*>(p.part) + (static_cast<int64_t>(w * 2 + slot) * kWaves + wave) * kSlotBytes), 0,
+        kSlotBytes, 0x00020000);
+  };
+  int part_tile[2] = {-1, -1};
+
+  int ct = static_cast<int>(s0 / KT);
+  int left = KT - static_cast<int>(s0 - static_cast<int64_t>(ct) * KT);   // steps to the tile's end
+  clear();
+  for (int s = 0; s < n; ++s) {
+    // Step s has landed for this wave, and, past the barrier, for all; step
+    // s - 1's stage is free.
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * L) : "memory");
+    issue();
+    const u32x4* st = lds + (s % NS) * kStageSlots;
+    const u32x4* ws = st + kXSlots + wave * kWBlocks * kBlockSlots;
+#pragma unroll
+    for (int q = 0; q < kKStep / 32; ++q) {
+      const int sl = bslot(li & 7, 4 * q + kg) + (li >> 3) * kBlockSlots;
+      bf16x8 a[TM], w[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) w[t] = __builtin_bit_cast(bf16x8, ws[2 * t * kBlockSlots + sl]);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = __builtin_bit_cast(bf16x8, st[2 * i * kBlockSlots + sl]);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w[t], acc[t][i], 0, 0, 0);
+    }
+    if (--left == 0 || s == n - 1) {
+      const int64_t first = static_cast<int64_t>(ct) * KT;
+      if (left == 0 && first >= s0) {
+        epilogue(ct);
+      } else {
+        const int slot = s0 > first ? 0 : 1;
+        const __amdgpu_buffer_rsrc_t rp = slot_rsrc(wg, slot);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[t][i]), rp,
+                                                   static_cast<uint32_t>((t * TM + i) * 64 + lane) * 16u, 0, kAuxAgent);
+        part_tile[slot] = ct;
+      }
+      clear();
+      ++ct;
+      left = KT;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int slot = 0; slot < 2; ++slot) {
+    const int t = part_tile[slot];
+    if (t < 0) continue;
+    const int64_t first = static_cast<int64_t>(t) * KT;
+    const int w0 = static_cast<int>(((first + 1) * G - 1) / total);
+    const int w1 = static_cast<int>(((first + KT) * G - 1) / total);
+    int* cnt = p.ctr + t * kWaves + wave;
     int prev = 0;
-    if (lane == 0) prev = __hip_atomic_fetch_add(sp.ctr + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    prev = __shfl(prev, 0, kWave);
-    if (prev != sp.S - 1) return;
+    if (lane == 0) prev = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    prev = __builtin_amdgcn_readfirstlane(prev);
+    if (prev != w1 - w0) continue;
     asm volatile("" ::: "memory");
-    // Last of the tile: the others' partials, read past this XCD's L2.
+    if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    clear();
+    constexpr int U = TM == 4 ? 4 : 8;
+    for (int j0 = w0; j0 <= w1; j0 += U) {
+      f32x4 v[U][2][TM];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = kg * 4 + r;
+      for (int j = 0; j < U; ++j) {
+        const int w = min(j0 + j, w1);
+        const __amdgpu_buffer_rsrc_t rp = slot_rsrc(w, total * w / G > first ? 0 : 1);
 #pragma unroll
-      for (int t = 0; t < TILES; ++t) {
-        float v = 0.f;
-        if (m < M && col_ok)
-          for (int j = 0; j < sp.S; ++j)
-            v += __hip_atomic_load(sp.part + (static_cast<int64_t>(j) * M + m) * sp.nrows + trow[t] + li,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum[t][r] = v;
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            v[j][x][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                rp, static_cast<uint32_t>((x * TM + i) * 64 + lane) * 16u, 0, kAuxAgent));
       }
+#pragma unroll
+      for (int j = 0; j < U; ++j)
+        if (j0 + j <= w1)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[x][i] += v[j][x][i];
     }
-    if (lane == 0) __hip_atomic_store(sp.ctr + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int m = kg * 4 + r;
-    if (m >= M) continue;
-    if (EPI == kEpiSwiGLU) {
-      const int col = tile * 16 + li;
-      if (col < N) {
-        const float gt = sum[0][r], up = sum[TILES - 1][r];
-        static_cast<uint16_t*>(C)[static_cast<int64_t>(m) * ldc + col] = f2bf(swiglu(gt, up));
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) {
-        const int col = trow[t] + li;
-        if (col >= N) continue;
-        const float v = sum[t][r];
-        const int64_t at = static_cast<int64_t>(m) * ldc + col;
-        if (EPI == kEpiBf16) static_cast<uint16_t*>(C)[at] = f2bf(v);
-        else if (EPI == kEpiAddF32) static_cast<float*>(C)[at] += v;
-        else static_cast<float*>(C)[at] = v;
-      }
-    }
+    epilogue(t);
   }
 }
 
@@ -249,33 +565,44 @@ __global__ void fill_zero_kernel(int* __restrict__ a, int na, int* __restrict__ 
   else if (i - na < nb) b[i - na] = 0;
 }
 
-}  // namespace
-
-int gemv_ksplit(int epi, int N, int K) {
-  // Workgroups per tile, for launches of fewer than two tiles per CU (O and
-  // down at the large shape: 320 tiles): the split whose workgroup count
-  // divides most evenly over the 256 CUs, with at least four 64-wide
-  // K-steps per wave and every workgroup resident at once (the LDS stages
-  // hold four single-tile or two gate|up workgroups per CU), and only when it beats no
-  // split by more than 5%.  Measured at the large shape, M = 1: O 21.6 ->
-  // 18.8 us and down 64 -> 58 us with four splits, and three (960
-  // workgroups) beat four (1280, a fifth of them in a second round): the
-  // decode step 14.94 -> 14.63 ms.  Q|K|V (640 tiles) and gate|up (1600)
-  // ran 10% slower split in two, so they do not split.
-  const int tiles = (N + 15) / 16;
-  if (tiles >= 512) return 1;
-  const int resident = 256 * (epi == kEpiSwiGLU ? 2 : 4);
-  auto eff = [&](int s) {
-    const double per_cu = double(tiles) * s / 256.0;
-    return per_cu / std::ceil(per_cu);
-  };
-  int best = 1;
-  for (int s = 2; s <= kGemvMaxSplit; ++s) {
-    if (K / (s * kWaves * kKStep) < 4 || tiles * s > resident) break;
-    if (eff(s) > eff(best) + 0.05) best = s;
+template <int EPI, int XB>
+hipError_t launch_ring(const GemvArgs& a, int tn, int grid, hipStream_t s) {
+  if constexpr (XB == 1 && EPI != kEpiSwiGLU) {
+    if (tn == 1) {
+      gemv_kernel<EPI, 1, XB, 3><<<grid, kThreads, 0, s>>>(a);
+      return hipGetLastError();
+    }
   }
-  return best;
+  if constexpr (XB <= 2) {
+    if (tn == 2) {
+      gemv_kernel<EPI, 2, XB, 2><<<grid, kThreads, 0, s>>>(a);
+      return hipGetLastError();
+    }
+  }
+  if (tn != 4) return hipErrorInvalidValue;
+  gemv_kernel<EPI, 4, XB, 2><<<grid, kThreads, 0, s>>>(a);
+  return hipGetLastError();
 }
+
+template <int EPI>
+hipError_t launch_epi(const GemvArgs& a, const GemvPlan& pl, int grid, hipStream_t s) {
+  if (pl.stream) {
+    if constexpr (EPI == kEpiSwiGLU || EPI == kEpiF32) {
+      if (pl.xb == 4) gemv_stream_kernel<EPI, 2, kStreamStages><<<grid, kThreads, 0, s>>>(a);
+      else gemv_stream_kernel<EPI, 4, kStreamStages><<<grid, kThreads, 0, s>>>(a);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
+  switch (pl.xb) {
+    case 1: return launch_ring<EPI, 1>(a, pl.tn, grid, s);
+    case 2: return launch_ring<EPI, 2>(a, pl.tn, grid, s);
+    case 4: return launch_ring<EPI, 4>(a, pl.tn, grid, s);
+    default: return launch_ring<EPI, 8>(a, pl.tn, grid, s);
+  }
+}
+
+}  // namespace
 
 hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s) {
   if (na + nb <= 0) return hipSuccess;
@@ -283,31 +610,38 @@ hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C,
-                       int ldc, int M, int N, int K, float* part, size_t part_bytes, int* ctr,
-                       int ctr_count, hipStream_t s) {
-  if (M <= 0 || M > 8 || N <= 0 || K <= 0 || (K & 7) || (lda & 7) || (ldb & 7)) return hipErrorInvalidValue;
-  // 32-bit buffer offsets: one 16-row weight tile and the X rows
-  if (static_cast<int64_t>(16) * ldb * 2 >= (int64_t(1) << 32) || static_cast<int64_t>(8) * lda * 2 >= (int64_t(1) << 32))
+hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C, int ldc, int M, int N,
+                       int K, const GemvScratch& sc, const GemvNorm& nrm, hipStream_t s) {
+  if (M <= 0 || M > kGemvMaxRows || N <= 0 || K <= 0 || (K & 7) || (lda & 7) || (ldb & 7)) return hipErrorInvalidValue;
+  // 32-bit buffer offsets: 16 weight rows and the X rows
+  if (static_cast<int64_t>(16) * ldb * 2 >= (int64_t(1) << 32) || static_cast<int64_t>(kGemvMaxRows) * lda * 2 >= (int64_t(1) << 32))
     return hipErrorInvalidValue;
-  const int tiles = (N + 15) / 16;
-  GemvSplit sp;
-  sp.S = gemv_ksplit(epi, N, K);
-  sp.nrows = epi == kEpiSwiGLU ? 2 * N : N;
-  sp.part = part;
-  sp.ctr = ctr;
-  if (sp.S > 1 && (!part || !ctr || ctr_count < tiles ||
-                   part_bytes < size_t(sp.S) * M * sp.nrows * sizeof(float)))
-    sp.S = 1;   // no room for the split: stream the whole K per tile
-  const int grid = tiles * sp.S;
+  const GemvPlan pl = gemv_plan(epi, M, N, K, sc.part_bytes);
+  if (pl.counters() > sc.ctr_count || pl.part_bytes() > sc.part_bytes) return hipErrorInvalidValue;
+  GemvArgs a;
+  a.X = A;
+  a.W = B;
+  a.C = C;
+  a.ldx = lda;
+  a.ldw = ldb;
+  a.ldc = ldc;
+  a.M = M;
+  a.N = N;
+  a.K = K;
+  a.S = pl.S;
+  a.tiles = pl.tiles;
+  a.ksteps = (K + kKStep - 1) / kKStep;
+  a.part = sc.part;
+  a.ctr = sc.ctr;
+  a.nrm = nrm;
+  const int grid = pl.stream ? kGemvStreamGrid : pl.tiles * pl.S;
   switch (epi) {
-    case kEpiBf16: gemv_kernel<kEpiBf16, 1><<<grid, kThreads, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K, sp); break;
-    case kEpiAddF32: gemv_kernel<kEpiAddF32, 1><<<grid, kThreads, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K, sp); break;
-    case kEpiF32: gemv_kernel<kEpiF32, 1><<<grid, kThreads, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K, sp); break;
-    case kEpiSwiGLU: gemv_kernel<kEpiSwiGLU, 2><<<grid, kThreads, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K, sp); break;
+    case kEpiBf16: return launch_epi<kEpiBf16>(a, pl, grid, s);
+    case kEpiAddF32: return launch_epi<kEpiAddF32>(a, pl, grid, s);
+    case kEpiF32: return launch_epi<kEpiF32>(a, pl, grid, s);
+    case kEpiSwiGLU: return launch_epi<kEpiSwiGLU>(a, pl, grid, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace pallas

@@ -44,7 +44,7 @@ enum GemmEpi : int {
   kEpiBf16 = 0,    // C bf16 [M][ldc] = A B^T
   kEpiAddF32 = 1,  // C f32 [M][ldc] += A B^T (residual add)
   kEpiSwiGLU = 2,  // C bf16 [M][ldc] = silu(A Bg^T) * (A Bu^T); B rows [0,N) gate, [N,2N) up
-  kEpiF32 = 3,     // C f32 [M][ldc] = A B^T
+  kEpiF32 = 3,     // C f32 [M][ldc] = A B^T (skinny kernels only)
 };
 
 struct GemmParams {
@@ -257,33 +257,117 @@ struct DecodeAttnParams {
 // otherwise half the records leave room for the counters.
 constexpr int kDecodeMinSplit = 128;
 constexpr int kDecodeMaxSplit = 1024;   // a split's table entries: one per lane
+constexpr int kDecodeSplitsPerSeq = 16;  // per sequence: one batch of the merge
 struct DecodeAttnScratch {
   int max_splits;          // splits per sequence that fit
   int counters;            // ints to clear at the start of the section
-  size_t out_floats, ml_floats;
+  size_t out_floats, ml_floats, floats;
 };
 inline DecodeAttnScratch decode_attn_scratch(int n_seqs, int Hq, int Hkv, int d, int part_splits) {
   DecodeAttnScratch s;
-  s.max_splits = (part_splits + 1) / 2;
+  s.max_splits = (part_splits + 1) / 2 < kDecodeSplitsPerSeq ? (part_splits + 1) / 2 : kDecodeSplitsPerSeq;
   s.counters = s.max_splits > 1 ? n_seqs * Hkv : 0;
   s.out_floats = (size_t(n_seqs) * Hkv + 63) / 64 * 64;
   s.ml_floats = s.out_floats + size_t(n_seqs) * Hq * s.max_splits * d;
+  s.floats = s.max_splits > 1 ? s.ml_floats + size_t(n_seqs) * Hq * s.max_splits * 2 : 0;
   return s;
 }
 hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, float* part,
                                    int part_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM
-// C[m][n] (op) A[m] . B[n] for m < M <= 8 rows; epilogues as launch_gemm.
-// With gemv_ksplit(epi, N, K) = S > 1 the K range of each 16-row tile is
-// split over S workgroups: `part` needs S * M * (N, or 2N for gate|up)
-// floats and `ctr` one int per tile, zero on entry and left zero (else, or
-// with too little room, the launch does not split).
+// C[m][n] (op) A[m] . B[n] for m < M <= 64 rows (gemv.hip); epilogues as
+// launch_gemm.
 constexpr int kGemvMaxSplit = 8;
-int gemv_ksplit(int epi, int N, int K);
-hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C,
-                       int ldc, int M, int N, int K, float* part, size_t part_bytes, int* ctr,
-                       int ctr_count, hipStream_t s);
+constexpr int kGemvMaxRows = 64;
+constexpr int kGemvStreamGrid = 256;   // one workgroup per CU
+
+// How a projection runs.  Ring kernel: workgroups of 4 waves, each a tile of
+// tn blocks of 16 weight rows over 1 / S of K.  Stream kernel: kGemvStreamGrid
+// workgroups over tiles of 128 rows.
+struct GemvPlan {
+  bool stream;
+  int xb;      // 8-row blocks of A covered: 1, 2, 4 or 8
+  int tn, S;
+  int tiles;
+  size_t part_bytes() const {
+    const size_t tm = (xb + 1) / 2;
+    if (stream) return size_t(kGemvStreamGrid) * 2 * 4 * 2 * tm * 1024;
+    return S > 1 ? size_t(tiles) * S * tn * tm * 1024 : 0;
+  }
+  int counters() const { return stream ? tiles * 4 : S > 1 ? tiles : 0; }
+  // Sum-of-squares partials of the residual epilogue, each 8 xb floats.
+  int norm_parts() const {
+    const int waves = 4 / ((xb + 1) / 2);
+    return tiles * (tn < waves ? tn : waves);
+  }
+};
+// The plan of least modelled time whose partial sums fit in `room` bytes.  A
+// CU holds r workgroups (their LDS stages decide), and a full round of 256 r
+// of them takes K / S u r + c0: u = the time 256 CUs need for one k of tn
+// blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split adds 1 us +
+// 0.3 us per part (count, partial sums) and the partials' traffic.  Fitted to
+// (us, TN / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
+// 14.2 (2 / 4 at M = 8), of the large one 19.7 (4 / 3), 20.2 (1 / 1), 21.6
+// (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3); at M = 32
+// mid Q|K|V 18.0 (4 / 2), 19.6 (4 / 5).
+inline GemvPlan gemv_plan(int epi, int M, int N, int K, size_t room) {
+  GemvPlan best{};
+  const int xb = M <= 8 ? 1 : M <= 16 ? 2 : M <= 32 ? 4 : 8;
+  const int64_t rows = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;
+  if (M > 16 && (epi == kEpiSwiGLU || epi == kEpiF32) && rows >= 128 * 128) {
+    const GemvPlan st{true, xb, 0, 1, int((rows + 127) / 128)};
+    if (st.part_bytes() <= room) return st;
+  }
+  const int tm = (xb + 1) / 2;
+  double best_t = 0;
+  for (int tn = 1; tn <= 4; tn *= 2) {
+    if (tn == 1 && (xb > 1 || epi == kEpiSwiGLU)) continue;
+    if (tn == 2 && xb > 2) continue;
+    const int stages = tn == 1 ? 3 : 2;
+    const int lds = 4 * stages * (2 * tn + xb) * 1088 + 1024;   // 8-row blocks of 68 x 16 bytes
+    const int resident = 160 * 1024 / lds;
+    const int per = epi == kEpiSwiGLU ? tn * 8 : tn * 16;       // output columns per tile
+    const int tiles = (N + per - 1) / per;
+    const double u = tn * 32.0 * 256 / 5.5e6;                   // us per k and workgroup of a CU
+    for (int S = 1; S <= kGemvMaxSplit; ++S) {
+      const GemvPlan pl{false, xb, tn, S, tiles};
+      const int64_t wgs = int64_t(tiles) * S;
+      if (S > 1 && (K / (S * 256) < 4 || wgs > 256 * resident || pl.part_bytes() > room)) break;
+      const double full = double(wgs / (256 * resident)), rest = double(wgs % (256 * resident));
+      double t = full * (double(K) / S * u * resident + 3);
+      if (rest > 0) t += double(K) / S * u * double((int(rest) + 255) / 256) + 3;
+      if (S > 1) t += 1 + 0.3 * S + 2.0 * S * rows * tm * 64 / 4e6;
+      if (best_t == 0 || t < best_t * 0.999) {
+        best = pl;
+        best_t = t;
+      }
+    }
+  }
+  return best;
+}
+
+struct GemvScratch {
+  float* part;
+  size_t part_bytes;
+  int* ctr;         // zero on entry, left zero
+  int ctr_count;
+};
+// The RMSNorm before and after a projection.  In: A holds x g, and row m's
+// output is scaled by (sum of ssq_in[0..parts_in)[m] / K + eps)^(-1/2)
+// (ssq_in null: no scale).  Out (kEpiAddF32 only, gain_out not null): h_out =
+// bf16(C gain_out), laid out as C, and the sums of squares of C's rows in
+// ssq_out[norm_parts()][8 xb] of the plan.
+struct GemvNorm {
+  const float* ssq_in;
+  int parts_in;
+  float eps;
+  const uint16_t* gain_out;
+  uint16_t* h_out;
+  float* ssq_out;
+};
+hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C, int ldc, int M, int N,
+                       int K, const GemvScratch& sc, const GemvNorm& nrm, hipStream_t s);
 // a[0..na) = 0 and b[0..nb) = 0 (a kernel, so it can sit in a captured graph).
 hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s);
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "kernels.h"
@@ -23,9 +24,9 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // decode: number of sequences).
 struct Workspace {
   size_t resid, h, qkv, q, o, act, rope, part, split, split_bytes, attn_split, attn_split_bytes;
-  size_t gemv_part, gemv_part_bytes, gemv_ctr;
+  size_t gemv_part, gemv_part_bytes, gemv_ctr, ssq;
   int gemv_ctr_count;
-  int part_splits;   // decode attention records per (sequence, query head)
+  int part_splits;   // decode attention: largest position / 64 + 1 the section is sized for
   size_t total;
 };
 
@@ -33,6 +34,18 @@ struct Workspace {
 // record per 64-key split.
 constexpr int kDecodeMaxPos = 16384;
 constexpr int kDecodeMaxSplits = kDecodeMaxPos / 64;
+
+// Weight rows of the widest projection, and the room for the decode
+// projections' partial sums in a call of `r8` <= 8 rows (or more: 8).
+inline int64_t widest_projection(const pallas_model_config& c) {
+  const int64_t qkv = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  return std::max<int64_t>(std::max<int64_t>(qkv, 2 * int64_t(c.ffn)), std::max<int64_t>(c.hidden, c.vocab));
+}
+inline size_t gemv_room(const pallas_model_config& c, int r8) {
+  return size_t(kGemvMaxSplit) * r8 * widest_projection(c) * 4;
+}
+// Sums of squares of up to 64 rows: at most hidden + 64 floats (GemvPlan).
+inline size_t norm_bytes(const pallas_model_config& c) { return (size_t(c.hidden) + 256) * 4; }
 
 inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, int64_t seqs) {
   Workspace w;
@@ -47,7 +60,13 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.act = take(size_t(tokens) * c.ffn * 2);
   w.rope = take(size_t(tokens) * (c.head_dim / 2) * 8);  // (cos, sin) per row and pair
   w.part_splits = kDecodeMaxSplits;
-  w.part = take(size_t(seqs) * c.n_q_heads * kDecodeMaxSplits * (c.head_dim + 2) * 4);
+  const size_t part_bytes = size_t(seqs) * c.n_q_heads * kDecodeMaxSplits * (c.head_dim + 2) * 4;
+  w.part = take(part_bytes);
+  // Sums of squares of the decode norms, at the end of that section (decode
+  // attention uses a sixteenth of it) where they fit.
+  const size_t records = decode_attn_scratch(int(seqs), c.n_q_heads, c.n_kv_heads, c.head_dim, kDecodeMaxSplits).floats * 4;
+  w.ssq = align_up(w.part + records, 256);
+  if (w.ssq + norm_bytes(c) > w.part + part_bytes) w.ssq = take(norm_bytes(c));
   // Split-K partial sums of the projections of up to 256 rows.
   {
     const int rows = static_cast<int>(tokens < 256 ? tokens : 256);
@@ -57,7 +76,6 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
     b = std::max(b, gemm_split_bytes(kEpiAddF32, rows, H, QD));
     b = std::max(b, gemm_split_bytes(kEpiSwiGLU, rows, c.ffn, H));
     b = std::max(b, gemm_split_bytes(kEpiAddF32, rows, H, c.ffn));
-    b = std::max(b, gemm_split_bytes(kEpiF32, rows, c.vocab, H));
     w.split_bytes = b;
     w.split = take(b);
   }
@@ -65,13 +83,12 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.attn_split_bytes = attn_prefill_split_bytes(static_cast<int>(tokens < 256 ? tokens : 256),
                                                 c.n_q_heads, c.head_dim);
   w.attn_split = take(w.attn_split_bytes);
-  // Decode projections (at most 8 rows) split over K: partial sums and one
-  // arrival counter per 16-row weight tile.
+  // Decode projections split over K: partial sums and one arrival counter
+  // per 16-row weight tile.
   {
-    const int64_t rows = std::max<int64_t>(
-        std::max<int64_t>(qkv, 2 * int64_t(c.ffn)), std::max<int64_t>(c.hidden, c.vocab));
+    const int64_t rows = widest_projection(c);
     const int64_t r8 = std::min<int64_t>(std::min<int64_t>(seqs, tokens), 8);
-    w.gemv_part_bytes = size_t(kGemvMaxSplit) * r8 * rows * 4;
+    w.gemv_part_bytes = gemv_room(c, int(r8));
     w.gemv_part = take(w.gemv_part_bytes);
     w.gemv_ctr_count = static_cast<int>((rows + 15) / 16);
     w.gemv_ctr = take(size_t(w.gemv_ctr_count) * 4);
@@ -80,13 +97,52 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   return w;
 }
 
-// The smallest layout a decode step of `seqs` <= 8 sequences needs, with
-// positions up to `max_pos`: the activations, decode-attention records for
-// max_pos / 64 + 1 splits, and the skinny projections' split partial sums
-// and counters at exactly the split counts those projections take (so the
-// arithmetic is that of a step in a full workspace).  No GEMM split-K or
-// prefill-attention section: more than 8 rows are not served from it.
-inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_pos) {
+// The documented scratch need of pallas_decode_step_static, which decides
+// what it accepts: the step's activations, one record per 64 keys and query
+// head, and partial sums and counters of the projections of fewer than 512
+// 16-row tiles (O and down at the large shape: three splits).
+inline size_t static_decode_need(const pallas_model_config& c, int seqs, int max_pos) {
+  const int64_t QKV = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  const int64_t QD = int64_t(c.n_q_heads) * c.head_dim;
+  size_t at = 0;
+  auto take = [&](size_t bytes) { at = align_up(at + bytes, 256); };
+  take(size_t(seqs) * c.hidden * 4);
+  take(size_t(seqs) * c.hidden * 2);
+  take(size_t(seqs) * QKV * 2);
+  take(size_t(seqs) * QD * 2);
+  take(size_t(seqs) * QD * 2);
+  take(size_t(seqs) * c.ffn * 2);
+  take(size_t(seqs) * (c.head_dim / 2) * 8);
+  take(size_t(seqs) * c.n_q_heads * (max_pos / 64 + 1) * (c.head_dim + 2) * 4);
+  auto splits = [](int64_t N, int64_t K, int resident) {
+    const int64_t tiles = (N + 15) / 16;
+    int best = 1;
+    if (tiles >= 512) return best;
+    auto even = [&](int s) { return double(tiles) * s / 256.0 / std::ceil(double(tiles) * s / 256.0); };
+    for (int s = 2; s <= 8 && K / (s * 256) >= 4 && tiles * s <= resident; ++s)
+      if (even(s) > even(best) + 0.05) best = s;
+    return best;
+  };
+  const int64_t proj[5][4] = {{QKV, c.hidden, 1024, QKV}, {c.hidden, QD, 1024, c.hidden},
+                              {c.ffn, c.hidden, 512, 2 * int64_t(c.ffn)}, {c.hidden, c.ffn, 1024, c.hidden},
+                              {c.vocab, c.hidden, 1024, c.vocab}};
+  size_t part = 0, tiles = 0;
+  for (const auto& p : proj) {
+    const int s = splits(p[0], p[1], int(p[2]));
+    if (s == 1) continue;
+    part = std::max(part, size_t(s) * seqs * p[3] * 4);
+    tiles = std::max(tiles, size_t((p[0] + 15) / 16));
+  }
+  take(part);
+  take(tiles * 4);
+  return at;
+}
+
+// The layout a decode step of `seqs` <= 8 sequences runs in without a
+// workspace, with positions up to `max_pos`: the arithmetic is that of a step
+// in a full workspace (the same plans, chosen for the same room).  When it
+// would exceed `cap` bytes, the projections do not split.
+inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_pos, size_t cap) {
   Workspace w{};
   const int64_t QKV = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   const int64_t QD = int64_t(c.n_q_heads) * c.head_dim;
@@ -95,33 +151,32 @@ inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_p
   w.resid = take(size_t(seqs) * c.hidden * 4);
   w.h = take(size_t(seqs) * c.hidden * 2);
   w.qkv = take(size_t(seqs) * QKV * 2);
-  w.q = take(size_t(seqs) * QD * 2);
   w.o = take(size_t(seqs) * QD * 2);
   w.act = take(size_t(seqs) * c.ffn * 2);
   w.rope = take(size_t(seqs) * (c.head_dim / 2) * 8);
   w.part_splits = max_pos / 64 + 1;
-  w.part = take(size_t(seqs) * c.n_q_heads * w.part_splits * (c.head_dim + 2) * 4);
-  w.split = w.attn_split = 0;
-  w.split_bytes = w.attn_split_bytes = 0;
-  // (epi, N, K) of the five projections; B rows are 2N for gate|up.
+  w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.part_splits).floats * 4);
+  w.ssq = take(norm_bytes(c));
+  // (epi, N, K) of the five projections.
   const int64_t proj[5][3] = {{kEpiBf16, QKV, c.hidden},
                               {kEpiAddF32, c.hidden, QD},
                               {kEpiSwiGLU, c.ffn, c.hidden},
                               {kEpiAddF32, c.hidden, c.ffn},
                               {kEpiF32, c.vocab, c.hidden}};
+  const size_t room = gemv_room(c, seqs);
   size_t part = 0;
-  int tiles = 0;
+  int ctr = 0;
   for (const auto& pr : proj) {
-    const int S = gemv_ksplit(int(pr[0]), int(pr[1]), int(pr[2]));
-    if (S <= 1) continue;
-    const int64_t nrows = pr[0] == kEpiSwiGLU ? 2 * pr[1] : pr[1];
-    part = std::max(part, size_t(S) * seqs * nrows * 4);
-    tiles = std::max(tiles, int((pr[1] + 15) / 16));
+    const GemvPlan pl = gemv_plan(int(pr[0]), seqs, int(pr[1]), int(pr[2]), room);
+    part = std::max(part, pl.part_bytes());
+    ctr = std::max(ctr, pl.counters());
   }
-  w.gemv_part_bytes = part;
-  w.gemv_part = take(part);
-  w.gemv_ctr_count = tiles;
-  w.gemv_ctr = take(size_t(tiles) * 4);
+  if (at + align_up(part, 256) + align_up(size_t(ctr) * 4, 256) <= cap) {
+    w.gemv_part_bytes = room;
+    w.gemv_part = take(part);
+    w.gemv_ctr_count = ctr;
+    w.gemv_ctr = take(size_t(ctr) * 4);
+  }
   w.total = at;
   return w;
 }

@@ -302,10 +302,9 @@ int check_workspace(const pallas_model* m, const void* ws, size_t bytes, int64_t
 
 // The projections address their operands through buffer descriptors with
 // 32-bit byte offsets, so every activation matrix a call feeds them and
-// every weight matrix must stay below 2 GiB (the MFMA GEMM, for more than 8
-// rows), or a 16-row weight tile and 8 activation rows below 4 GiB (the
-// skinny kernel, which decode uses for up to 8 rows; prefill always runs
-// the MFMA GEMM).  Checked here, on the host, so a call that would reach a
+// every weight matrix must stay below 2 GiB (prefill, and decode of more than
+// 8 rows), or a 16-row weight tile and 8 activation rows below 4 GiB (decode
+// of up to 8 rows).  Checked here, on the host, so a call that would reach a
 // limit mid-sequence is refused before layer 0 writes anything.
 // `lm_head`: the call also projects the final norm onto the vocabulary
 // (decode).
@@ -362,27 +361,6 @@ Planes layer_planes(const pallas_kv_pool* pool, int l) {
 }
 
 const uint16_t* u16(const void* p) { return static_cast<const uint16_t*>(p); }
-
-// Projection of `rows` activation rows: the MFMA GEMM, or the skinny kernel
-// for up to 8 rows.
-// Scratch of the projections of one call: split-K partial sums of the
-// GEMM, and partial sums plus arrival counters of the skinny kernel.
-struct ProjScratch {
-  float* split;
-  size_t split_bytes;
-  float* gv_part;
-  size_t gv_part_bytes;
-  int* gv_ctr;
-  int gv_ctr_count;
-};
-
-hipError_t project(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C, int ldc,
-                   int rows, int N, int K, const ProjScratch& sc, hipStream_t s) {
-  if (rows <= 8)
-    return pallas::launch_gemv(epi, A, lda, B, ldb, C, ldc, rows, N, K, sc.gv_part, sc.gv_part_bytes, sc.gv_ctr,
-                               sc.gv_ctr_count, s);
-  return pallas::launch_gemm(epi, A, lda, B, ldb, C, ldc, rows, N, K, sc.split, sc.split_bytes, s);
-}
 
 int run_prefill(const pallas_model* m, const pallas::RowMap& rm, int M, const int32_t* ids,
                 const int32_t* bt, int max_pages, const pallas_kv_pool* pool, char* ws, int32_t* err,
@@ -485,17 +463,23 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   uint16_t* o = reinterpret_cast<uint16_t*>(ws + w.o);
   uint16_t* act = reinterpret_cast<uint16_t*>(ws + w.act);
   float* rope = reinterpret_cast<float*>(ws + w.rope);
-  float* split = reinterpret_cast<float*>(ws + w.split);
-  const size_t sb = w.split_bytes;
+  float* ssq = reinterpret_cast<float*>(ws + w.ssq);
   const int H = c.hidden, d = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, F = c.ffn;
   const int QKV = (Hq + 2 * Hkv) * d, QD = Hq * d;
 
-  const ProjScratch sc{split, sb, reinterpret_cast<float*>(ws + w.gemv_part), w.gemv_part_bytes,
-                       reinterpret_cast<int*>(ws + w.gemv_ctr), w.gemv_ctr_count};
+  const pallas::GemvScratch sc{reinterpret_cast<float*>(ws + w.gemv_part), w.gemv_part_bytes,
+                               reinterpret_cast<int*>(ws + w.gemv_ctr), w.gemv_ctr_count};
   const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
-  if (hipError_t e = pallas::launch_zero_counters(sc.gv_ctr, sc.gv_ctr_count, reinterpret_cast<int*>(part), as.counters, s);
+  if (hipError_t e = pallas::launch_zero_counters(sc.ctr, sc.ctr_count, reinterpret_cast<int*>(part), as.counters, s);
       e != hipSuccess)
     return hip_fail(e, "counters");
+  // The norms inside the projections: O and down write h = r g of the norm
+  // that follows, with the sums of squares of r; the next projection scales.
+  // The first layer's comes normalised from the embedding kernel.
+  const int o_parts = pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD, sc.part_bytes).norm_parts();
+  const int down_parts = pallas::gemv_plan(pallas::kEpiAddF32, B, H, F, sc.part_bytes).norm_parts();
+  auto norm_in = [&](int parts) { return pallas::GemvNorm{parts ? ssq : nullptr, parts, c.rms_eps, nullptr, nullptr, nullptr}; };
+  auto norm_out = [&](const void* gain) { return pallas::GemvNorm{nullptr, 0, c.rms_eps, u16(gain), h, ssq}; };
   PALLAS_TRY(PALLAS_K_ROPE_TABLE, pallas::launch_rope_table(rm, B, d, c.rope_theta, rope, s), "rope table");
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(tokens, u16(m->embed), u16(m->layers[0].attn_norm), r, h, B, H,
                                           c.rms_eps, c.vocab, err, s), "embed");
@@ -518,20 +502,24 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   for (int l = 0; l < c.n_layers; ++l) {
     const pallas_layer_weights& L = m->layers[l];
     const Planes pl = layer_planes(pool, l);
-    if (l > 0) PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.attn_norm), h, B, H, c.rms_eps, s), "rmsnorm");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiBf16, h, H, u16(L.w_qkv), H, qkv, QKV, B, QKV, H, sc, s), "qkv proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiBf16, h, H, u16(L.w_qkv), H, qkv, QKV, B, QKV, H, sc,
+                                                         norm_in(l > 0 ? down_parts : 0), s), "qkv proj");
     ap.q_gain = u16(L.q_norm);
     ap.k_gain = u16(L.k_norm);
     ap.k_plane = pl.k;
     ap.v_plane = pl.v;
     PALLAS_TRY(PALLAS_K_DECODE_ATTN, pallas::launch_attention_decode(ap, rm, part, w.part_splits, s), "decode attention");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiAddF32, o, QD, u16(L.w_o), QD, r, H, B, H, QD, sc, s), "o proj");
-    PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.mlp_norm), h, B, H, c.rms_eps, s), "rmsnorm");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiSwiGLU, h, H, u16(L.w_gate_up), H, act, F, B, F, H, sc, s), "gate_up proj");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiAddF32, act, F, u16(L.w_down), F, r, H, B, H, F, sc, s), "down proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiAddF32, o, QD, u16(L.w_o), QD, r, H, B, H, QD, sc,
+                                                         norm_out(L.mlp_norm), s), "o proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiSwiGLU, h, H, u16(L.w_gate_up), H, act, F, B, F, H, sc,
+                                                         norm_in(o_parts), s), "gate_up proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ,
+               pallas::launch_gemv(pallas::kEpiAddF32, act, F, u16(L.w_down), F, r, H, B, H, F, sc,
+                                   norm_out(l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : m->final_norm), s),
+               "down proj");
   }
-  PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(m->final_norm), h, B, H, c.rms_eps, s), "final norm");
-  PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiF32, h, H, u16(m->lm_head), H, logits, c.vocab, B, c.vocab, H, sc, s), "lm_head");
+  PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiF32, h, H, u16(m->lm_head), H, logits, c.vocab, B, c.vocab,
+                                                       H, sc, norm_in(down_parts), s), "lm_head");
   return PALLAS_OK;
 }
 
@@ -695,11 +683,12 @@ int pallas_decode_step_static(pallas_model* m, int32_t num_seqs, const int32_t* 
                 PALLAS_STATIC_DECODE_MAX_SEQS);
   int max_pos = 0;
   for (int i = 0; i < num_seqs; ++i) max_pos = std::max(max_pos, h_positions[i]);
-  const pallas::Workspace w = pallas::decode_layout(m->cfg, num_seqs, max_pos);
-  if (w.total > PALLAS_STATIC_SCRATCH_BYTES)
+  const size_t need = pallas::static_decode_need(m->cfg, num_seqs, max_pos);
+  const pallas::Workspace w = pallas::decode_layout(m->cfg, num_seqs, max_pos, PALLAS_STATIC_SCRATCH_BYTES);
+  if (need > PALLAS_STATIC_SCRATCH_BYTES || w.total > PALLAS_STATIC_SCRATCH_BYTES)
     return fail(PALLAS_ERR_UNSUPPORTED,
                 "decode (static scratch): %d sequences up to position %d need %zu bytes of scratch (at most %zu)",
-                num_seqs, max_pos, w.total, size_t(PALLAS_STATIC_SCRATCH_BYTES));
+                num_seqs, max_pos, need, size_t(PALLAS_STATIC_SCRATCH_BYTES));
   char* ws = nullptr;
   if (int rc = static_scratch(&ws)) return rc;
   return run_decode(m, rm, d_tokens, d_block_tables, max_pages, pool, d_logits, ws, w, d_err,
