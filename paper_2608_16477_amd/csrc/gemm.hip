@@ -59,10 +59,17 @@ constexpr int kGroupM = 6;
 //              has to hide its loads behind).
 // The 192-row shapes exist for row counts such as 1536 = 8 x 192, where
 // 256-row tiles leave CUs idle (gemm_tile).
+//   128 x 256, 128 x 128, 128 x 64: waves 2 x 4, 4 x 2, 4 x 2, each 64 x 64,
+//              32 x 64, 32 x 32; 3, 4 and 4-deep rings;
+//   64 x 128:  waves 2 x 4, each 32 x 32; a 4-deep ring.
+// They serve launches of few rows.  Small tiles are bound by LDS: at 128
+// bytes per clock the operand reads and writes of a K-step take 704 cycles
+// for 128 x 64, 1024 for 128 x 128 and 1216 for 192 x 128 (measured 0.34,
+// 0.55 and 0.60 us per step), against 256, 512 and 768 cycles of MFMAs.
 template <int BM_, int BN_>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_;
-  static constexpr int WAVES_N = BN_ == 128 ? 2 : 4;
+  static constexpr int WAVES_N = BN_ <= 128 && BM_ > 64 ? 2 : 4;
   static constexpr int WAVES_M = 8 / WAVES_N;
   static constexpr int WM = BM_ / WAVES_M;        // rows per wave
   static constexpr int WN = BN_ / WAVES_N;        // B rows (columns) per wave
@@ -95,7 +102,7 @@ __device__ __forceinline__ int swz(int row, int c) { return row * kChunks + (c ^
 // whole row offset: a row past the matrix reads zeros.  Without a K tail
 // the step's column offset goes into the scalar offset; with one (K not a
 // multiple of BK) each lane checks its column against K.
-template <int N, bool kTail>
+template <int N, bool kTail, int kAux>
 __device__ __forceinline__ void load_row_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t limit,
                                              const uint32_t* voff, const int* kcol, uint32_t step,
                                              int k0, int K, u32x4* lds_tile, int wave, int i) {
@@ -103,17 +110,17 @@ __device__ __forceinline__ void load_row_lds(__amdgpu_buffer_rsrc_t rsrc, uint32
   const uint32_t vo = voff[i & 1] + static_cast<uint32_t>(i & ~1) * step;
   if (kTail) {
     const uint32_t off = kcol[i & 1] < K - k0 ? vo + static_cast<uint32_t>(k0) * 2u : limit;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, off, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, off, 0, 0, kAux);
   } else {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, vo, k0 * 2, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, vo, k0 * 2, 0, kAux);
   }
 }
-template <int N, bool kTail>
+template <int N, bool kTail, int kAux>
 __device__ __forceinline__ void load_tile_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t limit,
                                               const uint32_t* voff, const int* kcol, uint32_t step,
                                               int k0, int K, u32x4* lds_tile, int wave) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) load_row_lds<N, kTail>(rsrc, limit, voff, kcol, step, k0, K, lds_tile, wave, i);
+  for (int i = 0; i < N; ++i) load_row_lds<N, kTail, kAux>(rsrc, limit, voff, kcol, step, k0, K, lds_tile, wave, i);
 }
 
 template <int BM_, int BN_>
@@ -130,7 +137,7 @@ enum { kUnitsPlain = 0, kUnitsTailFull = 1, kUnitsTailHalf = 2 };
 
 // One workgroup: its unit, then the output tile (M tile tm, column tile tn
 // of BN_ B rows) over its K split, with its LDS ring `lds`.
-template <int EPI, int BM_, int BN_, int kUnits>
+template <int EPI, int BM_, int BN_, int kUnits, int kAuxB>
 __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_, BN_>& lds) {
   using T = TileCfg<BM_, BN_>;
   constexpr int BM = T::BM, BN = T::BN, IM = T::IM, JN = T::JN, WM = T::WM, WN = T::WN;
@@ -244,8 +251,8 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
 #pragma unroll
     for (int st = 0; st < kStages; ++st) {
       if (st < KT) {
-        load_tile_lds<kLoadsA, true>(ra, p.a_bytes, a_off, kcol_a, a_step, kb + st * BK, p.K, lds[st], wave);
-        load_tile_lds<kLoadsB, true>(rb, p.b_bytes, b_off, kcol_b, b_step, kb + st * BK, p.K, lds[st] + kSlotsA,
+        load_tile_lds<kLoadsA, true, 0>(ra, p.a_bytes, a_off, kcol_a, a_step, kb + st * BK, p.K, lds[st], wave);
+        load_tile_lds<kLoadsB, true, kAuxB>(rb, p.b_bytes, b_off, kcol_b, b_step, kb + st * BK, p.K, lds[st] + kSlotsA,
                                      wave);
       }
     }
@@ -310,9 +317,9 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
 #pragma unroll
         for (int q = i * kLoadsStep / (IM / 2); q < (i + 1) * kLoadsStep / (IM / 2) && q < kLoadsStep; ++q) {
           if (q < kLoadsA)
-            load_row_lds<kLoadsA, kTail>(ra, p.a_bytes, a_off, kcol_a, a_step, kload, p.K, lds[lslot], wave, q);
+            load_row_lds<kLoadsA, kTail, 0>(ra, p.a_bytes, a_off, kcol_a, a_step, kload, p.K, lds[lslot], wave, q);
           else
-            load_row_lds<kLoadsB, kTail>(rb, p.b_bytes, b_off, kcol_b, b_step, kload, p.K, lds[lslot] + kSlotsA,
+            load_row_lds<kLoadsB, kTail, kAuxB>(rb, p.b_bytes, b_off, kcol_b, b_step, kload, p.K, lds[lslot] + kSlotsA,
                                          wave, q - kLoadsA);
         }
       }
@@ -464,7 +471,9 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
         for (int j = 0; j < JN; ++j) {
           const int col = tn * BN + wn * WN + j * 16 + l16e;
           if (col >= p.N) continue;
-          static_cast<uint16_t*>(p.C)[static_cast<int64_t>(row) * p.ldc + col] = f2bf(acc[i][j][r]);
+          const int64_t at = static_cast<int64_t>(row) * p.ldc + col;
+          if (EPI == kEpiF32) static_cast<float*>(p.C)[at] = acc[i][j][r];
+          else static_cast<uint16_t*>(p.C)[at] = f2bf(acc[i][j][r]);
         }
       }
     }
@@ -479,10 +488,10 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
 }
 
 // Tiles of one width.
-template <int EPI, int BM_, int BN_>
+template <int EPI, int BM_, int BN_, int kAuxB>
 __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(16))) LdsRing<BM_, BN_> lds;
-  gemm_workgroup<EPI, BM_, BN_, kUnitsPlain>(p, lds);
+  gemm_workgroup<EPI, BM_, BN_, kUnitsPlain, kAuxB>(p, lds);
 }
 
 // Full-width tiles with a split tail: the last p.tail_half full tiles of
@@ -494,8 +503,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_tail_kernel(GemmParams 
   __shared__ __attribute__((aligned(16))) LdsRing<256, 128> lds;
   const int loc = static_cast<int>(blockIdx.x) / kXcds;
   if (loc >= p.tiles_per_xcd + p.tail_half) return;
-  if (loc >= p.tiles_per_xcd - p.tail_half) gemm_workgroup<EPI, 256, 128, kUnitsTailHalf>(p, lds);
-  else gemm_workgroup<EPI, 256, 256, kUnitsTailFull>(p, reinterpret_cast<LdsRing<256, 256>&>(lds));
+  if (loc >= p.tiles_per_xcd - p.tail_half) gemm_workgroup<EPI, 256, 128, kUnitsTailHalf, 0>(p, lds);
+  else gemm_workgroup<EPI, 256, 256, kUnitsTailFull, 0>(p, reinterpret_cast<LdsRing<256, 256>&>(lds));
 }
 
 // Split-K reduction: C = epilogue(sum over ks of part[ks]), the splits
@@ -520,6 +529,8 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
   if (EPI == kEpiAddF32) {
     f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(C) + static_cast<int64_t>(row) * ldc + c);
     *dst = *dst + a;
+  } else if (EPI == kEpiF32) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(C) + static_cast<int64_t>(row) * ldc + c) = a;
   } else {
     if (EPI == kEpiSwiGLU) {
 #pragma unroll
@@ -532,30 +543,117 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
   }
 }
 
-// The instantiation for a tile shape (gemm_tile never picks 192-wide B
-// tiles for the SwiGLU product, which has no such instantiation).
-template <int EPI>
-void launch_tiles(const GemmParams& p, int bm, int bn, int grid, hipStream_t s) {
-  if (bm == 256 && bn == 128) gemm_bf16_kernel<EPI, 256, 128><<<grid, kThreads, 0, s>>>(p);
-  else if (bm == 192 && bn == 256) gemm_bf16_kernel<EPI, 192, 256><<<grid, kThreads, 0, s>>>(p);
-  else if (bm == 192 && bn == 128) gemm_bf16_kernel<EPI, 192, 128><<<grid, kThreads, 0, s>>>(p);
-  else if constexpr (EPI != kEpiSwiGLU) {
-    if (bm == 192 && bn == 192) {
-      gemm_bf16_kernel<EPI, 192, 192><<<grid, kThreads, 0, s>>>(p);
-      return;
-    }
+// Split-K reduction of a residual projection and the RMSNorm that follows it:
+// one workgroup per row adds the splits in order and the residual, stores
+// the new residual and its norm.  The partial sums come from other XCDs'
+// writes, far away: kBatch splits' loads are in flight at once.  (256 rows of
+// 5120, six splits: 12.3 + 5.6 us in two launches -> 8.9; 32 rows of 4096,
+// eight splits: 5.8 + 4.6 -> 4.9.)
+constexpr int kNormThreads = 512;
+template <int kVecs>
+__global__ __launch_bounds__(kNormThreads) void gemm_reduce_norm_kernel(const float* __restrict__ part, int S, int M,
+                                                                        int N, float* __restrict__ r, int ldc,
+                                                                        const uint16_t* __restrict__ gain,
+                                                                        uint16_t* __restrict__ h, float eps) {
+  constexpr int kBatch = 8;
+  __shared__ float sh[kNormThreads / 64];
+  const int row = blockIdx.x;
+  const uint32_t split = static_cast<uint32_t>(M) * N * 4u;   // S splits stay below 2^32 bytes (host)
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)part, 0, S * split, 0x00020000);
+  float* rr = r + static_cast<int64_t>(row) * ldc;
+  f32x4 a[kVecs], old[kVecs];
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    const int i = (v * kNormThreads + threadIdx.x) * 4;
+    old[v] = i < N ? *reinterpret_cast<const f32x4*>(rr + i) : f32x4{};
+    a[v] = f32x4{};
   }
-  if (bm == 256 && bn == 256) {
-    if (p.tail_half) gemm_bf16_tail_kernel<EPI><<<grid, kThreads, 0, s>>>(p);
-    else gemm_bf16_kernel<EPI, 256, 256><<<grid, kThreads, 0, s>>>(p);
+  for (int k0 = 0; k0 < S; k0 += kBatch) {
+    f32x4 x[kBatch][kVecs];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+      for (int v = 0; v < kVecs; ++v) {
+        const int i = (v * kNormThreads + threadIdx.x) * 4;
+        // past the row or the splits: zeros
+        const uint32_t off = k0 + k < S && i < N ? (k0 + k) * split + (static_cast<uint32_t>(row) * N + i) * 4u : 0xFFFFFFF0u;
+        x[k][v] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, off, 0, 0));
+      }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+      for (int v = 0; v < kVecs; ++v) a[v] += x[k][v];
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    const int i = (v * kNormThreads + threadIdx.x) * 4;
+    a[v] = old[v] + a[v];
+    if (i < N) *reinterpret_cast<f32x4*>(rr + i) = a[v];
+    ss += a[v].x * a[v].x + a[v].y * a[v].y + a[v].z * a[v].z + a[v].w * a[v].w;
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < kNormThreads / 64; ++w) t += sh[w];
+  const float inv = rsqrtf(t / N + eps);
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    const int i = (v * kNormThreads + threadIdx.x) * 4;
+    if (i >= N) continue;
+    const u32x2 gg = *reinterpret_cast<const u32x2*>(gain + i);
+    u32x2 w;
+    w.x = pack_bf2(a[v].x * inv * bflo(gg.x), a[v].y * inv * bfhi(gg.x));
+    w.y = pack_bf2(a[v].z * inv * bflo(gg.y), a[v].w * inv * bfhi(gg.y));
+    *reinterpret_cast<u32x2*>(h + static_cast<int64_t>(row) * N + i) = w;
   }
 }
+
+#define PALLAS_GEMM_TILE(BM, BN, AUX)                                       \
+  if (bm == BM && bn == BN) {                                               \
+    gemm_bf16_kernel<EPI, BM, BN, AUX><<<grid, kThreads, 0, s>>>(p);        \
+    return;                                                                 \
+  }
+// Launches of at most 256 rows (one M tile): weights are read once, so they
+// are loaded non-temporally (gate|up of the large model at 256 rows 164 ->
+// 143 us, at 128 110 -> 102).
+constexpr int kAuxStream = 2;
+template <int EPI>
+void launch_few_rows(const GemmParams& p, int bm, int bn, int grid, hipStream_t s) {
+  PALLAS_GEMM_TILE(64, 128, kAuxStream)
+  PALLAS_GEMM_TILE(128, 256, kAuxStream)
+  if constexpr (EPI != kEpiF32) {
+    PALLAS_GEMM_TILE(128, 128, kAuxStream)
+    PALLAS_GEMM_TILE(192, 128, kAuxStream)
+    PALLAS_GEMM_TILE(192, 256, kAuxStream)
+    PALLAS_GEMM_TILE(256, 128, kAuxStream)
+    PALLAS_GEMM_TILE(256, 256, kAuxStream)
+  }
+}
+// The instantiation for a tile shape (gemm_tile never picks 192-wide or
+// 128-row tiles for the SwiGLU product, which has no such instantiations).
+template <int EPI>
+void launch_tiles(const GemmParams& p, int bm, int bn, int grid, hipStream_t s) {
+  PALLAS_GEMM_TILE(256, 128, 0)
+  PALLAS_GEMM_TILE(192, 256, 0)
+  PALLAS_GEMM_TILE(192, 128, 0)
+  if constexpr (EPI != kEpiSwiGLU) {
+    PALLAS_GEMM_TILE(192, 192, 0)
+    PALLAS_GEMM_TILE(128, 128, 0)
+    PALLAS_GEMM_TILE(128, 64, 0)
+  }
+  if (p.tail_half) gemm_bf16_tail_kernel<EPI><<<grid, kThreads, 0, s>>>(p);
+  else gemm_bf16_kernel<EPI, 256, 256, 0><<<grid, kThreads, 0, s>>>(p);
+}
+#undef PALLAS_GEMM_TILE
 
 }  // namespace
 
 hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C,
                        int ldc, int M, int N, int K, float* part, size_t part_bytes, hipStream_t s,
-                       unsigned long long* clk) {
+                       unsigned long long* clk, const GemmNorm* norm) {
   const int64_t brows64 = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;
   // byte offsets are 32-bit (buffer addressing): both operands below 2 GiB
   if (int64_t(M) * lda * 2 >= (int64_t(1) << 31) || brows64 * ldb * 2 >= (int64_t(1) << 31) ||
@@ -572,7 +670,9 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   p.ldb = ldb;
   p.ldc = ldc;
   p.ksplit = gemm_ksplit(epi, M, N, K);
-  const GemmTile tile = p.ksplit == 1 ? gemm_tile(epi, M, N) : GemmTile{256, 256};
+  const bool few = M <= kGemmFewRows;
+  if (epi == kEpiF32 && M > 64) return hipErrorInvalidValue;   // decode only
+  const GemmTile tile = few ? gemm_tile_few(epi, M, N) : gemm_tile(epi, M, N);
   const int bm = tile.bm, bn = tile.bn;
   p.tiles_m = (M + bm - 1) / bm;
   p.tiles_n = gemm_tiles_n(epi, N, bn);
@@ -587,7 +687,7 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   // A last round that keeps at most half of an XCD's 32 CUs busy runs as
   // half-width tiles (full-width launches without a K split only).
   p.tail_half = 0;
-  if (bm == 256 && bn == 256 && p.ksplit == 1) {
+  if (bm == 256 && bn == 256 && !few) {
     const int rounds = (p.tiles_per_xcd + 31) / 32, last = p.tiles_per_xcd - 32 * (rounds - 1);
     if (rounds > 1 && last <= 16) p.tail_half = last;
   }
@@ -597,20 +697,41 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   p.b_bytes = static_cast<uint32_t>(brows * ldb * 2);
   p.clk = clk;
   const int grid = (p.tiles_per_xcd + p.tail_half) * kXcds;
-  switch (epi) {
-    case kEpiBf16: launch_tiles<kEpiBf16>(p, bm, bn, grid, s); break;
-    case kEpiAddF32: launch_tiles<kEpiAddF32>(p, bm, bn, grid, s); break;
-    case kEpiSwiGLU: launch_tiles<kEpiSwiGLU>(p, bm, bn, grid, s); break;
-    default: return hipErrorInvalidValue;
+  if (few) {
+    switch (epi) {
+      case kEpiBf16: launch_few_rows<kEpiBf16>(p, bm, bn, grid, s); break;
+      case kEpiAddF32: launch_few_rows<kEpiAddF32>(p, bm, bn, grid, s); break;
+      case kEpiSwiGLU: launch_few_rows<kEpiSwiGLU>(p, bm, bn, grid, s); break;
+      case kEpiF32: launch_few_rows<kEpiF32>(p, bm, bn, grid, s); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (epi) {
+      case kEpiBf16: launch_tiles<kEpiBf16>(p, bm, bn, grid, s); break;
+      case kEpiAddF32: launch_tiles<kEpiAddF32>(p, bm, bn, grid, s); break;
+      case kEpiSwiGLU: launch_tiles<kEpiSwiGLU>(p, bm, bn, grid, s); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   if (p.ksplit > 1) {
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    if (norm && gemm_fuses_norm(epi, M, N, K)) {
+      float* r = static_cast<float*>(C);
+      switch ((N + 2047) / 2048) {
+        case 1: gemm_reduce_norm_kernel<1><<<M, kNormThreads, 0, s>>>(part, p.ksplit, M, N, r, ldc, norm->gain, norm->h, norm->eps); break;
+        case 2: gemm_reduce_norm_kernel<2><<<M, kNormThreads, 0, s>>>(part, p.ksplit, M, N, r, ldc, norm->gain, norm->h, norm->eps); break;
+        case 3: gemm_reduce_norm_kernel<3><<<M, kNormThreads, 0, s>>>(part, p.ksplit, M, N, r, ldc, norm->gain, norm->h, norm->eps); break;
+        default: gemm_reduce_norm_kernel<4><<<M, kNormThreads, 0, s>>>(part, p.ksplit, M, N, r, ldc, norm->gain, norm->h, norm->eps); break;
+      }
+      return hipGetLastError();
+    }
     const int64_t threads = int64_t(M) * (N / 4);
     const int rgrid = static_cast<int>((threads + 255) / 256);
     switch (epi) {
       case kEpiBf16: gemm_reduce_kernel<kEpiBf16><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
       case kEpiAddF32: gemm_reduce_kernel<kEpiAddF32><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
       case kEpiSwiGLU: gemm_reduce_kernel<kEpiSwiGLU><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
+      default: gemm_reduce_kernel<kEpiF32><<<rgrid, 256, 0, s>>>(part, p.ksplit, M, N, p.part_ld, C, ldc); break;
     }
   }
   return hipGetLastError();

@@ -1,4 +1,4 @@
-// Skinny GEMM for decode (M <= 64 rows): C = X W^T streaming the weights once.
+// Skinny GEMM for decode (M <= 16 rows): C = X W^T streaming the weights once.
 //
 // A workgroup of 4 waves owns a tile of TN blocks of 16 weight rows (for the
 // gate|up projection half of them gate rows and half the matching up rows)
@@ -14,9 +14,8 @@
 // per-tile counter, and the last to arrive adds the splits in order and
 // applies the epilogue (gemv_plan chooses TN and the splits).
 //
-// More than 16 rows through a wide weight (gate|up, lm_head) take a second
-// kernel (gemv_stream_kernel): X is then a large part of what a wave has in
-// flight, so four waves share each X stage and stream 128 weight rows past it.
+// More than 16 rows run the GEMM (gemm.hip): X is then a large part of what a
+// wave keeps in flight, and its tiles share it between waves.
 //
 // Weights are loaded non-temporally: they are read once per step, and the
 // stream runs 10% faster that way (M = 1: gate|up of the mid / large model 36
@@ -58,9 +57,8 @@ struct GemvArgs {
   void* C;
   int ldx, ldw, ldc, M, N, K;
   int S;          // K splits over workgroups
-  int tiles, ksteps;   // stream kernel: 128-row tiles, K / 64 rounded up
   float* part;    // partial tiles
-  int* ctr;       // [tiles] (stream kernel: [tiles][wave]), zero on entry
+  int* ctr;       // [tiles], zero on entry
   GemvNorm nrm;
 };
 
@@ -104,7 +102,7 @@ struct RowScale {
   }
 };
 
-// XB: 8-row blocks of X (M <= 8 XB); NS: stages in flight per wave.
+// XB: 8-row blocks of X (M <= 8 XB), 1 or 2; NS: stages in flight per wave.
 template <int EPI, int TN, int XB, int NS>
 __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
   constexpr int TM = (XB + 1) / 2;                // 16-row blocks of X
@@ -350,215 +348,6 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
   }
 }
 
-// 8-row weight blocks per wave of the stream kernel.
-constexpr int kWBlocks = 4;
-constexpr int kStreamStages = 4;
-
-// Wide weights, more than 16 rows.  The (tile, K step) pairs of all 128-row
-// tiles form one sequence that is cut evenly over the workgroups, so every
-// CU streams the same bytes.  Each wave owns 32 rows of a tile (gate|up: 16
-// gate and 16 up rows) over all of K; the X blocks of a stage are loaded by
-// the four waves together, with one barrier per step.  A tile cut between
-// workgroups is summed, in their order, by the last of them to arrive.
-// (M = 64, large / mid model: gate|up 160 -> 123 / 66 -> 53 us against the
-// other kernel, lm_head 330 -> 237; M = 32: 126 -> 106 / 50.7 -> 44.4, 260 ->
-// 230.  Launches of a few tiles pay too much for the cut ones: Q|K|V of the
-// mid model 23.5 against 18 us.)
-template <int EPI, int TM, int NS>
-__global__ __launch_bounds__(kThreads) void gemv_stream_kernel(GemvArgs p) {
-  static_assert(EPI == kEpiSwiGLU || EPI == kEpiF32, "epilogues without loads: none may wait on the stream");
-  constexpr int XPW = TM == 4 ? 2 : 1;                   // 8-row X blocks per wave
-  constexpr int L = kWBlocks + XPW;                      // load instructions per wave and step
-  constexpr int kXSlots = kWaves * XPW * kBlockSlots;
-  constexpr int kWSlots = kWaves * kWBlocks * kBlockSlots;
-  constexpr int kStageSlots = kXSlots + kWSlots;         // X blocks, then the waves' W blocks
-  constexpr int kMpad = 16 * TM;
-  using Scale = RowScale<kMpad>;
-  __shared__ __attribute__((aligned(16))) u32x4 lds[NS * kStageSlots + (kWaves + 1) * Scale::kQ];
-  f32x4* const scratch = reinterpret_cast<f32x4*>(lds + NS * kStageSlots);
-  float* const row_inv = reinterpret_cast<float*>(lds + NS * kStageSlots + kWaves * Scale::kQ);   // [kMpad]
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int li = lane & 15, kg = lane >> 4;
-  const int M = p.M, N = p.N;
-  const int G = gridDim.x, wg = blockIdx.x;
-  const int KT = p.ksteps;
-  const int64_t total = static_cast<int64_t>(p.tiles) * KT;
-  const int64_t s0 = total * wg / G, s1 = total * (wg + 1) / G;
-  const int n = static_cast<int>(s1 - s0);
-
-  const int b = lane & 15;
-  const int rr = (b & 3) | ((b >> 3) << 2);
-  const int lc = ((lane >> 4) << 1) | ((b >> 2) & 1);
-  const uint32_t woff = static_cast<uint32_t>(rr) * p.ldw * 2u + lc * 16u;
-  const uint32_t xoff = static_cast<uint32_t>(wave * XPW * 8 + rr) * p.ldx * 2u + lc * 16u;
-  const __amdgpu_buffer_rsrc_t rx =
-      __builtin_amdgcn_make_buffer_rsrc((void*)p.X, 0, static_cast<uint32_t>(M) * p.ldx * 2u, 0x00020000);
-
-  // Column (output) of this wave's 16-row block t of a tile.
-  auto col0 = [&](int tile, int t) {
-    return EPI == kEpiSwiGLU ? tile * 64 + wave * 16 : tile * 128 + wave * 32 + t * 16;
-  };
-  int it = static_cast<int>(s0 / KT), ik = static_cast<int>(s0 - static_cast<int64_t>(it) * KT), is = 0;
-  auto issue = [&]() {
-    u32x4* st = lds + (is % NS) * kStageSlots;
-    const int k0 = ik * kKStep;
-    const bool in = is < n && k0 + lc * 8 < p.K;
-    const uint32_t ko = static_cast<uint32_t>(k0) * 2u;
-#pragma unroll
-    for (int x = 0; x < XPW; ++x)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + (wave * XPW + x) * kBlockSlots), 16,
-                                               in ? xoff + ko + x * 8u * p.ldx * 2u : kOob, 0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < kWBlocks; ++q) {
-      const int c = col0(it, q >> 1) + (q & 1) * 8;
-      const int valid = __builtin_amdgcn_readfirstlane(max(0, min(8, N - c)));
-      const int row = valid > 0 ? (EPI == kEpiSwiGLU && q >= 2 ? N : 0) + c : 0;
-      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(p.W + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(row)) * p.ldw), 0, static_cast<uint32_t>(valid) * p.ldw * 2u, 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + kXSlots + (wave * kWBlocks + q) * kBlockSlots), 16,
-                                               in ? woff + ko : kOob, 0, 0, kAuxStream);
-    }
-    ++is;
-    if (++ik == KT) {
-      ik = 0;
-      ++it;
-    }
-  };
-
-#pragma unroll
-  for (int i = 0; i < NS - 1; ++i) issue();
-  Scale scale;
-  scale.load(p.nrm);
-  scale.finish(p.nrm, p.K, scratch, row_inv);   // read past the first step's barrier
-
-  f32x4 acc[2][TM];
-  auto clear = [&] {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int i = 0; i < TM; ++i) acc[t][i] = f32x4{0, 0, 0, 0};
-  };
-
-  auto epilogue = [&](int tile) {
-    float inv[TM][4];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) inv[i][r] = p.nrm.ssq_in ? row_inv[i * 16 + kg * 4 + r] : 1.f;
-    constexpr int kT = EPI == kEpiSwiGLU ? 1 : 2;
-#pragma unroll
-    for (int t = 0; t < kT; ++t) {
-      const int col = col0(tile, t) + li;
-      if (col >= N) continue;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = i * 16 + kg * 4 + r;
-          if (m >= M) continue;
-          const int64_t at = static_cast<int64_t>(m) * p.ldc + col;
-          const float v = acc[t][i][r] * inv[i][r];
-          if (EPI == kEpiSwiGLU) static_cast<uint16_t*>(p.C)[at] = f2bf(swiglu(v, acc[1][i][r] * inv[i][r]));
-          else static_cast<float*>(p.C)[at] = v;
-        }
-    }
-  };
-
-  // Partial tiles: slot 0 of a workgroup for a tile that began in an earlier
-  // one, slot 1 for the tile its run ends in.
-  constexpr uint32_t kSlotBytes = 2 * TM * 1024;
-  auto slot_rsrc = [&](int w, int slot) {
-    return __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(reinterpret_cast<char*>(p.part) + (static_cast<int64_t>(w * 2 + slot) * kWaves + wave) * kSlotBytes), 0,
-        kSlotBytes, 0x00020000);
-  };
-  int part_tile[2] = {-1, -1};
-
-  int ct = static_cast<int>(s0 / KT);
-  int left = KT - static_cast<int>(s0 - static_cast<int64_t>(ct) * KT);   // steps to the tile's end
-  clear();
-  for (int s = 0; s < n; ++s) {
-    // Step s has landed for this wave, and, past the barrier, for all; step
-    // s - 1's stage is free.
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * L) : "memory");
-    issue();
-    const u32x4* st = lds + (s % NS) * kStageSlots;
-    const u32x4* ws = st + kXSlots + wave * kWBlocks * kBlockSlots;
-#pragma unroll
-    for (int q = 0; q < kKStep / 32; ++q) {
-      const int sl = bslot(li & 7, 4 * q + kg) + (li >> 3) * kBlockSlots;
-      bf16x8 a[TM], w[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) w[t] = __builtin_bit_cast(bf16x8, ws[2 * t * kBlockSlots + sl]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = __builtin_bit_cast(bf16x8, st[2 * i * kBlockSlots + sl]);
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < TM; ++i) acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w[t], acc[t][i], 0, 0, 0);
-    }
-    if (--left == 0 || s == n - 1) {
-      const int64_t first = static_cast<int64_t>(ct) * KT;
-      if (left == 0 && first >= s0) {
-        epilogue(ct);
-      } else {
-        const int slot = s0 > first ? 0 : 1;
-        const __amdgpu_buffer_rsrc_t rp = slot_rsrc(wg, slot);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[t][i]), rp,
-                                                   static_cast<uint32_t>((t * TM + i) * 64 + lane) * 16u, 0, kAuxAgent);
-        part_tile[slot] = ct;
-      }
-      clear();
-      ++ct;
-      left = KT;
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-  for (int slot = 0; slot < 2; ++slot) {
-    const int t = part_tile[slot];
-    if (t < 0) continue;
-    const int64_t first = static_cast<int64_t>(t) * KT;
-    const int w0 = static_cast<int>(((first + 1) * G - 1) / total);
-    const int w1 = static_cast<int>(((first + KT) * G - 1) / total);
-    int* cnt = p.ctr + t * kWaves + wave;
-    int prev = 0;
-    if (lane == 0) prev = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    prev = __builtin_amdgcn_readfirstlane(prev);
-    if (prev != w1 - w0) continue;
-    asm volatile("" ::: "memory");
-    if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    clear();
-    constexpr int U = TM == 4 ? 4 : 8;
-    for (int j0 = w0; j0 <= w1; j0 += U) {
-      f32x4 v[U][2][TM];
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int w = min(j0 + j, w1);
-        const __amdgpu_buffer_rsrc_t rp = slot_rsrc(w, total * w / G > first ? 0 : 1);
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-            v[j][x][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                rp, static_cast<uint32_t>((x * TM + i) * 64 + lane) * 16u, 0, kAuxAgent));
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j)
-        if (j0 + j <= w1)
-#pragma unroll
-          for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int i = 0; i < TM; ++i) acc[x][i] += v[j][x][i];
-    }
-    epilogue(t);
-  }
-}
-
 __global__ void fill_zero_kernel(int* __restrict__ a, int na, int* __restrict__ b, int nb) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < na) a[i] = 0;
@@ -573,11 +362,9 @@ hipError_t launch_ring(const GemvArgs& a, int tn, int grid, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  if constexpr (XB <= 2) {
-    if (tn == 2) {
-      gemv_kernel<EPI, 2, XB, 2><<<grid, kThreads, 0, s>>>(a);
-      return hipGetLastError();
-    }
+  if (tn == 2) {
+    gemv_kernel<EPI, 2, XB, 2><<<grid, kThreads, 0, s>>>(a);
+    return hipGetLastError();
   }
   if (tn != 4) return hipErrorInvalidValue;
   gemv_kernel<EPI, 4, XB, 2><<<grid, kThreads, 0, s>>>(a);
@@ -586,20 +373,7 @@ hipError_t launch_ring(const GemvArgs& a, int tn, int grid, hipStream_t s) {
 
 template <int EPI>
 hipError_t launch_epi(const GemvArgs& a, const GemvPlan& pl, int grid, hipStream_t s) {
-  if (pl.stream) {
-    if constexpr (EPI == kEpiSwiGLU || EPI == kEpiF32) {
-      if (pl.xb == 4) gemv_stream_kernel<EPI, 2, kStreamStages><<<grid, kThreads, 0, s>>>(a);
-      else gemv_stream_kernel<EPI, 4, kStreamStages><<<grid, kThreads, 0, s>>>(a);
-      return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
-  }
-  switch (pl.xb) {
-    case 1: return launch_ring<EPI, 1>(a, pl.tn, grid, s);
-    case 2: return launch_ring<EPI, 2>(a, pl.tn, grid, s);
-    case 4: return launch_ring<EPI, 4>(a, pl.tn, grid, s);
-    default: return launch_ring<EPI, 8>(a, pl.tn, grid, s);
-  }
+  return pl.xb == 1 ? launch_ring<EPI, 1>(a, pl.tn, grid, s) : launch_ring<EPI, 2>(a, pl.tn, grid, s);
 }
 
 }  // namespace
@@ -629,12 +403,10 @@ hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   a.N = N;
   a.K = K;
   a.S = pl.S;
-  a.tiles = pl.tiles;
-  a.ksteps = (K + kKStep - 1) / kKStep;
   a.part = sc.part;
   a.ctr = sc.ctr;
   a.nrm = nrm;
-  const int grid = pl.stream ? kGemvStreamGrid : pl.tiles * pl.S;
+  const int grid = pl.tiles * pl.S;
   switch (epi) {
     case kEpiBf16: return launch_epi<kEpiBf16>(a, pl, grid, s);
     case kEpiAddF32: return launch_epi<kEpiAddF32>(a, pl, grid, s);

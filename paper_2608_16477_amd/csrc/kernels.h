@@ -83,7 +83,10 @@ inline int gemm_tiles_n(int epi, int N, int bn = 256) {
 // best so far only when modelled at least 1% cheaper, so near-ties keep
 // the earlier (larger) tile: at the mid model's gate|up, 1536 rows, the
 // split-tail 256 x 256 launch and 192 x 256 model within 0.1% of each
-// other, and the 256 x 256 one measured 248-250 against 253 us.
+// other, and the 256 x 256 one measured 248-250 against 253 us.  The
+// 128-row shapes spread a few hundred rows over more CUs: 500 rows of the mid
+// model's O 40.9 (192 x 128) -> 29.6 us (128 x 64), its down 118 -> 80; 320
+// rows of the large model's O 74 -> 44 us, its down 248 -> 135.
 struct GemmTile {
   int bm, bn;
 };
@@ -91,11 +94,14 @@ inline GemmTile gemm_tile(int epi, int M, int N) {
   struct Cand {
     int bm, bn, rate;   // rate: FLOP rate per CU, percent of 256 x 256
   };
-  static const Cand cands[] = {{256, 256, 100}, {256, 128, 77}, {192, 256, 85}, {192, 192, 80}, {192, 128, 70}};
+  static const Cand cands[] = {{256, 256, 100}, {256, 128, 77}, {192, 256, 85}, {192, 192, 80}, {192, 128, 70},
+                               {128, 128, 49}, {128, 64, 38}};
   GemmTile best{256, 256};
   double best_cost = 0;
   for (const Cand& c : cands) {
-    if (epi == kEpiSwiGLU && c.bn == 192) continue;   // gate and up blocks pair up
+    // gate|up: blocks pair up (no 192-wide tiles), and its many columns never
+    // leave so few tiles that the 128-row shapes paid
+    if (epi == kEpiSwiGLU && (c.bn == 192 || c.bm == 128)) continue;
     const int tiles = ((M + c.bm - 1) / c.bm) * gemm_tiles_n(epi, N, c.bn);
     const int per_xcd = (tiles + 7) / 8, rounds = (per_xcd + 31) / 32;
     double r = rounds;
@@ -109,17 +115,32 @@ inline GemmTile gemm_tile(int epi, int M, int N) {
   return best;
 }
 
-// K-range splits per tile.  Only GEMMs of a single 256-row M tile split
-// (their few tiles would leave most of the 256 CUs idle): each split keeps
-// at least 8 K-steps of 64 and the splits fill about 256 workgroups.  The
-// factor depends on N and K alone within M <= 256, and is 1 above, so a
-// row's arithmetic is the same in prefills of any two lengths on the same
-// side of 256 rows.
+// Launches of at most kGemmFewRows rows take one M tile, the shortest that
+// covers them, with columns of 128 B rows, or of 256 where the 128-wide tiles
+// need another round of the 256 CUs that the 256-wide ones do not (a 256-wide
+// round takes about 1.75 times as long): gate|up of the large model at 128
+// rows 129 -> 110 us.
+constexpr int kGemmFewRows = 256;
+inline GemmTile gemm_tile_few(int epi, int M, int N) {
+  auto rounds = [&](int bn) { return (gemm_tiles_n(epi, N, bn) + 255) / 256; };
+  const int bn = rounds(256) * 1.75 < rounds(128) ? 256 : 128;
+  if (M <= 64 && bn == 128) return {64, 128};
+  return {M <= 128 ? 128 : M <= 192 ? 192 : 256, bn};
+}
+
+// K-range splits per tile.  Only launches of at most 256 rows split (their
+// few tiles would leave most of the 256 CUs idle): 128-wide tiles times
+// splits fill at most 256 workgroups, and each split keeps at least 16 K-steps
+// of 64 (fewer splits, larger tiles and less partial-sum traffic than with
+// 256 x 256 tiles: at 256 rows Q|K|V / O / down of the large model 52 / 47 /
+// 94 -> 41 / 36 / 80 us, of the mid one 37 / 31 / 52 -> 27 / 21 / 41; at 64
+// rows 39 / 34 / 72 -> 26 / 23 / 54).  The factor depends on N and K alone
+// within M <= 256, and is 1 above, so a row's arithmetic is the same in
+// prefills of any two lengths on the same side of 256 rows.
 inline int gemm_ksplit(int epi, int M, int N, int K) {
-  if (M > 256 || N % 4 != 0) return 1;
-  const int tiles = gemm_tiles_n(epi, N), steps = (K + 63) / 64;
-  int s = 256 / tiles;
-  if (s > steps / 8) s = steps / 8;
+  if (M > kGemmFewRows || N % 4 != 0) return 1;
+  int s = 256 / gemm_tiles_n(epi, N, 128);
+  if (s > K / 1024) s = K / 1024;
   if (s > 16) s = 16;
   return s < 1 ? 1 : s;
 }
@@ -134,9 +155,19 @@ inline size_t gemm_split_bytes(int epi, int M, int N, int K) {
 // GEMM splits K (gemm_ksplit > 1), `part` (16-byte aligned, at least
 // gemm_split_bytes) receives the partial sums and a second kernel reduces
 // them into C; ldc must then be a multiple of 4.
+// `norm` (kEpiAddF32): where gemm_fuses_norm, the RMSNorm of the new C, h
+// [M][N] = bf16(C / rms(C) gain), is written by the reduction.
+struct GemmNorm {
+  const uint16_t* gain;
+  uint16_t* h;
+  float eps;
+};
+inline bool gemm_fuses_norm(int epi, int M, int N, int K) {
+  return epi == kEpiAddF32 && N <= 8192 && gemm_ksplit(epi, M, N, K) > 1;
+}
 hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C,
                        int ldc, int M, int N, int K, float* part, size_t part_bytes, hipStream_t s,
-                       unsigned long long* clk = nullptr);
+                       unsigned long long* clk = nullptr, const GemmNorm* norm = nullptr);
 
 }  // namespace pallas
 
@@ -276,54 +307,37 @@ hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, 
                                    int part_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM
-// C[m][n] (op) A[m] . B[n] for m < M <= 64 rows (gemv.hip); epilogues as
+// C[m][n] (op) A[m] . B[n] for m < M <= 16 rows (gemv.hip); epilogues as
 // launch_gemm.
 constexpr int kGemvMaxSplit = 8;
-constexpr int kGemvMaxRows = 64;
-constexpr int kGemvStreamGrid = 256;   // one workgroup per CU
+constexpr int kGemvMaxRows = 16;
 
-// How a projection runs.  Ring kernel: workgroups of 4 waves, each a tile of
-// tn blocks of 16 weight rows over 1 / S of K.  Stream kernel: kGemvStreamGrid
-// workgroups over tiles of 128 rows.
+// How a projection runs: workgroups of 4 waves, each a tile of tn blocks of
+// 16 weight rows over 1 / S of K.
 struct GemvPlan {
-  bool stream;
-  int xb;      // 8-row blocks of A covered: 1, 2, 4 or 8
+  int xb;      // 8-row blocks of A covered: 1 or 2
   int tn, S;
   int tiles;
-  size_t part_bytes() const {
-    const size_t tm = (xb + 1) / 2;
-    if (stream) return size_t(kGemvStreamGrid) * 2 * 4 * 2 * tm * 1024;
-    return S > 1 ? size_t(tiles) * S * tn * tm * 1024 : 0;
-  }
-  int counters() const { return stream ? tiles * 4 : S > 1 ? tiles : 0; }
+  size_t part_bytes() const { return S > 1 ? size_t(tiles) * S * tn * 1024 : 0; }
+  int counters() const { return S > 1 ? tiles : 0; }
   // Sum-of-squares partials of the residual epilogue, each 8 xb floats.
-  int norm_parts() const {
-    const int waves = 4 / ((xb + 1) / 2);
-    return tiles * (tn < waves ? tn : waves);
-  }
+  int norm_parts() const { return tiles * tn; }
 };
 // The plan of least modelled time whose partial sums fit in `room` bytes.  A
 // CU holds r workgroups (their LDS stages decide), and a full round of 256 r
 // of them takes K / S u r + c0: u = the time 256 CUs need for one k of tn
 // blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split adds 1 us +
 // 0.3 us per part (count, partial sums) and the partials' traffic.  Fitted to
-// (us, TN / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
+// (us, tn / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
 // 14.2 (2 / 4 at M = 8), of the large one 19.7 (4 / 3), 20.2 (1 / 1), 21.6
-// (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3); at M = 32
-// mid Q|K|V 18.0 (4 / 2), 19.6 (4 / 5).
+// (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3).
 inline GemvPlan gemv_plan(int epi, int M, int N, int K, size_t room) {
   GemvPlan best{};
-  const int xb = M <= 8 ? 1 : M <= 16 ? 2 : M <= 32 ? 4 : 8;
+  const int xb = M <= 8 ? 1 : 2;
   const int64_t rows = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;
-  if (M > 16 && (epi == kEpiSwiGLU || epi == kEpiF32) && rows >= 128 * 128) {
-    const GemvPlan st{true, xb, 0, 1, int((rows + 127) / 128)};
-    if (st.part_bytes() <= room) return st;
-  }
-  const int tm = (xb + 1) / 2;
   double best_t = 0;
   for (int tn = 1; tn <= 4; tn *= 2) {
     if (tn == 1 && (xb > 1 || epi == kEpiSwiGLU)) continue;
-    if (tn == 2 && xb > 2) continue;
     const int stages = tn == 1 ? 3 : 2;
     const int lds = 4 * stages * (2 * tn + xb) * 1088 + 1024;   // 8-row blocks of 68 x 16 bytes
     const int resident = 160 * 1024 / lds;
@@ -331,13 +345,13 @@ inline GemvPlan gemv_plan(int epi, int M, int N, int K, size_t room) {
     const int tiles = (N + per - 1) / per;
     const double u = tn * 32.0 * 256 / 5.5e6;                   // us per k and workgroup of a CU
     for (int S = 1; S <= kGemvMaxSplit; ++S) {
-      const GemvPlan pl{false, xb, tn, S, tiles};
+      const GemvPlan pl{xb, tn, S, tiles};
       const int64_t wgs = int64_t(tiles) * S;
       if (S > 1 && (K / (S * 256) < 4 || wgs > 256 * resident || pl.part_bytes() > room)) break;
       const double full = double(wgs / (256 * resident)), rest = double(wgs % (256 * resident));
       double t = full * (double(K) / S * u * resident + 3);
       if (rest > 0) t += double(K) / S * u * double((int(rest) + 255) / 256) + 3;
-      if (S > 1) t += 1 + 0.3 * S + 2.0 * S * rows * tm * 64 / 4e6;
+      if (S > 1) t += 1 + 0.3 * S + 2.0 * S * rows * 64 / 4e6;
       if (best_t == 0 || t < best_t * 0.999) {
         best = pl;
         best_t = t;

@@ -44,7 +44,8 @@ inline int64_t widest_projection(const pallas_model_config& c) {
 inline size_t gemv_room(const pallas_model_config& c, int r8) {
   return size_t(kGemvMaxSplit) * r8 * widest_projection(c) * 4;
 }
-// Sums of squares of up to 64 rows: at most hidden + 64 floats (GemvPlan).
+// Sums of squares of up to 16 rows: one partial of 16 floats per 16 columns
+// (GemvPlan, whole tiles of up to 64 columns).
 inline size_t norm_bytes(const pallas_model_config& c) { return (size_t(c.hidden) + 256) * 4; }
 
 inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, int64_t seqs) {
@@ -76,6 +77,7 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
     b = std::max(b, gemm_split_bytes(kEpiAddF32, rows, H, QD));
     b = std::max(b, gemm_split_bytes(kEpiSwiGLU, rows, c.ffn, H));
     b = std::max(b, gemm_split_bytes(kEpiAddF32, rows, H, c.ffn));
+    b = std::max(b, gemm_split_bytes(kEpiF32, rows, c.vocab, H));
     w.split_bytes = b;
     w.split = take(b);
   }

@@ -408,11 +408,14 @@ int run_prefill(const pallas_model* m, const pallas::RowMap& rm, int M, const in
   ap.d = d;
   ap.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(double(d)));
 
+  // Split O and down projections write the norm that follows themselves.
+  const bool o_norms = pallas::gemm_fuses_norm(pallas::kEpiAddF32, M, H, QD);
+  const bool down_norms = pallas::gemm_fuses_norm(pallas::kEpiAddF32, M, H, F);
   for (int l = 0; l < c.n_layers; ++l) {
     const pallas_layer_weights& L = m->layers[l];
     const bool last = l == c.n_layers - 1;
     const Planes pl = layer_planes(pool, l);
-    if (l > 0) PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.attn_norm), h, M, H, c.rms_eps, s), "rmsnorm");
+    if (l > 0 && !down_norms) PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.attn_norm), h, M, H, c.rms_eps, s), "rmsnorm");
     qp.q_gain = u16(L.q_norm);
     qp.k_gain = u16(L.k_norm);
     qp.k_plane = pl.k;
@@ -433,18 +436,20 @@ int run_prefill(const pallas_model* m, const pallas::RowMap& rm, int M, const in
     qp.qkv_ld = QKV;
     qp.kv_only = 0;
     PALLAS_TRY(PALLAS_K_QKV_EPI, pallas::launch_qkv_rope(qp, rm, M, s), "qkv epilogue");
+    const pallas::GemmNorm o_norm{u16(L.mlp_norm), h, c.rms_eps};
+    const pallas::GemmNorm down_norm{u16(m->layers[l + 1].attn_norm), h, c.rms_eps};
     ap.k_plane = pl.k;
     ap.v_plane = pl.v;
     PALLAS_TRY(PALLAS_K_ATTN, pallas::launch_attention_prefill(ap, rm, reinterpret_cast<float*>(ws + w.attn_split),
                                                                w.attn_split_bytes, s), "attention");
     PALLAS_TRY(PALLAS_K_GEMM_O, pallas::launch_gemm(pallas::kEpiAddF32, o, QD, u16(L.w_o), QD, r, H, M, H, QD, split, sb, s,
-                                                     pallas::profile_clock_slot(PALLAS_K_GEMM_O)), "o gemm");
-    PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.mlp_norm), h, M, H, c.rms_eps, s), "rmsnorm");
+                                                     pallas::profile_clock_slot(PALLAS_K_GEMM_O), &o_norm), "o gemm");
+    if (!o_norms) PALLAS_TRY(PALLAS_K_RMSNORM, pallas::launch_rmsnorm(r, u16(L.mlp_norm), h, M, H, c.rms_eps, s), "rmsnorm");
     PALLAS_TRY(PALLAS_K_GEMM_GATE_UP, pallas::launch_gemm(pallas::kEpiSwiGLU, h, H, u16(L.w_gate_up), H, act, F, M, F, H, split, sb, s,
                                                          pallas::profile_clock_slot(PALLAS_K_GEMM_GATE_UP)),
                "gate_up gemm");
     PALLAS_TRY(PALLAS_K_GEMM_DOWN, pallas::launch_gemm(pallas::kEpiAddF32, act, F, u16(L.w_down), F, r, H, M, H, F, split, sb, s,
-                                                        pallas::profile_clock_slot(PALLAS_K_GEMM_DOWN)), "down gemm");
+                                                        pallas::profile_clock_slot(PALLAS_K_GEMM_DOWN), &down_norm), "down gemm");
   }
   return PALLAS_OK;
 }
@@ -476,10 +481,22 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   // The norms inside the projections: O and down write h = r g of the norm
   // that follows, with the sums of squares of r; the next projection scales.
   // The first layer's comes normalised from the embedding kernel.
-  const int o_parts = pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD, sc.part_bytes).norm_parts();
-  const int down_parts = pallas::gemv_plan(pallas::kEpiAddF32, B, H, F, sc.part_bytes).norm_parts();
+  const int o_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD, sc.part_bytes).norm_parts();
+  const int down_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, F, sc.part_bytes).norm_parts();
   auto norm_in = [&](int parts) { return pallas::GemvNorm{parts ? ssq : nullptr, parts, c.rms_eps, nullptr, nullptr, nullptr}; };
   auto norm_out = [&](const void* gain) { return pallas::GemvNorm{nullptr, 0, c.rms_eps, u16(gain), h, ssq}; };
+  // More than kGemvMaxRows rows run the GEMM's 64-row tiles; O and down are
+  // then followed by the norm itself (in their split reduction, or a launch).
+  float* split = reinterpret_cast<float*>(ws + w.split);
+  auto project = [&](int epi, const uint16_t* A, const uint16_t* W, void* C, int N, int K, const pallas::GemvNorm& n) {
+    if (B <= pallas::kGemvMaxRows) return pallas::launch_gemv(epi, A, K, W, K, C, N, B, N, K, sc, n, s);
+    const pallas::GemmNorm gn{n.gain_out, h, c.rms_eps};
+    hipError_t e = pallas::launch_gemm(epi, A, K, W, K, C, N, B, N, K, split, w.split_bytes, s, nullptr,
+                                       n.gain_out ? &gn : nullptr);
+    if (e == hipSuccess && n.gain_out && !pallas::gemm_fuses_norm(epi, B, N, K))
+      e = pallas::launch_rmsnorm(static_cast<const float*>(C), n.gain_out, h, B, N, c.rms_eps, s);
+    return e;
+  };
   PALLAS_TRY(PALLAS_K_ROPE_TABLE, pallas::launch_rope_table(rm, B, d, c.rope_theta, rope, s), "rope table");
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(tokens, u16(m->embed), u16(m->layers[0].attn_norm), r, h, B, H,
                                           c.rms_eps, c.vocab, err, s), "embed");
@@ -502,24 +519,20 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   for (int l = 0; l < c.n_layers; ++l) {
     const pallas_layer_weights& L = m->layers[l];
     const Planes pl = layer_planes(pool, l);
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiBf16, h, H, u16(L.w_qkv), H, qkv, QKV, B, QKV, H, sc,
-                                                         norm_in(l > 0 ? down_parts : 0), s), "qkv proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiBf16, h, u16(L.w_qkv), qkv, QKV, H, norm_in(l > 0 ? down_parts : 0)),
+               "qkv proj");
     ap.q_gain = u16(L.q_norm);
     ap.k_gain = u16(L.k_norm);
     ap.k_plane = pl.k;
     ap.v_plane = pl.v;
     PALLAS_TRY(PALLAS_K_DECODE_ATTN, pallas::launch_attention_decode(ap, rm, part, w.part_splits, s), "decode attention");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiAddF32, o, QD, u16(L.w_o), QD, r, H, B, H, QD, sc,
-                                                         norm_out(L.mlp_norm), s), "o proj");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiSwiGLU, h, H, u16(L.w_gate_up), H, act, F, B, F, H, sc,
-                                                         norm_in(o_parts), s), "gate_up proj");
-    PALLAS_TRY(PALLAS_K_DECODE_PROJ,
-               pallas::launch_gemv(pallas::kEpiAddF32, act, F, u16(L.w_down), F, r, H, B, H, F, sc,
-                                   norm_out(l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : m->final_norm), s),
-               "down proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiAddF32, o, u16(L.w_o), r, H, QD, norm_out(L.mlp_norm)), "o proj");
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiSwiGLU, h, u16(L.w_gate_up), act, F, H, norm_in(o_parts)),
+               "gate_up proj");
+    const void* next = l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : m->final_norm;
+    PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiAddF32, act, u16(L.w_down), r, H, F, norm_out(next)), "down proj");
   }
-  PALLAS_TRY(PALLAS_K_DECODE_PROJ, pallas::launch_gemv(pallas::kEpiF32, h, H, u16(m->lm_head), H, logits, c.vocab, B, c.vocab,
-                                                       H, sc, norm_in(down_parts), s), "lm_head");
+  PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiF32, h, u16(m->lm_head), logits, c.vocab, H, norm_in(down_parts)), "lm_head");
   return PALLAS_OK;
 }
 
