@@ -397,9 +397,9 @@ double pallas_waste_bound(double t_max, double e_early, double t_avail);
 
 /* Per-kernel timing (tracing).  Kernel classes of the calls above: */
 typedef enum {
-  PALLAS_K_EMBED = 0,      /* token embedding + first RMSNorm */
+  PALLAS_K_EMBED = 0,      /* token embedding, first RMSNorm, rotary factors */
   PALLAS_K_RMSNORM = 1,    /* prefill only: decode folds its norms into the projections */
-  PALLAS_K_ROPE_TABLE = 2,
+  PALLAS_K_ROPE_TABLE = 2, /* none: the rotary factors come with PALLAS_K_EMBED */
   PALLAS_K_GEMM_QKV = 3,   /* prefill Q|K|V projection (K|V only in the last layer) */
   PALLAS_K_QKV_EPI = 4,    /* prefill QK-norm, rotary, paged K/V store */
   PALLAS_K_ATTN = 5,       /* prefill causal attention */

@@ -348,12 +348,6 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
   }
 }
 
-__global__ void fill_zero_kernel(int* __restrict__ a, int na, int* __restrict__ b, int nb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < na) a[i] = 0;
-  else if (i - na < nb) b[i - na] = 0;
-}
-
 template <int EPI, int XB>
 hipError_t launch_ring(const GemvArgs& a, int tn, int grid, hipStream_t s) {
   if constexpr (XB == 1 && EPI != kEpiSwiGLU) {
@@ -377,12 +371,6 @@ hipError_t launch_epi(const GemvArgs& a, const GemvPlan& pl, int grid, hipStream
 }
 
 }  // namespace
-
-hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s) {
-  if (na + nb <= 0) return hipSuccess;
-  fill_zero_kernel<<<(na + nb + 255) / 256, 256, 0, s>>>(a, na, b, nb);
-  return hipGetLastError();
-}
 
 hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C, int ldc, int M, int N,
                        int K, const GemvScratch& sc, const GemvNorm& nrm, hipStream_t s) {

@@ -192,18 +192,20 @@ __host__ __device__ inline int row_seq(const RowMap& rm, int row) {
 }
 
 // ------------------------------------------------------------ norms / embed
-// r[t] = float(E[ids[t]]); h[t] = bf16(rmsnorm(r[t]) * g)
+// r[t] = float(E[ids[t]]); h[t] = bf16(rmsnorm(r[t]) * g); tab[t][i] = (cos,
+// sin)(pos(t) * theta^(-2i/d)), evaluated in double; the spans are cleared
+// (by the kernel, so a captured graph holds no memset).
+struct ClearSpan {
+  int32_t* p;
+  int n;
+};
 hipError_t launch_embed_rmsnorm(const int32_t* ids, const uint16_t* embed, const uint16_t* gain,
                                 float* r, uint16_t* h, int rows, int H, float eps, int vocab,
-                                int32_t* err, hipStream_t s);
+                                int32_t* err, const RowMap& rm, int d, float theta, float* tab,
+                                ClearSpan a, ClearSpan b, hipStream_t s);
 // h[t] = bf16(rmsnorm(r[t]) * g)
 hipError_t launch_rmsnorm(const float* r, const uint16_t* gain, uint16_t* h, int rows, int H,
                           float eps, hipStream_t s);
-
-// ------------------------------------------------------------ rotary table
-// tab[t][i] = (cos, sin)(pos(t) * theta^(-2i/d)), evaluated in double
-hipError_t launch_rope_table(const RowMap& rm, int rows, int d, float theta, float* tab,
-                             hipStream_t s);
 
 // ------------------------------------------------------------ QKV epilogue
 struct QkvParams {
@@ -240,10 +242,12 @@ struct AttnParams {
 // Key-range splits of prefill attention.  Only calls of at most 256 rows
 // split (as the GEMMs, so longer prefills keep identical bytes per row),
 // and only when their (query block, KV head) workgroups are too few to fill
-// the chip: up to 8 splits of at least 2 key tiles of 64.
+// the chip: up to 8 splits of at least 2 key tiles of 64, as many as run at
+// once (two workgroups per CU: a 256-token chunk at position 2744 of the large
+// model, 144 workgroups, took 55 us in 576 and 47 in 432).
 inline int attn_prefill_splits(int rows, int workgroups, int max_tiles) {
   if (rows > 256 || workgroups >= 256) return 1;
-  int s = (512 + workgroups - 1) / workgroups;
+  int s = 512 / workgroups;
   if (s > 8) s = 8;
   if (s > max_tiles / 2) s = max_tiles / 2;
   if (s < 1) return 1;
@@ -382,7 +386,5 @@ struct GemvNorm {
 };
 hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, int ldb, void* C, int ldc, int M, int N,
                        int K, const GemvScratch& sc, const GemvNorm& nrm, hipStream_t s);
-// a[0..na) = 0 and b[0..nb) = 0 (a kernel, so it can sit in a captured graph).
-hipError_t launch_zero_counters(int* a, int na, int* b, int nb, hipStream_t s);
 
 }  // namespace pallas

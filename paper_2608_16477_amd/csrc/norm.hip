@@ -1,4 +1,4 @@
-// Token embedding, RMSNorm and the rotary angle table.
+// Token embedding with the first RMSNorm and the rotary factors, and RMSNorm.
 //
 // RMSNorm: h = bf16(x * (mean(x^2) + eps)^(-1/2) * g) with x the float32
 // residual row; one workgroup per row, float4 loads, a wave64 butterfly sum
@@ -33,11 +33,31 @@ __device__ __forceinline__ void store_norm4(uint16_t* h, const uint16_t* g, int 
   *reinterpret_cast<u32x2*>(h + i) = out;
 }
 
+// The start of a call, one workgroup per row: the row's embedding as its
+// residual, the first RMSNorm, the row's rotary factors (tab[row][i] = (cos,
+// sin)(pos theta^(-2i/d)), in double), and clears of the counters a decode
+// step needs.  One launch instead of three of 3 to 5 us.
 __global__ __launch_bounds__(kThreads) void embed_rmsnorm_kernel(
     const int32_t* __restrict__ ids, const uint16_t* __restrict__ E, const uint16_t* __restrict__ g,
-    float* __restrict__ r, uint16_t* __restrict__ h, int H, float eps, int vocab, int32_t* err) {
+    float* __restrict__ r, uint16_t* __restrict__ h, int H, float eps, int vocab, int32_t* err, RowMap rm, int half,
+    double log2_theta_over_half, float* __restrict__ tab, ClearSpan ca, ClearSpan cb) {
   __shared__ float sh[kThreads / 64];
   const int t = blockIdx.x;
+  for (int i = t * kThreads + threadIdx.x; i < ca.n + cb.n; i += gridDim.x * kThreads) {
+    if (i < ca.n) ca.p[i] = 0;
+    else cb.p[i - ca.n] = 0;
+  }
+  if (threadIdx.x < half) {
+    const int s = row_seq(rm, t);
+    const double pos = double(rm.base_pos[s] + (t - rm.cu[s]));
+    // theta^(-2i/d) = 2^(-i * log2(theta) / (d/2))
+    const double inv_freq = exp2(-double(threadIdx.x) * log2_theta_over_half);
+    double sn, cs;
+    sincos(pos * inv_freq, &sn, &cs);
+    float* dst = tab + 2 * (static_cast<int64_t>(t) * half + threadIdx.x);
+    dst[0] = static_cast<float>(cs);
+    dst[1] = static_cast<float>(sn);
+  }
   int id = ids[t];
   if (id < 0 || id >= vocab) {
     if (threadIdx.x == 0 && err) atomicOr(err, static_cast<int32_t>(PALLAS_DEVERR_TOKEN));
@@ -108,28 +128,17 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const float* __restri
     store_norm4(hh, g, i, *reinterpret_cast<const f32x4*>(rr + i), inv);
 }
 
-__global__ void rope_table_kernel(RowMap rm, int rows, int half, double log2_theta_over_half,
-                                  float* __restrict__ tab) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * half) return;
-  const int t = idx / half, i = idx - t * half;
-  const int s = row_seq(rm, t);
-  const double pos = double(rm.base_pos[s] + (t - rm.cu[s]));
-  // theta^(-2i/d) = 2^(-i * log2(theta) / (d/2))
-  const double inv_freq = exp2(-double(i) * log2_theta_over_half);
-  double sn, cs;
-  sincos(pos * inv_freq, &sn, &cs);
-  tab[2 * idx] = static_cast<float>(cs);
-  tab[2 * idx + 1] = static_cast<float>(sn);
-}
-
 }  // namespace
 
 hipError_t launch_embed_rmsnorm(const int32_t* ids, const uint16_t* embed, const uint16_t* gain,
                                 float* r, uint16_t* h, int rows, int H, float eps, int vocab,
-                                int32_t* err, hipStream_t s) {
+                                int32_t* err, const RowMap& rm, int d, float theta, float* tab,
+                                ClearSpan a, ClearSpan b, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  embed_rmsnorm_kernel<<<rows, kThreads, 0, s>>>(ids, embed, gain, r, h, H, eps, vocab, err);
+  const int half = d / 2;
+  if (half > kThreads) return hipErrorInvalidValue;
+  embed_rmsnorm_kernel<<<rows, kThreads, 0, s>>>(ids, embed, gain, r, h, H, eps, vocab, err, rm, half,
+                                                 log2(double(theta)) / half, tab, a, b);
   return hipGetLastError();
 }
 
@@ -140,15 +149,6 @@ hipError_t launch_rmsnorm(const float* r, const uint16_t* gain, uint16_t* h, int
     rmsnorm_reg_kernel<<<rows, kThreads, 0, s>>>(r, gain, h, H, eps);
   else
     rmsnorm_kernel<<<rows, kThreads, 0, s>>>(r, gain, h, H, eps);
-  return hipGetLastError();
-}
-
-hipError_t launch_rope_table(const RowMap& rm, int rows, int d, float theta, float* tab,
-                             hipStream_t s) {
-  const int half = d / 2;
-  const int n = rows * half;
-  if (n <= 0) return hipSuccess;
-  rope_table_kernel<<<(n + 255) / 256, 256, 0, s>>>(rm, rows, half, log2(double(theta)) / half, tab);
   return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 // sequences.  Every check runs before anything is enqueued, so a rejected
 // call writes nothing.
 #include <algorithm>
+#include <array>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -379,9 +380,8 @@ int run_prefill(const pallas_model* m, const pallas::RowMap& rm, int M, const in
   const int H = c.hidden, d = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, F = c.ffn;
   const int QKV = (Hq + 2 * Hkv) * d, QD = Hq * d, KVD = 2 * Hkv * d;
 
-  PALLAS_TRY(PALLAS_K_ROPE_TABLE, pallas::launch_rope_table(rm, M, d, c.rope_theta, rope, s), "rope table");
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(ids, u16(m->embed), u16(m->layers[0].attn_norm), r, h, M, H,
-                                          c.rms_eps, c.vocab, err, s), "embed");
+                                          c.rms_eps, c.vocab, err, rm, d, c.rope_theta, rope, {}, {}, s), "embed");
   pallas::QkvParams qp;
   qp.rope = rope;
   qp.q_out = q;
@@ -475,9 +475,11 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   const pallas::GemvScratch sc{reinterpret_cast<float*>(ws + w.gemv_part), w.gemv_part_bytes,
                                reinterpret_cast<int*>(ws + w.gemv_ctr), w.gemv_ctr_count};
   const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
-  if (hipError_t e = pallas::launch_zero_counters(sc.ctr, sc.ctr_count, reinterpret_cast<int*>(part), as.counters, s);
-      e != hipSuccess)
-    return hip_fail(e, "counters");
+  int gemv_counters = 0;   // those the step's plans use
+  if (B <= pallas::kGemvMaxRows)
+    for (const auto& p : {std::array<int, 3>{pallas::kEpiBf16, QKV, H}, {pallas::kEpiAddF32, H, QD}, {pallas::kEpiSwiGLU, F, H},
+                          {pallas::kEpiAddF32, H, F}, {pallas::kEpiF32, c.vocab, H}})
+      gemv_counters = std::max(gemv_counters, pallas::gemv_plan(p[0], B, p[1], p[2], sc.part_bytes).counters());
   // The norms inside the projections: O and down write h = r g of the norm
   // that follows, with the sums of squares of r; the next projection scales.
   // The first layer's comes normalised from the embedding kernel.
@@ -497,9 +499,10 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
       e = pallas::launch_rmsnorm(static_cast<const float*>(C), n.gain_out, h, B, N, c.rms_eps, s);
     return e;
   };
-  PALLAS_TRY(PALLAS_K_ROPE_TABLE, pallas::launch_rope_table(rm, B, d, c.rope_theta, rope, s), "rope table");
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(tokens, u16(m->embed), u16(m->layers[0].attn_norm), r, h, B, H,
-                                          c.rms_eps, c.vocab, err, s), "embed");
+                                          c.rms_eps, c.vocab, err, rm, d, c.rope_theta, rope,
+                                          {sc.ctr, gemv_counters}, {reinterpret_cast<int32_t*>(part), as.counters}, s),
+             "embed");
   pallas::DecodeAttnParams ap;
   ap.qkv = qkv;
   ap.qkv_ld = QKV;
