@@ -59,13 +59,16 @@ constexpr int kGroupM = 6;
 //              has to hide its loads behind).
 // The 192-row shapes exist for row counts such as 1536 = 8 x 192, where
 // 256-row tiles leave CUs idle (gemm_tile).
-//   128 x 256, 128 x 128, 128 x 64: waves 2 x 4, 4 x 2, 4 x 2, each 64 x 64,
-//              32 x 64, 32 x 32; 3, 4 and 4-deep rings;
+//   128 x 256, 128 x 128, 128 x 96, 128 x 64: waves 2 x 4, then 4 x 2, each
+//              64 x 64, 32 x 64, 32 x 48, 32 x 32; 3-deep, then 4-deep rings;
 //   64 x 128:  waves 2 x 4, each 32 x 32; a 4-deep ring.
 // They serve launches of few rows.  Small tiles are bound by LDS: at 128
 // bytes per clock the operand reads and writes of a K-step take 704 cycles
-// for 128 x 64, 1024 for 128 x 128 and 1216 for 192 x 128 (measured 0.34,
-// 0.55 and 0.60 us per step), against 256, 512 and 768 cycles of MFMAs.
+// for 128 x 64, 864 for 128 x 96, 1024 for 128 x 128 and 1216 for 192 x 128
+// (measured 0.34, 0.48, 0.55 and 0.60 us per step), against 256, 384, 512 and
+// 768 cycles of MFMAs.  (With 4 waves of 64 x 48 the reads of a 128 x 96 step
+// fall to 672 cycles, but one wave per SIMD leaves their latency open: the
+// same time; 128 x 128 and 192 x 128 with 4 waves were 5 to 30% slower.)
 template <int BM_, int BN_>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_;
@@ -93,8 +96,8 @@ __device__ __forceinline__ int swz(int row, int c) { return row * kChunks + (c ^
 
 // Operand loads into LDS.  A loader wave issues N load instructions per
 // operand tile and K-step; instruction i fills slots [(wave*N+i)*64, +64),
-// tile rows 8 (wave N + i) + lane / 8.  The lane's chunk swizzle depends on
-// i only through its parity, so the lane keeps two offsets, voff[0..1]
+// tile rows 8 (wave N + i) + lane / 8.  For a given wave the lane's chunk
+// swizzle depends on i only through its parity, so the lane keeps two offsets, voff[0..1]
 // (its row's byte offset plus its chunk's column offset for instructions
 // 0 and 1), and instruction i adds the 8 (i - i mod 2) rows past those,
 // `step` bytes each, in a vector register computed at the load (16 offsets
@@ -220,7 +223,6 @@ __device__ __forceinline__ void gemm_workgroup(const GemmParams& p, LdsRing<BM_,
     }
     b_off[i] = static_cast<uint32_t>(gn * p.ldb * 2 + chunk * 16);
   }
-  static_assert(kLoadsA % 2 == 0 && kLoadsB % 2 == 0, "loads come in even/odd pairs");
   const uint32_t a_step = 8u * p.lda * 2u, b_step = 8u * p.ldb * 2u;
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)p.A, 0, p.a_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)p.B, 0, p.b_bytes, 0x00020000);
@@ -642,6 +644,7 @@ void launch_tiles(const GemmParams& p, int bm, int bn, int grid, hipStream_t s) 
   if constexpr (EPI != kEpiSwiGLU) {
     PALLAS_GEMM_TILE(192, 192, 0)
     PALLAS_GEMM_TILE(128, 128, 0)
+    PALLAS_GEMM_TILE(128, 96, 0)
     PALLAS_GEMM_TILE(128, 64, 0)
   }
   if (p.tail_half) gemm_bf16_tail_kernel<EPI><<<grid, kThreads, 0, s>>>(p);

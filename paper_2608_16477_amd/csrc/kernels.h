@@ -86,7 +86,10 @@ inline int gemm_tiles_n(int epi, int N, int bn = 256) {
 // other, and the 256 x 256 one measured 248-250 against 253 us.  The
 // 128-row shapes spread a few hundred rows over more CUs: 500 rows of the mid
 // model's O 40.9 (192 x 128) -> 29.6 us (128 x 64), its down 118 -> 80; 320
-// rows of the large model's O 74 -> 44 us, its down 248 -> 135.
+// rows of the large model's O 74 -> 44 us, its down 248 -> 135.  128 x 96 is
+// for launches that 128 x 64 would run in two rounds: 500 rows of the large
+// model's O 69 (128 x 128) -> 63 us, its down 232 -> 201; 640 rows of the mid
+// model's O 39 -> 35, its down 114 -> 102.
 struct GemmTile {
   int bm, bn;
 };
@@ -95,12 +98,12 @@ inline GemmTile gemm_tile(int epi, int M, int N) {
     int bm, bn, rate;   // rate: FLOP rate per CU, percent of 256 x 256
   };
   static const Cand cands[] = {{256, 256, 100}, {256, 128, 77}, {192, 256, 85}, {192, 192, 80}, {192, 128, 70},
-                               {128, 128, 49}, {128, 64, 38}};
+                               {128, 128, 49}, {128, 96, 44}, {128, 64, 38}};
   GemmTile best{256, 256};
   double best_cost = 0;
   for (const Cand& c : cands) {
-    // gate|up: blocks pair up (no 192-wide tiles), and its many columns never
-    // leave so few tiles that the 128-row shapes paid
+    // gate|up: blocks pair up (no 96 or 192-wide tiles), and its many columns
+    // never leave so few tiles that the 128-row shapes paid
     if (epi == kEpiSwiGLU && (c.bn == 192 || c.bm == 128)) continue;
     const int tiles = ((M + c.bm - 1) / c.bm) * gemm_tiles_n(epi, N, c.bn);
     const int per_xcd = (tiles + 7) / 8, rounds = (per_xcd + 31) / 32;

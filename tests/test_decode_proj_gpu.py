@@ -1,9 +1,9 @@
 """The decode projections at the row counts and shapes where their plan
 changes, against the oracle's decode layer by layer over random caches: 1, 8,
-9, 16, 17, 32, 33 and 64 rows; K split over workgroups and not; weights wide
-enough for the shared-stage kernel (gate|up and lm_head of at least 16384
-rows, more than 16 rows) and not; row counts that are not multiples of a tile;
-a K that is not a multiple of 64.  Logits and residual within 1e-2 max|ref|
+9, 16, 17, 32, 33 and 64 rows (the streaming kernel up to 16 rows, the GEMM's
+64-row tiles above); K split over workgroups and not; more and fewer weight
+rows than the workgroups take at once; weight rows that are not multiples of a
+tile; a K that is not a multiple of 64.  Logits and residual within 1e-2 max|ref|
 per row (as the other decode tests), two calls bit for bit."""
 import numpy as np
 import pytest

@@ -20,6 +20,8 @@ ROWS = [1, 64, 65, 128, 129, 192, 193, 256, 257, 320, 500]
 SHAPES = {
     "wide": configs.TINY.replace(hidden=256, n_q_heads=4, n_kv_heads=2, ffn=16448, vocab=512),
     "deep": configs.TINY.replace(hidden=1024, n_q_heads=32, n_kv_heads=4, ffn=4112, vocab=512, qk_norm=True),
+    # 5120 Q|K|V columns: 128 x 96 tiles at 500 rows, the last row and column tile partial
+    "broad": configs.TINY.replace(hidden=320, n_q_heads=64, n_kv_heads=8, head_dim=64, ffn=1040, vocab=512),
 }
 
 
