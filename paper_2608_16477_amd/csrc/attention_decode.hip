@@ -247,40 +247,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     const int hs = ps * HPP + hsub;
     if (hs >= G + (last ? 2 : 0)) continue;
     u32x2 olo = lov[ps], ohi = hiv[ps];
-    if (hs <= G) {
-      float x0[4] = {bflo(olo.x), bfhi(olo.x), bflo(olo.y), bfhi(olo.y)};
-      float x1[4] = {bflo(ohi.x), bfhi(ohi.x), bflo(ohi.y), bfhi(ohi.y)};
-      if (p.qk_norm) {
-        float ss = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
-        if constexpr (LPH == 16) {
-          ss = row16_sum(ss);
-        } else {
-#pragma unroll
-          for (int o = LPH / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, kWave);
-        }
-        const float inv = rsqrtf(ss / D + p.eps);
-        const u32x2 g0 = hs < G ? gq[0] : gk[0], g1 = hs < G ? gq[1] : gk[1];
-        const float ga[4] = {bflo(g0.x), bfhi(g0.x), bflo(g0.y), bfhi(g0.y)};
-        const float gb[4] = {bflo(g1.x), bfhi(g1.x), bflo(g1.y), bfhi(g1.y)};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x0[e] = x0[e] * inv * ga[e];
-          x1[e] = x1[e] * inv * gb[e];
-        }
-      }
-      const float cs[4] = {cs01.x, cs01.z, cs23.x, cs23.z};
-      const float sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
-      float y0[4], y1[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y0[e] = x0[e] * cs[e] - x1[e] * sn[e];
-        y1[e] = x1[e] * cs[e] + x0[e] * sn[e];
-      }
-      olo = u32x2{pack_bf2(y0[0], y0[1]), pack_bf2(y0[2], y0[3])};
-      ohi = u32x2{pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3])};
-    }
+    if (hs <= G) norm_rope4<D>(olo, ohi, p.qk_norm, hs < G ? gq[0] : gk[0], hs < G ? gq[1] : gk[1], p.eps, cs01, cs23);
     *reinterpret_cast<u32x2*>(&heads[hs][4 * j]) = olo;
     *reinterpret_cast<u32x2*>(&heads[hs][HALF + 4 * j]) = ohi;
   }

@@ -70,12 +70,6 @@ constexpr int kDppXor2 = 0x4E;    // quad_perm [2, 3, 0, 1]
 constexpr int kDppRor4 = 0x124;   // row_ror:4
 constexpr int kDppRor8 = 0x128;   // row_ror:8
 
-// Sum of the 4 lanes of a quad (distances 1, 2).
-__device__ __forceinline__ float quad_sum(float v) {
-  v += dpp_read<kDppXor1>(v);
-  v += dpp_read<kDppXor2>(v);
-  return v;
-}
 // Sum of a 16-lane row (distances 8, 4, 2, 1).
 __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_read<kDppRor8>(v);
@@ -104,6 +98,46 @@ __device__ __forceinline__ float wave_max(float v) {
   r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
   return row16_max(v);
+}
+
+// QK-norm (when `norm`) and rotary embedding of four pairs of a D-wide head:
+// a lane holds elements [4j, 4j + 4) in `lo` and [4j + D/2, 4j + D/2 + 4) in
+// `hi`, their gains in g0 and g1, and (cos, sin) of pairs 4j .. 4j + 3 in cs01
+// and cs23.  The D / 8 lanes of a head are neighbours and all active.
+template <int D>
+__device__ __forceinline__ void norm_rope4(u32x2& lo, u32x2& hi, bool norm, u32x2 g0, u32x2 g1, float eps, f32x4 cs01,
+                                           f32x4 cs23) {
+  float x0[4] = {bflo(lo.x), bfhi(lo.x), bflo(lo.y), bfhi(lo.y)};
+  float x1[4] = {bflo(hi.x), bfhi(hi.x), bflo(hi.y), bfhi(hi.y)};
+  if (norm) {
+    float ss = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
+    if constexpr (D / 8 == 16) {
+      ss = row16_sum(ss);
+    } else {
+#pragma unroll
+      for (int o = D / 16; o > 0; o >>= 1) ss += __shfl_xor(ss, o, kWave);
+    }
+    const float inv = rsqrtf(ss / D + eps);
+    const float ga[4] = {bflo(g0.x), bfhi(g0.x), bflo(g0.y), bfhi(g0.y)};
+    const float gb[4] = {bflo(g1.x), bfhi(g1.x), bflo(g1.y), bfhi(g1.y)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x0[e] = x0[e] * inv * ga[e];
+      x1[e] = x1[e] * inv * gb[e];
+    }
+  }
+  const float cs[4] = {cs01.x, cs01.z, cs23.x, cs23.z};
+  const float sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
+  float y0[4], y1[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    y0[e] = x0[e] * cs[e] - x1[e] * sn[e];
+    y1[e] = x1[e] * cs[e] + x0[e] * sn[e];
+  }
+  lo = u32x2{pack_bf2(y0[0], y0[1]), pack_bf2(y0[2], y0[3])};
+  hi = u32x2{pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3])};
 }
 
 }  // namespace pallas

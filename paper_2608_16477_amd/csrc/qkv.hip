@@ -35,8 +35,6 @@ __global__ __launch_bounds__(kThreads) void qkv_rope_kernel(QkvParams p, RowMap 
   const int64_t slot = (static_cast<int64_t>(pg) * p.page + pos % p.page) * p.Hkv;
   const f32x4* rope = reinterpret_cast<const f32x4*>(p.rope + (static_cast<int64_t>(row) * HALF + 4 * j) * 2);
   const f32x4 cs01 = rope[0], cs23 = rope[1];   // (cos, sin) of pairs 4j .. 4j+3
-  const float cs[4] = {cs01.x, cs01.z, cs23.x, cs23.z};
-  const float sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
   const uint16_t* src_row = p.qkv + static_cast<int64_t>(row) * p.qkv_ld;
   bool flagged = false;
 
@@ -63,41 +61,15 @@ __global__ __launch_bounds__(kThreads) void qkv_rope_kernel(QkvParams p, RowMap 
     const int hh = hl + (p.kv_only ? p.Hq : 0); // head in [0, Hq + 2 Hkv)
     const bool is_q = hh < p.Hq;
     const bool is_k = !is_q && hh < p.Hq + p.Hkv;
-    const u32x2 lo = lov[ps], hi = hiv[ps];
-    float x0[4] = {bflo(lo.x), bfhi(lo.x), bflo(lo.y), bfhi(lo.y)};
-    float x1[4] = {bflo(hi.x), bfhi(hi.x), bflo(hi.y), bfhi(hi.y)};
-    u32x2 olo = lo, ohi = hi;
+    u32x2 olo = lov[ps], ohi = hiv[ps];
     if (is_q || is_k) {
+      const uint16_t* gsrc = is_q ? p.q_gain : p.k_gain;
+      u32x2 g0{}, g1{};
       if (p.qk_norm) {
-        float ss = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
-        if constexpr (LPH == 16) {
-          ss = row16_sum(ss);
-        } else {
-#pragma unroll
-          for (int o = LPH / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, kWave);
-        }
-        const float inv = rsqrtf(ss / D + p.eps);
-        const uint16_t* gsrc = is_q ? p.q_gain : p.k_gain;
-        const u32x2 g0 = *reinterpret_cast<const u32x2*>(gsrc + 4 * j);
-        const u32x2 g1 = *reinterpret_cast<const u32x2*>(gsrc + HALF + 4 * j);
-        const float ga[4] = {bflo(g0.x), bfhi(g0.x), bflo(g0.y), bfhi(g0.y)};
-        const float gb[4] = {bflo(g1.x), bfhi(g1.x), bflo(g1.y), bfhi(g1.y)};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x0[e] = x0[e] * inv * ga[e];
-          x1[e] = x1[e] * inv * gb[e];
-        }
+        g0 = *reinterpret_cast<const u32x2*>(gsrc + 4 * j);
+        g1 = *reinterpret_cast<const u32x2*>(gsrc + HALF + 4 * j);
       }
-      float y0[4], y1[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y0[e] = x0[e] * cs[e] - x1[e] * sn[e];
-        y1[e] = x1[e] * cs[e] + x0[e] * sn[e];
-      }
-      olo = u32x2{pack_bf2(y0[0], y0[1]), pack_bf2(y0[2], y0[3])};
-      ohi = u32x2{pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3])};
+      norm_rope4<D>(olo, ohi, p.qk_norm, g0, g1, p.eps, cs01, cs23);
     }
     if (!active) continue;
     uint16_t* dst;
