@@ -275,7 +275,10 @@ int pallas_assemble_kv(const pallas_kv_pool* dst, const int32_t* d_dst_block_tab
  * h_positions[i] = n_i; it attends to cached positions [0, n_i) and to
  * itself, writes its own K/V into slot n_i (the table needs capacity
  * n_i + 1), and the float32 logits of the next token go to
- * d_logits[i][0..V).  num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
+ * d_logits[i][0..V).  Rows may be tokens of one sequence, or share pages in
+ * other ways: in each layer every row's K/V counts as stored before any row
+ * attends.  (Which K/V a slot gets that two rows write is undefined.)
+ * num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
  * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention keeps one
  * partial record per 64 keys in a workspace section of fixed size), and
  * n_i + 1 <= max_pages * page (OUT_OF_RANGE).  For more than 8

@@ -16,6 +16,14 @@
 // split into three bf16 parts whose sum is P exactly, one MFMA each; the
 // matrix cores are idle here, and the kernel is bound by the K/V stream.
 //
+// A row may attend to slots that other rows of the call write (several tokens
+// of one sequence, a table that another row's reaches).  Those rows' stores
+// come from other workgroups of this launch, in no order, so such keys are
+// taken from the rows' projections instead: the result is that of storing
+// every row's K and V before any attention.  Finding them costs a compare of
+// the split's pages per row, behind the first loads (32 sequences: 2659 ->
+// 2682 us for 12 layers); a store launch of its own would be 4 to 5 us a layer.
+//
 // Splits are merged by the last workgroup of a (sequence, KV head) to
 // arrive: partial records and an arrival count through agent-scope accesses,
 // as the skinny projections do.
@@ -147,6 +155,32 @@ __device__ __forceinline__ void issue_block(const DecodeAttnParams& p, int kh, i
   }
 }
 
+// K (normalised and rotated) and V of row `row` of the call, as key `r` of the
+// 32-key block in stage Kst, Vst.  Rare: kept out of the stream's registers.
+template <int D>
+__device__ __forceinline__ void put_row(const DecodeAttnParams& p, int kh, int row, int r, u32x4* Kst, u32x4* Vst) {
+  constexpr int CH = D / 8, LPH = D / 8, HALF = D / 2;
+  const int lane = threadIdx.x & 63, j = lane % LPH;
+  if (lane >= 2 * LPH) return;                  // lanes [0, LPH): K, [LPH, 2 LPH): V
+  const bool isk = lane < LPH;
+  const uint16_t* src = p.qkv + static_cast<int64_t>(row) * p.qkv_ld +
+                        static_cast<int64_t>(p.Hq + (isk ? 0 : p.Hkv) + kh) * D;
+  u32x2 lo = *reinterpret_cast<const u32x2*>(src + 4 * j), hi = *reinterpret_cast<const u32x2*>(src + HALF + 4 * j);
+  if (isk) {
+    u32x2 g0{}, g1{};
+    if (p.qk_norm) {
+      g0 = *reinterpret_cast<const u32x2*>(p.k_gain + 4 * j);
+      g1 = *reinterpret_cast<const u32x2*>(p.k_gain + HALF + 4 * j);
+    }
+    const f32x4* rope = reinterpret_cast<const f32x4*>(p.rope + (static_cast<int64_t>(row) * HALF + 4 * j) * 2);
+    norm_rope4<D>(lo, hi, p.qk_norm, g0, g1, p.eps, rope[0], rope[1]);
+  }
+  u32x4* st = isk ? Kst : Vst;
+  const int swz = isk ? swz_k<CH>(r) : swz_v<CH>(r), c = j / 2;
+  reinterpret_cast<u32x2*>(st + r * CH + (c ^ swz))[j % 2] = lo;
+  reinterpret_cast<u32x2*>(st + r * CH + ((c + CH / 2) ^ swz))[j % 2] = hi;
+}
+
 template <int D, int kWaves>
 __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnParams p, RowMap rm, DecodeSplits sp,
                                                                float* __restrict__ part_o,
@@ -194,6 +228,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     if (pi * kPage < j1) entry = bt[pi];
     if (entry < 0 || entry >= p.num_pages) entry = -1;
   }
+  int wpos = lane < rm.n_seqs ? rm.base_pos[lane] : 0;   // lane i: the position row i writes
   // The row's Q heads (and K and V heads): a lane owns rotary pairs 4 j .. 4 j + 3.
   const int j = t % LPH, hsub = t / LPH;
   u32x2 lov[NPASS], hiv[NPASS];
@@ -222,7 +257,11 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   f32x4 cs01 = rope[0], cs23 = rope[1];         // (cos, sin) of pairs 4j .. 4j+3
 #pragma unroll
   for (int ps = 0; ps < NPASS; ++ps) asm volatile("" : "+v"(lov[ps]), "+v"(hiv[ps]));
-  asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry));
+  asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry), "+v"(wpos));
+  // The page it writes: not waited for before the stream starts.
+  int wpage = -1;
+  if (rm.n_seqs > 1 && lane < rm.n_seqs) wpage = p.bt[static_cast<int64_t>(lane) * p.max_pages + wpos / kPage];
+  asm volatile("" ::: "memory");
 
   // Wave w walks blocks w, w + 2, ... of the split.
   const int nblk = (j1 - j0 + kBlk - 1) / kBlk;
@@ -265,6 +304,20 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   const int vkey = 4 * q4 + (l16 >> 2);
   const uint32_t vb0 = static_cast<uint32_t>(vkey * D * 2 + ((swz_v<CH>(vkey) | ((l16 & 3) >> 1)) * 16) + (l16 & 1) * 8);
 
+  // Cached slots of this split that a row of this call writes (bit r of lane
+  // l: slot r of the split's page l).  Their K/V may not be in the pool yet:
+  // they are taken from that row, as if every row had stored its own first.
+  uint32_t fresh = 0;
+  if (rm.n_seqs > 1) {
+    for (int i = 0; i < rm.n_seqs; ++i) {
+      const int pg = __builtin_amdgcn_readlane(wpage, i), r = __builtin_amdgcn_readlane(wpos, i) % kPage;
+      if (entry == pg) fresh |= 1u << r;
+    }
+    const int cached = max(0, min(kPage, n - j0 - lane * kPage));
+    fresh = entry < 0 ? 0 : fresh & ((1u << cached) - 1);
+  }
+  const bool any_fresh = __builtin_amdgcn_ballot_w64(fresh != 0) != 0;
+
   f32x4 acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x4{};
@@ -276,6 +329,17 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");   // this block is here, the next may not be
     const int blk = wave + i * kWaves, jb = j0 + blk * kBlk;
     const int pg0 = __builtin_amdgcn_readlane(entry, blk * 2), pg1 = __builtin_amdgcn_readlane(entry, blk * 2 + 1);
+    if (any_fresh) {
+      for (int h = 0; h < 2; ++h) {
+        const int pg = h ? pg1 : pg0;
+        for (uint32_t bits = __builtin_amdgcn_readlane(fresh, blk * 2 + h); bits; bits &= bits - 1) {
+          const int r = __builtin_ctz(bits);
+          const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(wpage == pg && wpos % kPage == r));
+          put_row<D>(p, kh, rm.cu[from], h * kPage + r, Kst, Vst);
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     if (n - jb < kBlk) {
       // Position n is in this block: its K and V come from this row.
       const int r = n - jb;

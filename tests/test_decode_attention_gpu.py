@@ -98,3 +98,61 @@ def test_slot_outside_the_pool(P):
     assert int(err.item()) == 1
     assert torch.equal(d_pool.cpu().view(torch.int16), pool.view(torch.int16))
     assert torch.isfinite(logits).all()
+
+
+# Rows of one call that read slots which other rows of it write: (head_dim,
+# group, KV heads, tables, positions); rows with one table are one sequence.
+SHARED = {
+    # three tokens of one sequence, the last two on a new page
+    "three": (128, 8, 2, [0, 0, 0], [303, 304, 305]),
+    # within one page and one block, from position zero on, in any order
+    "start": (64, 2, 2, [0, 0, 0, 0], [2, 0, 3, 1]),
+    # two sequences of two and five tokens, over a split's edge, and one row by itself
+    "two": (128, 4, 8, [0, 1, 0, 1, 1, 2, 1, 1], [1022, 127, 1023, 128, 129, 40, 130, 131]),
+    # 64 tokens: every slot of some blocks comes from the call
+    "many": (64, 8, 8, [0] * 64, list(range(1000, 1064))),
+    "few keys": (128, 1, 4, [0] * 33, list(range(33))),
+}
+
+
+@pytest.mark.parametrize("name", SHARED)
+def test_rows_of_one_sequence(P, name):
+    """Several tokens of a sequence in one call: a row attends to the K/V of
+    the rows before it, whichever workgroup stores them, as when each token
+    has a call of its own (the oracle's decode, token by token)."""
+    d, group, hkv, of, pos = SHARED[name]
+    cfg = configs.TINY.replace(n_layers=2, hidden=256, n_q_heads=group * hkv, n_kv_heads=hkv, head_dim=d, ffn=256,
+                               vocab=512, qk_norm=True, name="shared")
+    glob, layers = gen.model_weights(cfg, seed=63, gain_sigma=0.1)
+    model = gpu_model(P, cfg, glob, layers)
+    ends = [max(n for n, o in zip(pos, of) if o == q) + 1 for q in range(max(of) + 1)]
+    pages = [(e + 15) // 16 for e in ends]
+    tables = gen.disjoint_block_tables(pages, sum(pages) + 3, max(pages), 63, 1)
+    pool = gen.kv_pool_normal(2, sum(pages) + 3, 16, hkv, d, 63)
+    for n, o in zip(pos, of):             # what the call writes holds NaN patterns before
+        pool.view(torch.int16)[:, :, tables[o, n // 16], n % 16] = gen.SENTINEL_BITS
+    d_pool = pool.to(DEV)
+    ids = gen.token_ids(len(pos), cfg.vocab, seed=63).numpy()
+    logits = torch.empty((len(pos), cfg.vocab), dtype=torch.float32, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    model.decode_step(torch.tensor(ids, dtype=torch.int32, device=DEV), pos, torch.tensor(tables[of], device=DEV),
+                      d_pool, logits, model.workspace(len(pos), len(pos)), err)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    got_pool, got = d_pool.cpu(), logits.double().cpu().numpy()
+    g, ls = oracle_weights(glob, layers)
+    shp = shape_of(cfg)
+    caches = []
+    for q, e in enumerate(ends):
+        t = np.arange(e)
+        kv = pool[:, :, torch.as_tensor(tables[q][t // 16], dtype=torch.long), torch.as_tensor(t % 16)].double().numpy()
+        caches.append(kv)
+    for i in sorted(range(len(pos)), key=lambda i: pos[i]):
+        n, kv = pos[i], caches[of[i]]
+        ref, k_new, v_new = om.decode(int(ids[i]), n, list(kv[:, 0]), list(kv[:, 1]), g, ls, shp)
+        e = rel_err(got[i], ref)
+        assert e <= TOL, f"row {i}, position {n}: logits rel err {e:.3g}"
+        for l in range(2):
+            kv[l, 0, n], kv[l, 1, n] = k_new[l][0], v_new[l][0]
+            at = got_pool[l][:, tables[of[i], n // 16], n % 16].double().numpy()
+            assert rel_err(at[0], k_new[l][0]) <= TOL and rel_err(at[1], v_new[l][0]) <= TOL
