@@ -20,9 +20,8 @@
 // of one sequence, a table that another row's reaches).  Those rows' stores
 // come from other workgroups of this launch, in no order, so such keys are
 // taken from the rows' projections instead: the result is that of storing
-// every row's K and V before any attention.  Finding them costs a compare of
-// the split's pages per row, behind the first loads (32 sequences: 2659 ->
-// 2682 us for 12 layers); a store launch of its own would be 4 to 5 us a layer.
+// every row's K and V before any attention.  The call's start launch flags the
+// rows that do.
 //
 // Splits are merged by the last workgroup of a (sequence, KV head) to
 // arrive: partial records and an arrival count through agent-scope accesses,
@@ -228,7 +227,14 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     if (pi * kPage < j1) entry = bt[pi];
     if (entry < 0 || entry >= p.num_pages) entry = -1;
   }
-  int wpos = lane < rm.n_seqs ? rm.base_pos[lane] : 0;   // lane i: the position row i writes
+  // Rare: some rows of the call write slots that this row reads (lane i: the
+  // position row i writes, and its page).
+  const bool shared = rm.n_seqs > 1 && p.shared[s];
+  int wpos = 0, wpage = -1;
+  if (__builtin_expect(shared, 0) && lane < rm.n_seqs) {
+    wpos = rm.base_pos[lane];
+    wpage = p.bt[static_cast<int64_t>(lane) * p.max_pages + wpos / kPage];
+  }
   // The row's Q heads (and K and V heads): a lane owns rotary pairs 4 j .. 4 j + 3.
   const int j = t % LPH, hsub = t / LPH;
   u32x2 lov[NPASS], hiv[NPASS];
@@ -257,11 +263,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   f32x4 cs01 = rope[0], cs23 = rope[1];         // (cos, sin) of pairs 4j .. 4j+3
 #pragma unroll
   for (int ps = 0; ps < NPASS; ++ps) asm volatile("" : "+v"(lov[ps]), "+v"(hiv[ps]));
-  asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry), "+v"(wpos));
-  // The page it writes: not waited for before the stream starts.
-  int wpage = -1;
-  if (rm.n_seqs > 1 && lane < rm.n_seqs) wpage = p.bt[static_cast<int64_t>(lane) * p.max_pages + wpos / kPage];
-  asm volatile("" ::: "memory");
+  asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry));
 
   // Wave w walks blocks w, w + 2, ... of the split.
   const int nblk = (j1 - j0 + kBlk - 1) / kBlk;
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   // l: slot r of the split's page l).  Their K/V may not be in the pool yet:
   // they are taken from that row, as if every row had stored its own first.
   uint32_t fresh = 0;
-  if (rm.n_seqs > 1) {
+  if (__builtin_expect(shared, 0)) {
     for (int i = 0; i < rm.n_seqs; ++i) {
       const int pg = __builtin_amdgcn_readlane(wpage, i), r = __builtin_amdgcn_readlane(wpos, i) % kPage;
       if (entry == pg) fresh |= 1u << r;
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");   // this block is here, the next may not be
     const int blk = wave + i * kWaves, jb = j0 + blk * kBlk;
     const int pg0 = __builtin_amdgcn_readlane(entry, blk * 2), pg1 = __builtin_amdgcn_readlane(entry, blk * 2 + 1);
-    if (any_fresh) {
+    if (__builtin_expect(any_fresh, 0)) {
       for (int h = 0; h < 2; ++h) {
         const int pg = h ? pg1 : pg0;
         for (uint32_t bits = __builtin_amdgcn_readlane(fresh, blk * 2 + h); bits; bits &= bits - 1) {

@@ -197,15 +197,22 @@ __host__ __device__ inline int row_seq(const RowMap& rm, int row) {
 // ------------------------------------------------------------ norms / embed
 // r[t] = float(E[ids[t]]); h[t] = bf16(rmsnorm(r[t]) * g); tab[t][i] = (cos,
 // sin)(pos(t) * theta^(-2i/d)), evaluated in double; the spans are cleared
-// (by the kernel, so a captured graph holds no memset).
+// (by the kernel, so a captured graph holds no memset).  `shared` (decode of
+// several rows; flag null: none): flag[i] = 1 where row i may attend to a slot
+// that another row of the call writes, else 0.
 struct ClearSpan {
   int32_t* p;
   int n;
 };
+struct SharedSlots {
+  const int32_t* bt;
+  int max_pages, num_pages, page;
+  int32_t* flag;
+};
 hipError_t launch_embed_rmsnorm(const int32_t* ids, const uint16_t* embed, const uint16_t* gain,
                                 float* r, uint16_t* h, int rows, int H, float eps, int vocab,
                                 int32_t* err, const RowMap& rm, int d, float theta, float* tab,
-                                ClearSpan a, ClearSpan b, hipStream_t s);
+                                ClearSpan a, ClearSpan b, const SharedSlots& shared, hipStream_t s);
 // h[t] = bf16(rmsnorm(r[t]) * g)
 hipError_t launch_rmsnorm(const float* r, const uint16_t* gain, uint16_t* h, int rows, int H,
                           float eps, hipStream_t s);
@@ -286,6 +293,7 @@ struct DecodeAttnParams {
   uint16_t* o;             // [rows][Hq * d]
   int Hq, Hkv, d;
   float scale_log2;        // log2(e) / sqrt(d)
+  const int32_t* shared;   // [rows] of the call's start (SharedSlots); read when there are several rows
   int32_t* err;
 };
 // Splits of at least kDecodeMinSplit keys, in a section of [n_seqs][Hq]

@@ -24,7 +24,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // decode: number of sequences).
 struct Workspace {
   size_t resid, h, qkv, q, o, act, rope, part, split, split_bytes, attn_split, attn_split_bytes;
-  size_t gemv_part, gemv_part_bytes, gemv_ctr, ssq;
+  size_t gemv_part, gemv_part_bytes, gemv_ctr, ssq, shared;
   int gemv_ctr_count;
   int part_splits;   // decode attention: largest position / 64 + 1 the section is sized for
   size_t total;
@@ -60,6 +60,7 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.o = take(size_t(tokens) * c.n_q_heads * c.head_dim * 2);
   w.act = take(size_t(tokens) * c.ffn * 2);
   w.rope = take(size_t(tokens) * (c.head_dim / 2) * 8);  // (cos, sin) per row and pair
+  w.shared = take(size_t(seqs) * 4);                     // decode: a flag per row
   w.part_splits = kDecodeMaxSplits;
   const size_t part_bytes = size_t(seqs) * c.n_q_heads * kDecodeMaxSplits * (c.head_dim + 2) * 4;
   w.part = take(part_bytes);
@@ -156,6 +157,7 @@ inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_p
   w.o = take(size_t(seqs) * QD * 2);
   w.act = take(size_t(seqs) * c.ffn * 2);
   w.rope = take(size_t(seqs) * (c.head_dim / 2) * 8);
+  w.shared = take(size_t(seqs) * 4);
   w.part_splits = max_pos / 64 + 1;
   w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.part_splits).floats * 4);
   w.ssq = take(norm_bytes(c));

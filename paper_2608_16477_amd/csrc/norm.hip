@@ -35,17 +35,33 @@ __device__ __forceinline__ void store_norm4(uint16_t* h, const uint16_t* g, int 
 
 // The start of a call, one workgroup per row: the row's embedding as its
 // residual, the first RMSNorm, the row's rotary factors (tab[row][i] = (cos,
-// sin)(pos theta^(-2i/d)), in double), and clears of the counters a decode
-// step needs.  One launch instead of three of 3 to 5 us.
+// sin)(pos theta^(-2i/d)), in double), clears of the counters a decode step
+// needs, and its rows' shared-slot flags.  One launch instead of three of 3 to 5 us.
 __global__ __launch_bounds__(kThreads) void embed_rmsnorm_kernel(
     const int32_t* __restrict__ ids, const uint16_t* __restrict__ E, const uint16_t* __restrict__ g,
     float* __restrict__ r, uint16_t* __restrict__ h, int H, float eps, int vocab, int32_t* err, RowMap rm, int half,
-    double log2_theta_over_half, float* __restrict__ tab, ClearSpan ca, ClearSpan cb) {
+    double log2_theta_over_half, float* __restrict__ tab, ClearSpan ca, ClearSpan cb, SharedSlots sl) {
   __shared__ float sh[kThreads / 64];
+  __shared__ int wpage[kMaxSeqs];
   const int t = blockIdx.x;
   for (int i = t * kThreads + threadIdx.x; i < ca.n + cb.n; i += gridDim.x * kThreads) {
     if (i < ca.n) ca.p[i] = 0;
     else cb.p[i - ca.n] = 0;
+  }
+  if (sl.flag) {
+    // Does a page that some row writes hold a position before this row's own?
+    if (threadIdx.x < rm.n_seqs)
+      wpage[threadIdx.x] = sl.bt[static_cast<int64_t>(threadIdx.x) * sl.max_pages + rm.base_pos[threadIdx.x] / sl.page];
+    __syncthreads();
+    const int n = rm.base_pos[t];
+    int any = 0;
+    for (int e = threadIdx.x; e * sl.page < n; e += kThreads) {
+      const int pg = sl.bt[static_cast<int64_t>(t) * sl.max_pages + e];
+      if (pg < 0 || pg >= sl.num_pages) continue;
+      for (int i = 0; i < rm.n_seqs; ++i) any |= wpage[i] == pg && e * sl.page + rm.base_pos[i] % sl.page < n;
+    }
+    any = __syncthreads_or(any);
+    if (threadIdx.x == 0) sl.flag[t] = any;
   }
   if (threadIdx.x < half) {
     const int s = row_seq(rm, t);
@@ -133,12 +149,12 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const float* __restri
 hipError_t launch_embed_rmsnorm(const int32_t* ids, const uint16_t* embed, const uint16_t* gain,
                                 float* r, uint16_t* h, int rows, int H, float eps, int vocab,
                                 int32_t* err, const RowMap& rm, int d, float theta, float* tab,
-                                ClearSpan a, ClearSpan b, hipStream_t s) {
+                                ClearSpan a, ClearSpan b, const SharedSlots& shared, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int half = d / 2;
   if (half > kThreads) return hipErrorInvalidValue;
   embed_rmsnorm_kernel<<<rows, kThreads, 0, s>>>(ids, embed, gain, r, h, H, eps, vocab, err, rm, half,
-                                                 log2(double(theta)) / half, tab, a, b);
+                                                 log2(double(theta)) / half, tab, a, b, shared);
   return hipGetLastError();
 }
 

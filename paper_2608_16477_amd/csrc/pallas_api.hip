@@ -381,7 +381,7 @@ int run_prefill(const pallas_model* m, const pallas::RowMap& rm, int M, const in
   const int QKV = (Hq + 2 * Hkv) * d, QD = Hq * d, KVD = 2 * Hkv * d;
 
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(ids, u16(m->embed), u16(m->layers[0].attn_norm), r, h, M, H,
-                                          c.rms_eps, c.vocab, err, rm, d, c.rope_theta, rope, {}, {}, s), "embed");
+                                          c.rms_eps, c.vocab, err, rm, d, c.rope_theta, rope, {}, {}, {}, s), "embed");
   pallas::QkvParams qp;
   qp.rope = rope;
   qp.q_out = q;
@@ -469,6 +469,7 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   uint16_t* act = reinterpret_cast<uint16_t*>(ws + w.act);
   float* rope = reinterpret_cast<float*>(ws + w.rope);
   float* ssq = reinterpret_cast<float*>(ws + w.ssq);
+  int32_t* shared = reinterpret_cast<int32_t*>(ws + w.shared);
   const int H = c.hidden, d = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, F = c.ffn;
   const int QKV = (Hq + 2 * Hkv) * d, QD = Hq * d;
 
@@ -501,7 +502,8 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   };
   PALLAS_TRY(PALLAS_K_EMBED, pallas::launch_embed_rmsnorm(tokens, u16(m->embed), u16(m->layers[0].attn_norm), r, h, B, H,
                                           c.rms_eps, c.vocab, err, rm, d, c.rope_theta, rope,
-                                          {sc.ctr, gemv_counters}, {reinterpret_cast<int32_t*>(part), as.counters}, s),
+                                          {sc.ctr, gemv_counters}, {reinterpret_cast<int32_t*>(part), as.counters},
+                                          {bt, max_pages, pool->num_pages, pool->page_size, B > 1 ? shared : nullptr}, s),
              "embed");
   pallas::DecodeAttnParams ap;
   ap.qkv = qkv;
@@ -518,6 +520,7 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   ap.Hkv = Hkv;
   ap.d = d;
   ap.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(double(d)));
+  ap.shared = shared;
   ap.err = err;
   for (int l = 0; l < c.n_layers; ++l) {
     const pallas_layer_weights& L = m->layers[l];
