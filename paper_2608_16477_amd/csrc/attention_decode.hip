@@ -2,12 +2,20 @@
 // QK-norm and rotary of the row's Q and K, the paged store of its K and V,
 // grouped-query attention over positions [0, n], in one kernel.
 //
-// A workgroup of two or four waves owns a run of keys ("split") of one (sequence, KV
-// head) and all G query heads that share it.  Each wave walks its share of the
-// split's 32-key blocks on its own: K and V rows go from memory
-// straight into a private two-stage LDS ring (buffer_load ... lds, whole
-// 256-byte head rows), so up to 32 KiB per wave and 128 KiB per CU are in
-// flight and the waves meet no barrier until the end.
+// A sequence's keys are cut into splits of a length that its own position
+// gives (decode_split_keys), and each split into four leaves.  A leaf is one
+// online softmax over its 32-key blocks in order; leaves are merged as a
+// binary tree.  A workgroup of two or four waves owns a run of splits of one
+// (sequence, KV head) and all G query heads that share it, and its waves equal
+// shares of the run's leaves.  Runs are aligned parts of the tree, so how many
+// splits a run has, and how many waves, changes no bit: a sequence's result
+// does not depend on the others in the call, though the division of the work
+// does (plan_decode_runs).
+//
+// Each wave walks its blocks on its own: K and V rows go from memory straight
+// into a private two-stage LDS ring (buffer_load ... lds, whole 256-byte head
+// rows), so up to 32 KiB per wave and 128 KiB per CU are in flight and the
+// waves meet no barrier until the end.
 //
 // Scores are S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (the G heads are the
 // columns, repeated up to 16): lane l holds keys 4 (l / 16) + r of head l mod 16.
@@ -23,16 +31,19 @@
 // every row's K and V before any attention.  The call's start launch flags the
 // rows that do.
 //
-// Splits are merged by the last workgroup of a (sequence, KV head) to
+// Runs are merged by the last workgroup of a (sequence, KV head) to
 // arrive: partial records and an arrival count through agent-scope accesses,
 // as the skinny projections do.
 //
 // Per layer against the three kernels this replaces (norm / rotary / store,
 // 64-key splits on the vector units, merge): 32 sequences of 136,000 keys in
-// all, 8 KV heads of 128 (558 MB): 213 -> 108 us (5.2 TB/s; bound by the K/V
-// stream); 8 sequences, 32,000 keys: 69 -> 33 us; one sequence of 4000 keys,
-// 64 query heads: 27 -> 13.6 us (bound by the chain of launch, table, stream,
-// record store, count and merge).
+// all, 8 KV heads of 128 (558 MB): 213 -> 109 us (5.1 TB/s; bound by the K/V
+// stream); 8 sequences, 32,000 keys: 69 -> 32 us; one sequence of 4000 keys,
+// 64 query heads: 27 -> 12 us (bound by the chain of launch, table, stream,
+// record store, count and merge).  Runs of equal length over all sequences,
+// whose merges depend on the batch, take 106, 31.7 and 12.1 us; 16 and 64
+// sequences of 500 to 8000 keys, 64 query heads, 29.2 against 31.8 and 136
+// against 145 us.
 #include <algorithm>
 #include <type_traits>
 
@@ -44,13 +55,12 @@ namespace pallas {
 namespace {
 
 constexpr int kPage = 16;        // tokens per cache page (the only page size the library accepts)
-// The declared bound is four times the launched size: it limits a wave to 256
+// The declared bound is above the launched 128 or 256: it limits a wave to 256
 // registers, and the compiler then keeps the accumulators in vector registers
 // (with 512 it moves them to accumulation registers and back in every block).
 constexpr int kBoundThreads = 512;
 constexpr int kBlk = 32;         // keys per block: two pages
 constexpr int kStages = 2;       // blocks in flight per wave
-constexpr int kMergeBatch = kDecodeSplitsPerSeq;   // split records read at once by the last arriver
 constexpr int kAuxAgent = 16;    // buffer cache policy: sc1 (device-coherent)
 constexpr int kAuxStream = 2;    // nt: K and V are read once per step
 
@@ -119,18 +129,46 @@ __device__ __forceinline__ uint32_t take_bf2(float& a, float& b) {
   return w;
 }
 
-// Splits of the call: sequence s has splits [first[s], first[s + 1]) of
-// split_keys keys each.
-struct DecodeSplits {
-  int32_t split_keys;
-  int32_t max_splits;               // records per (sequence, head): the largest split count
-  int32_t first[kMaxSeqs + 1];
+// A partial softmax: exponentials relative to the maximum m that sum to l, and
+// (beside it) a weighted sum of V.  Merging with an empty one (m -inf, zeros)
+// changes no bit, and the fused multiply-adds are written out, so every caller
+// rounds alike.
+struct Partial {
+  float m, l;
 };
+struct Weights {
+  float a, b;
+};
+__device__ __forceinline__ Partial merge(Partial a, Partial b, Weights& w) {
+  const float m = fmaxf(a.m, b.m);
+  w.a = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a.m - m);
+  w.b = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(b.m - m);
+  return {m, __builtin_fmaf(w.b, b.l, w.a * a.l)};
+}
+__device__ __forceinline__ f32x4 merge(f32x4 a, f32x4 b, Weights w) {
+  f32x4 v;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) v[x] = __builtin_fmaf(w.b, b[x], w.a * a[x]);
+  return v;
+}
 
-// Loads of the split's 32-key block `blk` (of nblk) into a stage: cached
-// rows only (positions below n, `cached` of them from the split's start); the
-// others, and rows on a page outside the pool, read zeros, as do blocks past
-// the split's.  Every wave issues the loads of every step, so the compiler
+// The N (a power of two) partials as a binary tree, into the first.
+template <int N>
+__device__ __forceinline__ void merge_tree(Partial* ml, f32x4* v) {
+#pragma unroll
+  for (int d = 1; d < N; d *= 2)
+#pragma unroll
+    for (int k = 0; k < N; k += 2 * d) {
+      Weights w;
+      ml[k] = merge(ml[k], ml[k + d], w);
+      v[k] = merge(v[k], v[k + d], w);
+    }
+}
+
+// Loads of the run's 32-key block `blk` (below nblk) into a stage: cached
+// rows only (positions below n, `cached` of them from the run's start); the
+// others, and rows on a page outside the pool, read zeros, as do blocks from
+// nblk on.  Every wave issues the loads of every step, so the compiler
 // can count the loads in flight.  koff / voff: byte offset
 // in a page of what this lane loads in instruction v of it.
 template <int D>
@@ -181,10 +219,11 @@ __device__ __forceinline__ void put_row(const DecodeAttnParams& p, int kh, int r
 }
 
 template <int D, int kWaves>
-__global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnParams p, RowMap rm, DecodeSplits sp,
+__global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnParams p, RowMap rm, DecodeRuns runs,
                                                                float* __restrict__ part_o,
                                                                float* __restrict__ part_ml, int* __restrict__ ctr) {
   constexpr int kThreads = kWaves * 64;
+  constexpr int kLevels = kWaves == 2 ? 3 : 2;  // a wave merges up to 2^kLevels leaves
   constexpr int CH = D / 8;                     // 16-byte chunks per row
   constexpr int RPI = 64 / CH;                  // rows per load instruction
   constexpr int IPP = kPage / RPI;              // load instructions per page
@@ -200,7 +239,7 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   constexpr int kRingSlots = kWaves * kStages * 2 * kStageSlots;
   __shared__ __attribute__((aligned(256))) u32x4 lds[kRingSlots + kHeadsMax * CH + kWaves * 4 + 1];
   uint16_t(*heads)[D] = reinterpret_cast<uint16_t(*)[D]>(lds + kRingSlots);   // Q heads, then K and V of this row
-  float(*wave_ml)[8][2] = reinterpret_cast<float(*)[8][2]>(lds + kRingSlots + kHeadsMax * CH);
+  Partial(*wave_ml)[8] = reinterpret_cast<Partial(*)[8]>(lds + kRingSlots + kHeadsMax * CH);   // [wave][head]
   int* arrived = reinterpret_cast<int*>(lds + kRingSlots + kHeadsMax * CH + kWaves * 4);
 
   const int t = threadIdx.x, lane = t & 63;
@@ -211,29 +250,23 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   int s = 0, hi = rm.n_seqs - 1;                // largest s with first[s] <= u
   while (s < hi) {
     const int mid = (s + hi + 1) >> 1;
-    if (sp.first[mid] <= u) s = mid; else hi = mid - 1;
+    if (runs.first[mid] <= u) s = mid; else hi = mid - 1;
   }
-  const int split = u - sp.first[s], nsplit = sp.first[s + 1] - sp.first[s];
+  const int run = u - runs.first[s], nrun = runs.first[s + 1] - runs.first[s];
   const int n = rm.base_pos[s], row = rm.cu[s];
-  const int j0 = split * sp.split_keys;
-  const int j1 = min(j0 + sp.split_keys, n + 1);
-  const bool last = split == nsplit - 1;        // holds position n
+  const int split_keys = decode_split_keys(n), run_keys = runs.per_run[s] * split_keys;
+  const int j0 = run * run_keys;
+  const int j1 = min(j0 + run_keys, n + 1);
+  const bool last = run == nrun - 1;            // holds position n
   const int32_t* bt = p.bt + static_cast<int64_t>(s) * p.max_pages;
+  int shared = rm.n_seqs > 1 ? p.shared[s] : 0;
 
-  // This split's table entries, one per lane (split_keys <= 64 pages).
+  // This run's table entries, one per lane (a run is at most 64 pages).
   int entry = -1;
   {
     const int pi = j0 / kPage + lane;
     if (pi * kPage < j1) entry = bt[pi];
     if (entry < 0 || entry >= p.num_pages) entry = -1;
-  }
-  // Rare: some rows of the call write slots that this row reads (lane i: the
-  // position row i writes, and its page).
-  const bool shared = rm.n_seqs > 1 && p.shared[s];
-  int wpos = 0, wpage = -1;
-  if (__builtin_expect(shared, 0) && lane < rm.n_seqs) {
-    wpos = rm.base_pos[lane];
-    wpage = p.bt[static_cast<int64_t>(lane) * p.max_pages + wpos / kPage];
   }
   // The row's Q heads (and K and V heads): a lane owns rotary pairs 4 j .. 4 j + 3.
   const int j = t % LPH, hsub = t / LPH;
@@ -265,9 +298,10 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   for (int ps = 0; ps < NPASS; ++ps) asm volatile("" : "+v"(lov[ps]), "+v"(hiv[ps]));
   asm volatile("" : "+v"(cs01), "+v"(cs23), "+v"(gq[0]), "+v"(gq[1]), "+v"(gk[0]), "+v"(gk[1]), "+v"(entry));
 
-  // Wave w walks blocks w, w + 2, ... of the split.
-  const int nblk = (j1 - j0 + kBlk - 1) / kBlk;
-  const int nb = wave < nblk ? (nblk - wave + kWaves - 1) / kWaves : 0;
+  // The run's leaves (a quarter of a split each) in order, as many per wave.
+  const int leaf_blocks = split_keys / (4 * kBlk), leaves = runs.per_run[s] * (4 / kWaves);
+  const int blk0 = wave * leaves * leaf_blocks;  // this wave's blocks: [blk0, blk1)
+  const int blk1 = min(blk0 + leaves * leaf_blocks, (j1 - j0 + kBlk - 1) / kBlk);
   u32x4* const myring = lds + wave * kStages * 2 * kStageSlots;   // [stage][K, V]
   const uint32_t rs = static_cast<uint32_t>(p.Hkv) * D * 2;   // bytes between tokens of a page
   // Byte offset in a page of what this lane loads in instruction v of it.
@@ -279,10 +313,10 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     voff[v] = r * rs + static_cast<uint32_t>(((lane % CH) ^ swz_v<CH>(r)) * 16);
   }
   constexpr int kLoads = 4 * IPP;               // load instructions per block
-  issue_block<D>(p, kh, entry, n - j0, wave, nblk, rs, koff, voff, myring);
-  issue_block<D>(p, kh, entry, n - j0, wave + kWaves, nblk, rs, koff, voff, myring + 2 * kStageSlots);
+  issue_block<D>(p, kh, entry, n - j0, blk0, blk1, rs, koff, voff, myring);
+  issue_block<D>(p, kh, entry, n - j0, blk0 + 1, blk1, rs, koff, voff, myring + 2 * kStageSlots);
 
-  // QK-norm and rotary of Q (and, in the last split, of K).
+  // QK-norm and rotary of Q (and, in the last run, of K).
 #pragma unroll
   for (int ps = 0; ps < NPASS; ++ps) {
     const int hs = ps * HPP + hsub;
@@ -306,11 +340,17 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   const int vkey = 4 * q4 + (l16 >> 2);
   const uint32_t vb0 = static_cast<uint32_t>(vkey * D * 2 + ((swz_v<CH>(vkey) | ((l16 & 3) >> 1)) * 16) + (l16 & 1) * 8);
 
-  // Cached slots of this split that a row of this call writes (bit r of lane
-  // l: slot r of the split's page l).  Their K/V may not be in the pool yet:
-  // they are taken from that row, as if every row had stored its own first.
+  // Rare: cached slots of this run that a row of this call writes (bit r of lane
+  // l: slot r of the run's page l).  Their K/V may not be in the pool yet: they
+  // are taken from that row, as if every row had stored its own first.  (Lane
+  // i: the position that row i writes, and its page.)
   uint32_t fresh = 0;
-  if (__builtin_expect(shared, 0)) {
+  int wpos = 0, wpage = -1;
+  if (shared) {
+    if (lane < rm.n_seqs) {
+      wpos = rm.base_pos[lane];
+      wpage = p.bt[static_cast<int64_t>(lane) * p.max_pages + wpos / kPage];
+    }
     for (int i = 0; i < rm.n_seqs; ++i) {
       const int pg = __builtin_amdgcn_readlane(wpage, i), r = __builtin_amdgcn_readlane(wpos, i) % kPage;
       if (entry == pg) fresh |= 1u << r;
@@ -320,18 +360,24 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   }
   const bool any_fresh = __builtin_amdgcn_ballot_w64(fresh != 0) != 0;
 
-  f32x4 acc[DT];
+  // Leaves are merged as a binary counter counts: held[v] is the merge of 2^v
+  // leaves that waits for the next 2^v.  (Set before they are read.)
+  f32x4 acc[DT], held[kLevels][DT];
+  Partial ml, held_ml[kLevels];
+  int blk = blk0;
+#pragma unroll 1
+  for (int leaf = 0; leaf < leaves; ++leaf) {
+  const int end = min(blk0 + (leaf + 1) * leaf_blocks, blk1);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x4{};
   float m = -INFINITY, lsum = 0.f;
-
-  for (int i = 0; i < nb; ++i) {
-    u32x4* const Kst = myring + (i % kStages) * 2 * kStageSlots;
+  for (; blk < end; ++blk) {
+    u32x4* const Kst = myring + (static_cast<unsigned>(blk - blk0) % kStages) * 2 * kStageSlots;
     u32x4* const Vst = Kst + kStageSlots;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");   // this block is here, the next may not be
-    const int blk = wave + i * kWaves, jb = j0 + blk * kBlk;
+    const int jb = j0 + blk * kBlk;
     const int pg0 = __builtin_amdgcn_readlane(entry, blk * 2), pg1 = __builtin_amdgcn_readlane(entry, blk * 2 + 1);
-    if (__builtin_expect(any_fresh, 0)) {
+    if (any_fresh) {
       for (int h = 0; h < 2; ++h) {
         const int pg = h ? pg1 : pg0;
         for (uint32_t bits = __builtin_amdgcn_readlane(fresh, blk * 2 + h); bits; bits &= bits - 1) {
@@ -410,9 +456,26 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
       for (int part = 2; part >= 0; --part)
         acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va[dt]), pb[part], acc[dt], 0, 0, 0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this block's LDS reads are done
-    issue_block<D>(p, kh, entry, n - j0, blk + kStages * kWaves, nblk, rs, koff, voff, Kst);
+    issue_block<D>(p, kh, entry, n - j0, blk + kStages, blk1, rs, koff, voff, Kst);
   }
-  lsum = rows_sum(lsum);
+  ml = {m, rows_sum(lsum)};
+  bool carry = true;
+#pragma unroll
+  for (int v = 0; v < kLevels; ++v) {
+    carry = carry && (2 << v) <= leaves;
+    if (carry && (leaf >> v & 1)) {
+      Weights w;
+      ml = merge(held_ml[v], ml, w);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] = merge(held[v][dt], acc[dt], w);
+    } else if (carry) {
+      held_ml[v] = ml;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) held[v][dt] = acc[dt];
+      carry = false;
+    }
+  }
+  }
 
   if (last && t < 2 * CH) {
     // K and V of position n (stored here: a store pending in the loop would
@@ -427,18 +490,15 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     }
   }
 
-  // Merge the waves through LDS (the first stage is free once both are here
-  // and nothing is in flight): om[wave][head][dim].
+  // Merge the waves through LDS (the ring is free once all are here and
+  // nothing is in flight): om[wave][head][dim].
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   float* om = reinterpret_cast<float*>(lds);
   if (l16 < G) {
     float* dst = om + (wave * 8 + l16) * D + 4 * q4;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + dt * 16) = acc[dt];
-    if (q4 == 0) {
-      wave_ml[wave][l16][0] = m;
-      wave_ml[wave][l16][1] = lsum;
-    }
+    if (q4 == 0) wave_ml[wave][l16] = ml;
   }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   const int quads = G * D / 4;                  // 4-wide output groups of this KV head
@@ -451,33 +511,31 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
     w.y = pack_bf2(v[2], v[3]);
     *reinterpret_cast<u32x2*>(orow + e * 4) = w;
   };
-  const int64_t rec0 = (static_cast<int64_t>(s) * p.Hkv + kh) * sp.max_splits;   // this (sequence, KV head)'s records
+  const int64_t rec0 = (static_cast<int64_t>(s) * p.Hkv + kh) * runs.most;   // this (sequence, KV head)'s records
   const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(part_o + rec0 * G * D), 0, static_cast<uint32_t>(sp.max_splits * G * D * 4), 0x00020000);
-  float* ml = part_ml + rec0 * G * 2;           // [split][head][max, sum]
+      (void*)(part_o + rec0 * G * D), 0, static_cast<uint32_t>(runs.most * G * D * 4), 0x00020000);
+  Partial* rec_ml = reinterpret_cast<Partial*>(part_ml) + rec0 * G;   // [run][head]
   for (int e = t; e < quads; e += kThreads) {
     const int g = e / (D / 4), dv = (e % (D / 4)) * 4;
-    float mm = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, wave_ml[w][g][0]);
-    f32x4 v = {};
+    Partial pm[kWaves];
+    f32x4 pv[kWaves];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float ww = mm == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wave_ml[w][g][0] - mm);
-      l += ww * wave_ml[w][g][1];
-      v += ww * *reinterpret_cast<const f32x4*>(om + (w * 8 + g) * D + dv);
+      pm[w] = wave_ml[w][g];
+      pv[w] = *reinterpret_cast<const f32x4*>(om + (w * 8 + g) * D + dv);
     }
-    if (nsplit == 1) {
-      store_out(e, v, l);
+    merge_tree<kWaves>(pm, pv);
+    if (nrun == 1) {
+      store_out(e, pv[0], pm[0].l);
     } else {
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, (split * G * D + e * 4) * 4, 0, kAuxAgent);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, pv[0]), ro, (run * G * D + e * 4) * 4, 0, kAuxAgent);
       if (dv == 0) {
-        __hip_atomic_store(ml + (split * G + g) * 2, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(ml + (split * G + g) * 2 + 1, l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rec_ml[run * G + g].m, pm[0].m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rec_ml[run * G + g].l, pm[0].l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
-  if (nsplit == 1) return;
+  if (nrun == 1) return;
   // Every wave's records have reached the device-coherent level (agent-scope
   // stores write through; vmcnt 0), then the count goes up; the last of the
   // (sequence, KV head) reads the others' past its own L2.
@@ -485,116 +543,135 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   int* cnt = ctr + s * p.Hkv + kh;
   if (t == 0) *arrived = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  if (*arrived != nsplit - 1) return;
+  if (*arrived != nrun - 1) return;
   if (t == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // All records of a batch of splits are in flight at once, for both of this
-  // thread's output groups.
-  constexpr int E = (8 * D / 4 + kThreads - 1) / kThreads, U = E == 1 ? kMergeBatch : kMergeBatch / 2;
+  // All records of a batch of runs are in flight at once, for both of this
+  // thread's output groups.  A batch is an aligned part of the tree.
+  constexpr int E = (8 * D / 4 + kThreads - 1) / kThreads, U = E == 1 ? kDecodeSplitsPerSeq : kDecodeSplitsPerSeq / 2;
   const __amdgpu_buffer_rsrc_t rml = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)ml, 0, static_cast<uint32_t>(nsplit * G * 8), 0x00020000);
-  float mm[E], l[E];
+      (void*)rec_ml, 0, static_cast<uint32_t>(nrun * G * 8), 0x00020000);
+  Partial total[E];
   f32x4 v[E];
 #pragma unroll
   for (int x = 0; x < E; ++x) {
-    mm[x] = -INFINITY;
-    l[x] = 0.f;
+    total[x] = {-INFINITY, 0.f};
     v[x] = f32x4{};
   }
-  for (int k0 = 0; k0 < nsplit; k0 += U) {
+  for (int k0 = 0; k0 < nrun; k0 += U) {
     f32x4 o[E][U];
-    u32x2 a[E][U];
+    Partial a[E][U];
 #pragma unroll
     for (int k = 0; k < U; ++k)
 #pragma unroll
       for (int x = 0; x < E; ++x) {
         const int e = x * kThreads + t, g = e / (D / 4);
-        const bool in = k0 + k < nsplit && e < quads;      // else: reads zeros
-        a[x][k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+        const bool in = k0 + k < nrun && e < quads;        // else: reads zeros
+        const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
             rml, in ? ((k0 + k) * G + g) * 8 : 0xFFFFFFF0u, 0, kAuxAgent));
+        a[x][k] = {__uint_as_float(r.x), __uint_as_float(r.y)};
         o[x][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
             ro, in ? ((k0 + k) * G * D + e * 4) * 4 : 0xFFFFFFF0u, 0, kAuxAgent));
       }
 #pragma unroll
     for (int x = 0; x < E; ++x) {
-      float m_new = mm[x];
 #pragma unroll
       for (int k = 0; k < U; ++k)
-        if (k0 + k < nsplit) m_new = fmaxf(m_new, __uint_as_float(a[x][k].x));
-      if (m_new == -INFINITY) continue;
-      const float w0 = __builtin_amdgcn_exp2f(mm[x] - m_new);
-      mm[x] = m_new;
-      l[x] *= w0;
-      v[x] *= w0;
-#pragma unroll
-      for (int k = 0; k < U; ++k)
-        if (k0 + k < nsplit) {
-          const float w = __builtin_amdgcn_exp2f(__uint_as_float(a[x][k].x) - m_new);
-          l[x] += w * __uint_as_float(a[x][k].y);
-          v[x] += w * o[x][k];
-        }
+        if (k0 + k >= nrun) a[x][k].m = -INFINITY;
+      merge_tree<U>(a[x], o[x]);
+      Weights w;
+      total[x] = merge(total[x], a[x][0], w);   // (the first batch: with an empty one)
+      v[x] = merge(v[x], o[x][0], w);
     }
   }
 #pragma unroll
   for (int x = 0; x < E; ++x)
-    if (x * kThreads + t < quads) store_out(x * kThreads + t, v[x], l[x]);
+    if (x * kThreads + t < quads) store_out(x * kThreads + t, v[x], total[x].l);
 }
 
 }  // namespace
 
-// Keys per split and waves per workgroup.
-//   The last arriver reads its records in batches of kMergeBatch, a memory
-// round trip each, so a sequence gets at most that many splits; below that,
-// 128 keys (at one sequence of the large model's layer: 1000 keys in 8 splits
-// take 10.7 us, in 2 14.5; 4000 keys in 16 14.1, in 32 17.5; 8000 in 16 16.6,
-// in 63 33).
-//   A call of at most one workgroup per CU runs four waves in each (200 keys
-// 8.7 against 9.4 us with two).  Larger calls run two, two workgroups to a CU
-// (their starts and merges overlap the other's stream), with the fewest keys
-// that fill a whole number of rounds: eight sequences of 32,000 keys in all
-// take 32.4 us in 472 workgroups and 36.5 in 536 (512 run at once).
+// How the work is divided (us per layer; 8 KV heads of 128, 4 or 8 query heads
+// per KV head).
+//   Up to one workgroup per CU, in runs of at most 512 keys: four waves in each
+// (one sequence of 2048 keys 10.9 against 12.4 with two; 4 sequences, 13,900
+// keys, 18.0 in 224 workgroups, 25 in the 376 that one split each would make).
+//   Else two waves, two workgroups to a CU (their starts and merges overlap the
+// other's stream), and the fewest whole rounds of them that runs of up to 1024
+// keys and four splits allow, filled by doubling the shortest runs only as
+// often as needed: 8 sequences 31.9 in 512 workgroups, 35.4 in 800, 39.6 in
+// 376; 16 sequences 31.4 in 504, 35 in 416 and in 976.
 constexpr int kCus = 256;
 
-hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, float* part, int part_splits,
-                                   hipStream_t s) {
-  if (p.Hq % p.Hkv != 0 || p.page != kPage || rm.n_seqs < 1 || rm.n_seqs > kMaxSeqs) return hipErrorInvalidValue;
+bool plan_decode_runs(const RowMap& rm, int Hkv, DecodeRuns& runs) {
+  if (rm.n_seqs < 1 || rm.n_seqs > kMaxSeqs) return false;
+  for (int i = 0; i < rm.n_seqs; ++i)
+    if (rm.base_pos[i] < 0 || decode_split_keys(rm.base_pos[i]) > kDecodeMaxRun) return false;
+  auto count = [&](int i) {
+    const int splits = rm.base_pos[i] / decode_split_keys(rm.base_pos[i]) + 1;
+    return (splits + runs.per_run[i] - 1) / runs.per_run[i];
+  };
+  int64_t wgs;
+  auto start = [&] {
+    wgs = 0;
+    for (int i = 0; i < rm.n_seqs; ++i) {
+      runs.per_run[i] = 1;
+      wgs += int64_t(count(i)) * Hkv;
+    }
+  };
+  // Doubles the shortest runs that may have up to `keys` keys until at most
+  // `most` workgroups are left.
+  auto grow = [&](int64_t most, int keys) {
+    while (wgs > most) {
+      int at = -1, least = 0;
+      for (int i = 0; i < rm.n_seqs; ++i) {
+        const int r = decode_split_keys(rm.base_pos[i]) * runs.per_run[i];
+        if (2 * r <= keys && 2 * runs.per_run[i] <= kDecodeMaxRunSplits && count(i) > 1 && (at < 0 || r < least)) {
+          at = i;
+          least = r;
+        }
+      }
+      if (at < 0) break;
+      wgs -= int64_t(count(at)) * Hkv;
+      runs.per_run[at] *= 2;
+      wgs += int64_t(count(at)) * Hkv;
+    }
+  };
+  start();
+  grow(kCus, kDecodeMaxRun / 2);
+  runs.wide = wgs <= kCus;
+  if (!runs.wide) {
+    start();
+    grow(0, kDecodeMaxRun);
+    const int64_t full = (wgs + 2 * kCus - 1) / (2 * kCus) * (2 * kCus);
+    start();
+    grow(full, kDecodeMaxRun);
+  }
+  runs.first[0] = 0;
+  runs.most = 1;
+  for (int i = 0; i < rm.n_seqs; ++i) {
+    runs.first[i + 1] = runs.first[i] + count(i);
+    runs.most = std::max(runs.most, count(i));
+  }
+  return true;
+}
+
+hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, const DecodeRuns& runs, float* part,
+                                   int part_splits, hipStream_t s) {
+  if (p.Hq % p.Hkv != 0 || p.page != kPage) return hipErrorInvalidValue;
   const int G = p.Hq / p.Hkv;
   if (G > 8 || (G & (G - 1)) != 0) return hipErrorInvalidValue;
-  for (int i = 0; i < rm.n_seqs; ++i)
-    if (rm.base_pos[i] < 0) return hipErrorInvalidValue;
-  auto splits = [&](int keys) {
-    int64_t c = 0;
-    for (int i = 0; i < rm.n_seqs; ++i) c += rm.base_pos[i] / keys + 1;
-    return c;
-  };
-  DecodeSplits sp;
-  int nmax = 0;
-  for (int i = 0; i < rm.n_seqs; ++i) nmax = std::max(nmax, rm.base_pos[i]);
-  sp.split_keys = (nmax / kMergeBatch + kDecodeMinSplit) / kDecodeMinSplit * kDecodeMinSplit;
-  if (sp.split_keys > kDecodeMaxSplit) return hipErrorInvalidValue;
-  const bool wide = splits(sp.split_keys) * p.Hkv <= kCus;
-  if (!wide) {
-    const int64_t round = 2 * kCus, want = (splits(kDecodeMaxSplit) * p.Hkv + round - 1) / round * round;
-    while (sp.split_keys < kDecodeMaxSplit && splits(sp.split_keys) * p.Hkv > want) sp.split_keys += 2 * kBlk;
-  }
-  sp.first[0] = 0;
-  sp.max_splits = 1;
-  for (int i = 0; i < rm.n_seqs; ++i) {
-    const int c = rm.base_pos[i] / sp.split_keys + 1;
-    sp.first[i + 1] = sp.first[i] + c;
-    sp.max_splits = std::max(sp.max_splits, c);
-  }
-  // Records of sp.max_splits splits in a section sized for part_splits ones
-  // of 64 keys: counters, then outputs, then maxima and sums.
+  // Records of runs.most runs in a section sized for part_splits splits of 64
+  // keys: counters, then outputs, then maxima and sums.
   const DecodeAttnScratch sc = decode_attn_scratch(rm.n_seqs, p.Hq, p.Hkv, p.d, part_splits);
-  if (sp.max_splits > 1 && sp.max_splits > sc.max_splits) return hipErrorInvalidValue;
+  if (runs.most > 1 && runs.most > sc.max_splits) return hipErrorInvalidValue;
   int* ctr = reinterpret_cast<int*>(part);
   float* po = part + sc.out_floats;
   float* pml = part + sc.ml_floats;
-  const int grid = sp.first[rm.n_seqs] * p.Hkv;
-  if (p.d == 128 && wide) attn_decode_kernel<128, 4><<<grid, 256, 0, s>>>(p, rm, sp, po, pml, ctr);
-  else if (p.d == 128) attn_decode_kernel<128, 2><<<grid, 128, 0, s>>>(p, rm, sp, po, pml, ctr);
-  else if (p.d == 64 && wide) attn_decode_kernel<64, 4><<<grid, 256, 0, s>>>(p, rm, sp, po, pml, ctr);
-  else if (p.d == 64) attn_decode_kernel<64, 2><<<grid, 128, 0, s>>>(p, rm, sp, po, pml, ctr);
+  const int grid = runs.first[rm.n_seqs] * p.Hkv;
+  if (p.d == 128 && runs.wide) attn_decode_kernel<128, 4><<<grid, 256, 0, s>>>(p, rm, runs, po, pml, ctr);
+  else if (p.d == 128) attn_decode_kernel<128, 2><<<grid, 128, 0, s>>>(p, rm, runs, po, pml, ctr);
+  else if (p.d == 64 && runs.wide) attn_decode_kernel<64, 4><<<grid, 256, 0, s>>>(p, rm, runs, po, pml, ctr);
+  else if (p.d == 64) attn_decode_kernel<64, 2><<<grid, 128, 0, s>>>(p, rm, runs, po, pml, ctr);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

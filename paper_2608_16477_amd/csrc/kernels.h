@@ -296,14 +296,22 @@ struct DecodeAttnParams {
   const int32_t* shared;   // [rows] of the call's start (SharedSlots); read when there are several rows
   int32_t* err;
 };
-// Splits of at least kDecodeMinSplit keys, in a section of [n_seqs][Hq]
-// [part_splits][d + 2] floats, part_splits = largest position / 64 + 1:
-// arrival counters (zero on entry, left zero), outputs [n_seqs][Hkv][split]
-// [G][d], then maxima and sums.  With fewer than two splits nothing is used;
-// otherwise half the records leave room for the counters.
+// Keys per split of a sequence at position n, from n alone: 128, and as many
+// more as keep a sequence at 16 splits.  One sequence (large layer, us): 1000
+// keys 9.9 in 128-key splits, 11.4 in 256, 13.8 in 512; 4000 keys 12.0 in 16
+// splits, 14.3 in 8; 8000 keys 15.2 in 16, 20 in 8; more than 16 cost more in
+// the merge than they save (4000 keys in 32: 17.5, before in 16 14.1).
 constexpr int kDecodeMinSplit = 128;
-constexpr int kDecodeMaxSplit = 1024;   // a split's table entries: one per lane
-constexpr int kDecodeSplitsPerSeq = 16;  // per sequence: one batch of the merge
+constexpr int kDecodeSplitsPerSeq = 16;
+constexpr int kDecodeMaxRun = 1024;     // keys of a workgroup: its table entries, one per lane
+constexpr int kDecodeMaxRunSplits = 4;  // its merges in progress are held in registers
+__host__ __device__ inline int decode_split_keys(int n) {
+  return (n / kDecodeSplitsPerSeq + kDecodeMinSplit) / kDecodeMinSplit * kDecodeMinSplit;
+}
+// A section of [n_seqs][Hq][part_splits][d + 2] floats, part_splits = largest
+// position / 64 + 1: arrival counters (zero on entry, left zero), outputs
+// [n_seqs][Hkv][run][G][d], then maxima and sums.  With fewer than two splits
+// nothing is used; otherwise half the records leave room for the counters.
 struct DecodeAttnScratch {
   int max_splits;          // splits per sequence that fit
   int counters;            // ints to clear at the start of the section
@@ -318,7 +326,17 @@ inline DecodeAttnScratch decode_attn_scratch(int n_seqs, int Hq, int Hkv, int d,
   s.floats = s.max_splits > 1 ? s.ml_floats + size_t(n_seqs) * Hq * s.max_splits * 2 : 0;
   return s;
 }
-hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, float* part,
+// Work of a call: sequence s has runs [first[s], first[s + 1]) of per_run[s]
+// splits each (a power of two), one workgroup per run and KV head.
+struct DecodeRuns {
+  int32_t wide;                     // four waves per workgroup, else two
+  int32_t most;                     // the largest run count of a sequence
+  int32_t first[kMaxSeqs + 1];
+  int32_t per_run[kMaxSeqs];
+};
+// False where a position is outside what the kernel takes.
+bool plan_decode_runs(const RowMap& rm, int Hkv, DecodeRuns& runs);
+hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, const DecodeRuns& runs, float* part,
                                    int part_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM

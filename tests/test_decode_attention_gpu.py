@@ -156,3 +156,55 @@ def test_rows_of_one_sequence(P, name):
             kv[l, 0, n], kv[l, 1, n] = k_new[l][0], v_new[l][0]
             at = got_pool[l][:, tables[of[i], n // 16], n % 16].double().numpy()
             assert rel_err(at[0], k_new[l][0]) <= TOL and rel_err(at[1], v_new[l][0]) <= TOL
+    if len(pos) <= 8:                     # the same bits as a call per token
+        d_pool = pool.to(DEV)
+        for i in sorted(range(len(pos)), key=lambda i: pos[i]):
+            model.decode_step(torch.tensor(ids[i:i + 1], dtype=torch.int32, device=DEV), [pos[i]],
+                              torch.tensor(tables[of[i]][None], device=DEV), d_pool, logits[:1], model.workspace(1, 1), err)
+            torch.cuda.synchronize()
+            assert np.array_equal(logits[0].double().cpu().numpy(), got[i]), f"row {i}, position {pos[i]}"
+        assert torch.equal(d_pool.cpu().view(torch.int16), got_pool.view(torch.int16))
+
+
+# head_dim, group, KV heads, positions.  Alone a row runs in workgroups of four
+# waves and one split each; two and five rows in workgroups of four waves and
+# longer runs; all of them in workgroups of two waves.
+BATCHES = [
+    (128, 2, 8, [300, 1000, 2500, 6000, 9000, 40, 127, 0]),
+    (64, 4, 4, [4095, 4096, 16383, 2047, 129, 8200, 700, 15000]),
+]
+
+
+@pytest.mark.parametrize("d,group,hkv,pos", BATCHES)
+def test_a_row_does_not_depend_on_its_batch(P, d, group, hkv, pos):
+    """A row of up to 8 has the same bits alone, beside others and in another
+    order: its splits follow from its own position, and every division of them
+    over workgroups and waves merges the same partials in the same tree."""
+    cfg = configs.TINY.replace(n_layers=2, hidden=256, n_q_heads=group * hkv, n_kv_heads=hkv, head_dim=d, ffn=256,
+                               vocab=512, qk_norm=True, name="batch")
+    glob, layers = gen.model_weights(cfg, seed=64, gain_sigma=0.1)
+    model = gpu_model(P, cfg, glob, layers)
+    pages = [n // 16 + 1 for n in pos]
+    tables = gen.disjoint_block_tables(pages, sum(pages), max(pages), 64, 1)
+    pool = gen.kv_pool_normal(2, sum(pages), 16, hkv, d, 64, DEV)
+    ids = gen.token_ids(len(pos), cfg.vocab, seed=64)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+
+    def step(rows):
+        out = torch.full((len(rows), cfg.vocab), float("nan"), device=DEV)
+        mine = pool.clone()
+        ws = model.workspace(len(rows), len(rows))
+        model.decode_step(ids[rows].to(DEV), [pos[i] for i in rows], torch.tensor(tables[rows], device=DEV), mine, out,
+                          ws, err)
+        torch.cuda.synchronize()
+        resid = residual_rows(ws, len(rows), cfg.hidden)
+        new = [mine[:, :, tables[i, pos[i] // 16], pos[i] % 16].clone() for i in rows]
+        return {i: (out[k], resid[k].clone(), new[k]) for k, i in enumerate(rows)}
+
+    alone = {i: step([i])[i] for i in range(len(pos))}
+    for rows in ([0, 1], [4, 2], [6, 3, 0, 7, 1], list(range(8)), list(reversed(range(8)))):
+        got = step(rows)
+        for i in rows:
+            for what, a, b in zip(("logits", "residual", "K/V"), got[i], alone[i]):
+                assert torch.equal(a, b), f"{what} of position {pos[i]} beside {[pos[k] for k in rows]}"
+    assert int(err.item()) == 0
