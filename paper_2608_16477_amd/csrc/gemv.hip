@@ -378,7 +378,7 @@ hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   // 32-bit buffer offsets: 16 weight rows and the X rows
   if (static_cast<int64_t>(16) * ldb * 2 >= (int64_t(1) << 32) || static_cast<int64_t>(kGemvMaxRows) * lda * 2 >= (int64_t(1) << 32))
     return hipErrorInvalidValue;
-  const GemvPlan pl = gemv_plan(epi, M, N, K, sc.part_bytes);
+  const GemvPlan pl = gemv_plan(epi, M, N, K);
   if (pl.counters() > sc.ctr_count || pl.part_bytes() > sc.part_bytes) return hipErrorInvalidValue;
   GemvArgs a;
   a.X = A;

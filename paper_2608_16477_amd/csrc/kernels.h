@@ -356,7 +356,8 @@ struct GemvPlan {
   // Sum-of-squares partials of the residual epilogue, each 8 xb floats.
   int norm_parts() const { return tiles * tn; }
 };
-// The plan of least modelled time whose partial sums fit in `room` bytes.  A
+// The plan of least modelled time, from the shape and from M <= 8 or more
+// alone (so a row's arithmetic does not depend on the rows beside it).  A
 // CU holds r workgroups (their LDS stages decide), and a full round of 256 r
 // of them takes K / S u r + c0: u = the time 256 CUs need for one k of tn
 // blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split adds 1 us +
@@ -364,7 +365,7 @@ struct GemvPlan {
 // (us, tn / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
 // 14.2 (2 / 4 at M = 8), of the large one 19.7 (4 / 3), 20.2 (1 / 1), 21.6
 // (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3).
-inline GemvPlan gemv_plan(int epi, int M, int N, int K, size_t room) {
+inline GemvPlan gemv_plan(int epi, int M, int N, int K) {
   GemvPlan best{};
   const int xb = M <= 8 ? 1 : 2;
   const int64_t rows = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;
@@ -380,7 +381,7 @@ inline GemvPlan gemv_plan(int epi, int M, int N, int K, size_t room) {
     for (int S = 1; S <= kGemvMaxSplit; ++S) {
       const GemvPlan pl{xb, tn, S, tiles};
       const int64_t wgs = int64_t(tiles) * S;
-      if (S > 1 && (K / (S * 256) < 4 || wgs > 256 * resident || pl.part_bytes() > room)) break;
+      if (S > 1 && (K / (S * 256) < 4 || wgs > 256 * resident)) break;
       const double full = double(wgs / (256 * resident)), rest = double(wgs % (256 * resident));
       double t = full * (double(K) / S * u * resident + 3);
       if (rest > 0) t += double(K) / S * u * double((int(rest) + 255) / 256) + 3;

@@ -35,14 +35,23 @@ struct Workspace {
 constexpr int kDecodeMaxPos = 16384;
 constexpr int kDecodeMaxSplits = kDecodeMaxPos / 64;
 
-// Weight rows of the widest projection, and the room for the decode
-// projections' partial sums in a call of `r8` <= 8 rows (or more: 8).
-inline int64_t widest_projection(const pallas_model_config& c) {
-  const int64_t qkv = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
-  return std::max<int64_t>(std::max<int64_t>(qkv, 2 * int64_t(c.ffn)), std::max<int64_t>(c.hidden, c.vocab));
-}
-inline size_t gemv_room(const pallas_model_config& c, int r8) {
-  return size_t(kGemvMaxSplit) * r8 * widest_projection(c) * 4;
+// Bytes of partial sums and arrival counters that a decode step of `rows` <=
+// kGemvMaxRows rows needs (the largest of its five projections').
+struct GemvNeed {
+  size_t part_bytes = 0;
+  int counters = 0;
+};
+inline GemvNeed gemv_need(const pallas_model_config& c, int rows) {
+  const int QKV = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, QD = c.n_q_heads * c.head_dim;
+  const int proj[5][3] = {{kEpiBf16, QKV, c.hidden}, {kEpiAddF32, c.hidden, QD}, {kEpiSwiGLU, c.ffn, c.hidden},
+                          {kEpiAddF32, c.hidden, c.ffn}, {kEpiF32, c.vocab, c.hidden}};
+  GemvNeed need;
+  for (const auto& p : proj) {
+    const GemvPlan pl = gemv_plan(p[0], rows, p[1], p[2]);
+    need.part_bytes = std::max(need.part_bytes, pl.part_bytes());
+    need.counters = std::max(need.counters, pl.counters());
+  }
+  return need;
 }
 // Sums of squares of up to 16 rows: one partial of 16 floats per 16 columns
 // (GemvPlan, whole tiles of up to 64 columns).
@@ -86,14 +95,12 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.attn_split_bytes = attn_prefill_split_bytes(static_cast<int>(tokens < 256 ? tokens : 256),
                                                 c.n_q_heads, c.head_dim);
   w.attn_split = take(w.attn_split_bytes);
-  // Decode projections split over K: partial sums and one arrival counter
-  // per 16-row weight tile.
+  // Decode projections split over K: partial sums and arrival counters.
   {
-    const int64_t rows = widest_projection(c);
-    const int64_t r8 = std::min<int64_t>(std::min<int64_t>(seqs, tokens), 8);
-    w.gemv_part_bytes = gemv_room(c, int(r8));
+    const GemvNeed few = gemv_need(c, 8), more = gemv_need(c, kGemvMaxRows);
+    w.gemv_part_bytes = std::max(few.part_bytes, more.part_bytes);
     w.gemv_part = take(w.gemv_part_bytes);
-    w.gemv_ctr_count = static_cast<int>((rows + 15) / 16);
+    w.gemv_ctr_count = std::max(few.counters, more.counters);
     w.gemv_ctr = take(size_t(w.gemv_ctr_count) * 4);
   }
   w.total = at;
@@ -142,10 +149,9 @@ inline size_t static_decode_need(const pallas_model_config& c, int seqs, int max
 }
 
 // The layout a decode step of `seqs` <= 8 sequences runs in without a
-// workspace, with positions up to `max_pos`: the arithmetic is that of a step
-// in a full workspace (the same plans, chosen for the same room).  When it
-// would exceed `cap` bytes, the projections do not split.
-inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_pos, size_t cap) {
+// workspace, with positions up to `max_pos` (the same plans and kernels as in a
+// full workspace).
+inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_pos) {
   Workspace w{};
   const int64_t QKV = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   const int64_t QD = int64_t(c.n_q_heads) * c.head_dim;
@@ -161,26 +167,11 @@ inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_p
   w.part_splits = max_pos / 64 + 1;
   w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.part_splits).floats * 4);
   w.ssq = take(norm_bytes(c));
-  // (epi, N, K) of the five projections.
-  const int64_t proj[5][3] = {{kEpiBf16, QKV, c.hidden},
-                              {kEpiAddF32, c.hidden, QD},
-                              {kEpiSwiGLU, c.ffn, c.hidden},
-                              {kEpiAddF32, c.hidden, c.ffn},
-                              {kEpiF32, c.vocab, c.hidden}};
-  const size_t room = gemv_room(c, seqs);
-  size_t part = 0;
-  int ctr = 0;
-  for (const auto& pr : proj) {
-    const GemvPlan pl = gemv_plan(int(pr[0]), seqs, int(pr[1]), int(pr[2]), room);
-    part = std::max(part, pl.part_bytes());
-    ctr = std::max(ctr, pl.counters());
-  }
-  if (at + align_up(part, 256) + align_up(size_t(ctr) * 4, 256) <= cap) {
-    w.gemv_part_bytes = room;
-    w.gemv_part = take(part);
-    w.gemv_ctr_count = ctr;
-    w.gemv_ctr = take(size_t(ctr) * 4);
-  }
+  const GemvNeed need = gemv_need(c, seqs);
+  w.gemv_part_bytes = need.part_bytes;
+  w.gemv_part = take(need.part_bytes);
+  w.gemv_ctr_count = need.counters;
+  w.gemv_ctr = take(size_t(need.counters) * 4);
   w.total = at;
   return w;
 }

@@ -2,7 +2,6 @@
 // sequences.  Every check runs before anything is enqueued, so a rejected
 // call writes nothing.
 #include <algorithm>
-#include <array>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -478,16 +477,12 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
   pallas::DecodeRuns runs;
   if (!pallas::plan_decode_runs(rm, Hkv, runs)) return fail(PALLAS_ERR_UNSUPPORTED, "decode: positions beyond what a split holds");
-  int gemv_counters = 0;   // those the step's plans use
-  if (B <= pallas::kGemvMaxRows)
-    for (const auto& p : {std::array<int, 3>{pallas::kEpiBf16, QKV, H}, {pallas::kEpiAddF32, H, QD}, {pallas::kEpiSwiGLU, F, H},
-                          {pallas::kEpiAddF32, H, F}, {pallas::kEpiF32, c.vocab, H}})
-      gemv_counters = std::max(gemv_counters, pallas::gemv_plan(p[0], B, p[1], p[2], sc.part_bytes).counters());
+  const int gemv_counters = B <= pallas::kGemvMaxRows ? pallas::gemv_need(c, B).counters : 0;
   // The norms inside the projections: O and down write h = r g of the norm
   // that follows, with the sums of squares of r; the next projection scales.
   // The first layer's comes normalised from the embedding kernel.
-  const int o_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD, sc.part_bytes).norm_parts();
-  const int down_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, F, sc.part_bytes).norm_parts();
+  const int o_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD).norm_parts();
+  const int down_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, F).norm_parts();
   auto norm_in = [&](int parts) { return pallas::GemvNorm{parts ? ssq : nullptr, parts, c.rms_eps, nullptr, nullptr, nullptr}; };
   auto norm_out = [&](const void* gain) { return pallas::GemvNorm{nullptr, 0, c.rms_eps, u16(gain), h, ssq}; };
   // More than kGemvMaxRows rows run the GEMM's 64-row tiles; O and down are
@@ -705,7 +700,7 @@ int pallas_decode_step_static(pallas_model* m, int32_t num_seqs, const int32_t* 
   int max_pos = 0;
   for (int i = 0; i < num_seqs; ++i) max_pos = std::max(max_pos, h_positions[i]);
   const size_t need = pallas::static_decode_need(m->cfg, num_seqs, max_pos);
-  const pallas::Workspace w = pallas::decode_layout(m->cfg, num_seqs, max_pos, PALLAS_STATIC_SCRATCH_BYTES);
+  const pallas::Workspace w = pallas::decode_layout(m->cfg, num_seqs, max_pos);
   if (need > PALLAS_STATIC_SCRATCH_BYTES || w.total > PALLAS_STATIC_SCRATCH_BYTES)
     return fail(PALLAS_ERR_UNSUPPORTED,
                 "decode (static scratch): %d sequences up to position %d need %zu bytes of scratch (at most %zu)",

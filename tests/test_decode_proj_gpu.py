@@ -68,3 +68,35 @@ def test_rows(P, name, rows):
         ref, _, _ = om.decode(int(ids[i]), n, list(kv[:, 0]), list(kv[:, 1]), g, ls, shp)
         e = rel_err(out[0][i].double().cpu().numpy(), ref)
         assert e <= TOL, f"row {i} of {rows}: logits rel err {e:.3g}"
+
+
+def test_rows_do_not_depend_on_their_number(P):
+    """A row's logits and residual have the same bits in calls of 1 to 8 rows,
+    each in a workspace of just its size.  (Partial sums of a K split of gate|up
+    or down that a one-row workspace must hold too.)"""
+    cfg = configs.TINY.replace(n_layers=2, hidden=2048, n_q_heads=16, n_kv_heads=4, head_dim=64, ffn=3072, vocab=512,
+                               qk_norm=True)
+    glob, layers = gen.model_weights(cfg, seed=72, gain_sigma=0.1)
+    model = gpu_model(P, cfg, glob, layers)
+    pos = [5, 40, 17, 0, 33, 21, 60, 9]
+    pages = [n // 16 + 1 for n in pos]
+    tables = gen.disjoint_block_tables(pages, sum(pages), max(pages), 72, 1)
+    pool = gen.kv_pool_normal(cfg.n_layers, sum(pages), 16, cfg.n_kv_heads, cfg.head_dim, 72, DEV)
+    ids = gen.token_ids(8, cfg.vocab, seed=72)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+
+    def step(rows):
+        out = torch.full((len(rows), cfg.vocab), float("nan"), device=DEV)
+        ws = model.workspace(len(rows), len(rows))
+        model.decode_step(ids[rows].to(DEV), [pos[i] for i in rows], torch.tensor(tables[rows], device=DEV), pool.clone(),
+                          out, ws, err)
+        torch.cuda.synchronize()
+        return out, residual_rows(ws, len(rows), cfg.hidden).clone()
+
+    alone = [step([i]) for i in range(8)]
+    for n in (2, 3, 4, 5, 7, 8):
+        out, resid = step(list(range(8 - n, 8)))
+        for k, i in enumerate(range(8 - n, 8)):
+            assert torch.equal(resid[k], alone[i][1][0]), f"residual of row {i} among {n}"
+            assert torch.equal(out[k], alone[i][0][0]), f"logits of row {i} among {n}"
+    assert int(err.item()) == 0
