@@ -278,6 +278,9 @@ int pallas_assemble_kv(const pallas_kv_pool* dst, const int32_t* d_dst_block_tab
  * d_logits[i][0..V).  Rows may be tokens of one sequence, or share pages in
  * other ways: in each layer every row's K/V counts as stored before any row
  * attends.  (Which K/V a slot gets that two rows write is undefined.)
+ * A row's results do not depend, to the bit, on the other rows of a call of
+ * up to 8 sequences, nor on those of a call of 9 to 64 (the two differ in
+ * the last bits: their projections split their sums in other ways).
  * num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
  * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention keeps one
  * partial record per 64 keys in a workspace section of fixed size), and

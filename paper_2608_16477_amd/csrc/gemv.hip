@@ -1,4 +1,4 @@
-// Skinny GEMM for decode (M <= 16 rows): C = X W^T streaming the weights once.
+// Skinny GEMM for decode (M <= 8 rows): C = X W^T streaming the weights once.
 //
 // A workgroup of 4 waves owns a tile of TN blocks of 16 weight rows (for the
 // gate|up projection half of them gate rows and half the matching up rows)
@@ -14,8 +14,13 @@
 // per-tile counter, and the last to arrive adds the splits in order and
 // applies the epilogue (gemv_plan chooses TN and the splits).
 //
-// More than 16 rows run the GEMM (gemm.hip): X is then a large part of what a
-// wave keeps in flight, and its tiles share it between waves.
+// More than 8 rows run the GEMM (gemm.hip): X is then a large part of what a
+// wave keeps in flight, and the GEMM's tiles share it between waves.  (With two
+// blocks of X rows here, decode steps of 9, 12 and 16 rows took 1451, 1521 and
+// 1644 us against 1566, 1594 and 1676 through the GEMM at 12 layers of the mid
+// model, but 1984, 2133 and 2372 against 1827, 1924 and 2038 at 8 layers of the
+// large one; and 9 to 64 rows share the GEMM's K splits, so a row has the same
+// bits among any of them.)
 //
 // Weights are loaded non-temporally: they are read once per step, and the
 // stream runs 10% faster that way (M = 1: gate|up of the mid / large model 36
@@ -38,6 +43,7 @@ namespace {
 
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
+constexpr int kRows = kGemvMaxRows;   // rows of X: one block
 constexpr int kKStep = 64;        // k per stage: one 128-byte line per row
 constexpr int kBlockSlots = 68;   // 8 rows x 8 slots of 16 B, plus 4 slots of padding
 constexpr int kAuxAgent = 16;     // buffer cache policy: sc1 (device-coherent)
@@ -62,22 +68,21 @@ struct GemvArgs {
   GemvNorm nrm;
 };
 
-// Sums of squares of X's rows ([part][kMpad], four rows per thread): the first
+// Sums of squares of X's rows ([part][kRows], four rows per thread): the first
 // loads of a thread, started early and not waited for until finish(), then
 // (mean(x^2) + eps)^(-1/2) per row.
-template <int kMpad>
 struct RowScale {
-  static constexpr int kQ = kMpad / 4;
+  static constexpr int kQ = kRows / 4;
   static constexpr int U = 4;
   u32x4 x[U];
   __device__ __forceinline__ void load(const GemvNorm& n) {
-    const uint32_t bytes = n.ssq_in ? static_cast<uint32_t>(n.parts_in) * (kMpad * 4) : 0;
+    const uint32_t bytes = n.ssq_in ? static_cast<uint32_t>(n.parts_in) * (kRows * 4) : 0;
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)n.ssq_in, 0, bytes, 0x00020000);
 #pragma unroll
     for (int u = 0; u < U; ++u)   // past the end: zeros
       x[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (threadIdx.x + u * kThreads) * 16u, 0, 0));
   }
-  // Into row_inv[kMpad] through scratch [kWaves][kQ]; every thread calls it.
+  // Into row_inv[kRows] through scratch [kWaves][kQ]; every thread calls it.
   // Read row_inv after a barrier.
   __device__ __forceinline__ void finish(const GemvNorm& n, int K, f32x4* scratch, float* row_inv) {
     if (!n.ssq_in) return;
@@ -92,7 +97,7 @@ struct RowScale {
       for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], o, kWave);
     if ((threadIdx.x & 63) < kQ) scratch[(threadIdx.x >> 6) * kQ + (threadIdx.x & 63)] = v;
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (threadIdx.x < kMpad) {
+    if (threadIdx.x < kRows) {
       float s = 0.f;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) s += reinterpret_cast<const float*>(scratch + w * kQ)[threadIdx.x];
@@ -102,23 +107,20 @@ struct RowScale {
   }
 };
 
-// XB: 8-row blocks of X (M <= 8 XB), 1 or 2; NS: stages in flight per wave.
-template <int EPI, int TN, int XB, int NS>
+// NS: stages in flight per wave.
+template <int EPI, int TN, int NS>
 __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
-  constexpr int TM = (XB + 1) / 2;                // 16-row blocks of X
-  constexpr int kBlocks = 2 * TN + XB;            // load instructions per stage
+  constexpr int kBlocks = 2 * TN + 1;             // load instructions per stage
   constexpr int kStageSlots = kBlocks * kBlockSlots;
   constexpr int HT = TN > 1 ? TN / 2 : 1;         // gate|up: gate blocks of a tile
   constexpr int kRing = kWaves * NS * kStageSlots;
-  constexpr int kRed = kWaves * TN * TM * 64;     // partial tiles
+  constexpr int kRed = kWaves * TN * 64;          // partial tiles
   // (one array: see the decode attention kernel's note on LDS waits)
   constexpr int kMain = kRing > kRed ? kRing : kRed;
-  constexpr int kMpad = 8 * XB;
-  using Scale = RowScale<kMpad>;
-  __shared__ __attribute__((aligned(16))) u32x4 lds[kMain + (kWaves + 1) * Scale::kQ + 1];
+  __shared__ __attribute__((aligned(16))) u32x4 lds[kMain + (kWaves + 1) * RowScale::kQ + 1];
   f32x4* const scratch = reinterpret_cast<f32x4*>(lds + kMain);
-  float* const row_inv = reinterpret_cast<float*>(lds + kMain + kWaves * Scale::kQ);   // [kMpad]
-  int* const arrived = reinterpret_cast<int*>(lds + kMain + (kWaves + 1) * Scale::kQ);
+  float* const row_inv = reinterpret_cast<float*>(lds + kMain + kWaves * RowScale::kQ);   // [kRows]
+  int* const arrived = reinterpret_cast<int*>(lds + kMain + (kWaves + 1) * RowScale::kQ);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int li = lane & 15, kg = lane >> 4;
   const int tile = static_cast<int>(blockIdx.x) / p.S, ks = static_cast<int>(blockIdx.x) % p.S;
@@ -163,37 +165,29 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + (2 * t + h) * kBlockSlots), 16,
                                                  in ? woff + ko + h * 8u * p.ldw * 2u : kOob, 0, 0, kAuxStream);
     }
-#pragma unroll
-    for (int x = 0; x < XB; ++x)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + (2 * TN + x) * kBlockSlots), 16,
-                                               in ? xoff + ko + x * 8u * p.ldx * 2u : kOob, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(st + 2 * TN * kBlockSlots), 16, in ? xoff + ko : kOob, 0, 0, 0);
   };
 
-  f32x4 acc[TN][TM];
+  f32x4 acc[TN];
 #pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) acc[t][i] = f32x4{0, 0, 0, 0};
+  for (int t = 0; t < TN; ++t) acc[t] = f32x4{0, 0, 0, 0};
   auto compute = [&](int s) {
     const u32x4* st = wbase + (s % NS) * kStageSlots;
 #pragma unroll
     for (int q = 0; q < kKStep / 32; ++q) {
       const int sl = bslot(li & 7, 4 * q + kg);
-      bf16x8 a[TM];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)   // XB = 1: rows 8 to 15 repeat 0 to 7
-        a[i] = __builtin_bit_cast(bf16x8, st[(2 * TN + 2 * i + (XB == 1 ? 0 : li >> 3)) * kBlockSlots + sl]);
+      // (rows 8 to 15 of the operand repeat 0 to 7)
+      const bf16x8 a = __builtin_bit_cast(bf16x8, st[2 * TN * kBlockSlots + sl]);
 #pragma unroll
       for (int t = 0; t < TN; ++t) {
         const bf16x8 w = __builtin_bit_cast(bf16x8, st[(2 * t + (li >> 3)) * kBlockSlots + sl]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w, acc[t][i], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w, acc[t], 0, 0, 0);
       }
     }
   };
 
   for (int s = 0; s < NS - 1 && s < nst; ++s) issue(s);
-  Scale scale;
+  RowScale scale;
   scale.load(p.nrm);
   for (int s = 0; s < nst; ++s) {
     asm volatile("" ::: "memory");
@@ -209,23 +203,20 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
   }
   static_assert(NS == 2 || NS == 3, "the tail leaves at most one step in flight");
 
-  // Epilogue units: block t (gate|up: the pair t, t + HT) of row block i.
-  // Wave w takes row block w % TM and every (4 / TM)-th t, so a wave's units
-  // share their rows.
+  // Epilogue units: block t (gate|up: the pair t, t + HT).  Wave w takes every
+  // fourth, from w on.
   constexpr int kT = EPI == kEpiSwiGLU ? HT : TN;     // unit columns per tile
-  constexpr int kWavesPerRow = kWaves / TM;
-  constexpr int kUnits = (kT + kWavesPerRow - 1) / kWavesPerRow;   // per wave
+  constexpr int kUnits = (kT + kWaves - 1) / kWaves;  // per wave
   constexpr int kPer = EPI == kEpiSwiGLU ? 2 : 1;     // blocks per unit
-  const int ui = wave % TM, ut0 = wave / TM;
   // What the residual epilogue reads, started before the reductions.
   float old[kUnits][4], gain[kUnits];
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) {
-    const int t = ut0 + u * kWavesPerRow, col = col0(t) + li;
+    const int t = wave + u * kWaves, col = col0(t) + li;
     gain[u] = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int m = ui * 16 + kg * 4 + r;
+      const int m = kg * 4 + r;
       old[u][r] = 0.f;
       if (EPI == kEpiAddF32 && t < kT && col < N && m < M)
         old[u][r] = static_cast<const float*>(p.C)[static_cast<int64_t>(m) * p.ldc + col];
@@ -235,36 +226,34 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
   __syncthreads();
   f32x4* red = reinterpret_cast<f32x4*>(lds);
 #pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) red[((wave * TN + t) * TM + i) * 64 + lane] = acc[t][i];
+  for (int t = 0; t < TN; ++t) red[(wave * TN + t) * 64 + lane] = acc[t];
   __syncthreads();
   f32x4 sum[kUnits][kPer];
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) {
-    const int t0 = ut0 + u * kWavesPerRow;
+    const int t0 = wave + u * kWaves;
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       const int t = t0 + e * HT;
       sum[u][e] = f32x4{};
       if (t0 < kT)
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) sum[u][e] += red[((w * TN + t) * TM + ui) * 64 + lane];
+        for (int w = 0; w < kWaves; ++w) sum[u][e] += red[(w * TN + t) * 64 + lane];
     }
   }
   if (p.S > 1) {
     // Partial tiles in register layout: 16 bytes per lane, whole lines.
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(p.part + static_cast<int64_t>(tile) * p.S * (TN * TM * 256)), 0,
-        static_cast<uint32_t>(p.S) * (TN * TM * 1024), 0x00020000);
+        (void*)(p.part + static_cast<int64_t>(tile) * p.S * (TN * 256)), 0,
+        static_cast<uint32_t>(p.S) * (TN * 1024), 0x00020000);
 #pragma unroll
     for (int u = 0; u < kUnits; ++u)
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
-        const int t0 = ut0 + u * kWavesPerRow, t = t0 + e * HT;
+        const int t0 = wave + u * kWaves, t = t0 + e * HT;
         __builtin_amdgcn_raw_buffer_store_b128(
             __builtin_bit_cast(u32x4, sum[u][e]), rp,
-            t0 < kT && ui * 16 + kg * 4 < M ? static_cast<uint32_t>(((ks * TN + t) * TM + ui) * 64 + lane) * 16u : kOob,
+            t0 < kT && kg * 4 < M ? static_cast<uint32_t>((ks * TN + t) * 64 + lane) * 16u : kOob,
             0, kAuxAgent);
       }
     // The partials are agent-scope stores, which write through this XCD's L2
@@ -288,12 +277,12 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
     for (int u = 0; u < kUnits; ++u)
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
-        const int t0 = ut0 + u * kWavesPerRow, t = t0 + e * HT;
+        const int t0 = wave + u * kWaves, t = t0 + e * HT;
         f32x4 v[kGemvMaxSplit];
 #pragma unroll
         for (int j = 0; j < kGemvMaxSplit; ++j)     // past S: reads zeros
           v[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-              rp, j < p.S && t0 < kT ? static_cast<uint32_t>(((j * TN + t) * TM + ui) * 64 + lane) * 16u : kOob, 0,
+              rp, j < p.S && t0 < kT ? static_cast<uint32_t>((j * TN + t) * 64 + lane) * 16u : kOob, 0,
               kAuxAgent));
         sum[u][e] = v[0];
 #pragma unroll
@@ -306,18 +295,18 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
     scale.finish(p.nrm, p.K, scratch, row_inv);
     asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-    for (int r = 0; r < 4; ++r) inv[r] = row_inv[min(ui * 16 + kg * 4 + r, kMpad - 1)];
+    for (int r = 0; r < 4; ++r) inv[r] = row_inv[min(kg * 4 + r, kRows - 1)];
   }
-  // lane holds column li and rows 16 ui + 4 kg + r
+  // lane holds column li and rows 4 kg + r
   float ss[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) {
-    const int t = ut0 + u * kWavesPerRow;
+    const int t = wave + u * kWaves;
     const int col = col0(t) + li;
     if (t >= kT || col >= N) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int m = ui * 16 + kg * 4 + r;
+      const int m = kg * 4 + r;
       if (m >= M) continue;
       const int64_t at = static_cast<int64_t>(m) * p.ldc + col;
       const float v = sum[u][0][r] * inv[r];
@@ -337,37 +326,24 @@ __global__ __launch_bounds__(kThreads) void gemv_kernel(GemvArgs p) {
       }
     }
   }
-  if (EPI == kEpiAddF32 && p.nrm.gain_out && ut0 < kT) {
+  if (EPI == kEpiAddF32 && p.nrm.gain_out && wave < kT) {
     // One partial per row and wave of the tile that covers it.
     f32x4 sq;
 #pragma unroll
     for (int r = 0; r < 4; ++r) sq[r] = row16_sum(ss[r]);
-    if (li == 0 && ui * 16 + kg * 4 < kMpad)
+    if (li == 0 && kg * 4 < kRows)
       *reinterpret_cast<f32x4*>(p.nrm.ssq_out +
-                                (static_cast<int64_t>(tile) * min(kT, kWavesPerRow) + ut0) * kMpad + ui * 16 + kg * 4) = sq;
+                                (static_cast<int64_t>(tile) * kT + wave) * kRows + kg * 4) = sq;
   }
-}
-
-template <int EPI, int XB>
-hipError_t launch_ring(const GemvArgs& a, int tn, int grid, hipStream_t s) {
-  if constexpr (XB == 1 && EPI != kEpiSwiGLU) {
-    if (tn == 1) {
-      gemv_kernel<EPI, 1, XB, 3><<<grid, kThreads, 0, s>>>(a);
-      return hipGetLastError();
-    }
-  }
-  if (tn == 2) {
-    gemv_kernel<EPI, 2, XB, 2><<<grid, kThreads, 0, s>>>(a);
-    return hipGetLastError();
-  }
-  if (tn != 4) return hipErrorInvalidValue;
-  gemv_kernel<EPI, 4, XB, 2><<<grid, kThreads, 0, s>>>(a);
-  return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemvArgs& a, const GemvPlan& pl, int grid, hipStream_t s) {
-  return pl.xb == 1 ? launch_ring<EPI, 1>(a, pl.tn, grid, s) : launch_ring<EPI, 2>(a, pl.tn, grid, s);
+  if (pl.tn == 2) gemv_kernel<EPI, 2, 2><<<grid, kThreads, 0, s>>>(a);
+  else if (pl.tn == 4) gemv_kernel<EPI, 4, 2><<<grid, kThreads, 0, s>>>(a);
+  else if constexpr (EPI != kEpiSwiGLU) gemv_kernel<EPI, 1, 3><<<grid, kThreads, 0, s>>>(a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -378,7 +354,7 @@ hipError_t launch_gemv(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   // 32-bit buffer offsets: 16 weight rows and the X rows
   if (static_cast<int64_t>(16) * ldb * 2 >= (int64_t(1) << 32) || static_cast<int64_t>(kGemvMaxRows) * lda * 2 >= (int64_t(1) << 32))
     return hipErrorInvalidValue;
-  const GemvPlan pl = gemv_plan(epi, M, N, K);
+  const GemvPlan pl = gemv_plan(epi, N, K);
   if (pl.counters() > sc.ctr_count || pl.part_bytes() > sc.part_bytes) return hipErrorInvalidValue;
   GemvArgs a;
   a.X = A;

@@ -340,24 +340,23 @@ hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, 
                                    int part_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM
-// C[m][n] (op) A[m] . B[n] for m < M <= 16 rows (gemv.hip); epilogues as
+// C[m][n] (op) A[m] . B[n] for m < M <= 8 rows (gemv.hip); epilogues as
 // launch_gemm.
 constexpr int kGemvMaxSplit = 8;
-constexpr int kGemvMaxRows = 16;
+constexpr int kGemvMaxRows = 8;
 
 // How a projection runs: workgroups of 4 waves, each a tile of tn blocks of
 // 16 weight rows over 1 / S of K.
 struct GemvPlan {
-  int xb;      // 8-row blocks of A covered: 1 or 2
   int tn, S;
   int tiles;
   size_t part_bytes() const { return S > 1 ? size_t(tiles) * S * tn * 1024 : 0; }
   int counters() const { return S > 1 ? tiles : 0; }
-  // Sum-of-squares partials of the residual epilogue, each 8 xb floats.
+  // Sum-of-squares partials of the residual epilogue, each kGemvMaxRows floats.
   int norm_parts() const { return tiles * tn; }
 };
-// The plan of least modelled time, from the shape and from M <= 8 or more
-// alone (so a row's arithmetic does not depend on the rows beside it).  A
+// The plan of least modelled time, from the shape alone (so a row's arithmetic
+// does not depend on the rows beside it).  A
 // CU holds r workgroups (their LDS stages decide), and a full round of 256 r
 // of them takes K / S u r + c0: u = the time 256 CUs need for one k of tn
 // blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split adds 1 us +
@@ -365,21 +364,20 @@ struct GemvPlan {
 // (us, tn / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
 // 14.2 (2 / 4 at M = 8), of the large one 19.7 (4 / 3), 20.2 (1 / 1), 21.6
 // (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3).
-inline GemvPlan gemv_plan(int epi, int M, int N, int K) {
+inline GemvPlan gemv_plan(int epi, int N, int K) {
   GemvPlan best{};
-  const int xb = M <= 8 ? 1 : 2;
   const int64_t rows = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;
   double best_t = 0;
   for (int tn = 1; tn <= 4; tn *= 2) {
-    if (tn == 1 && (xb > 1 || epi == kEpiSwiGLU)) continue;
+    if (tn == 1 && epi == kEpiSwiGLU) continue;
     const int stages = tn == 1 ? 3 : 2;
-    const int lds = 4 * stages * (2 * tn + xb) * 1088 + 1024;   // 8-row blocks of 68 x 16 bytes
+    const int lds = 4 * stages * (2 * tn + 1) * 1088 + 1024;   // 8-row blocks of 68 x 16 bytes
     const int resident = 160 * 1024 / lds;
     const int per = epi == kEpiSwiGLU ? tn * 8 : tn * 16;       // output columns per tile
     const int tiles = (N + per - 1) / per;
     const double u = tn * 32.0 * 256 / 5.5e6;                   // us per k and workgroup of a CU
     for (int S = 1; S <= kGemvMaxSplit; ++S) {
-      const GemvPlan pl{xb, tn, S, tiles};
+      const GemvPlan pl{tn, S, tiles};
       const int64_t wgs = int64_t(tiles) * S;
       if (S > 1 && (K / (S * 256) < 4 || wgs > 256 * resident)) break;
       const double full = double(wgs / (256 * resident)), rest = double(wgs % (256 * resident));
@@ -405,7 +403,7 @@ struct GemvScratch {
 // output is scaled by (sum of ssq_in[0..parts_in)[m] / K + eps)^(-1/2)
 // (ssq_in null: no scale).  Out (kEpiAddF32 only, gain_out not null): h_out =
 // bf16(C gain_out), laid out as C, and the sums of squares of C's rows in
-// ssq_out[norm_parts()][8 xb] of the plan.
+// ssq_out[norm_parts()][kGemvMaxRows] of the plan.
 struct GemvNorm {
   const float* ssq_in;
   int parts_in;

@@ -35,27 +35,27 @@ struct Workspace {
 constexpr int kDecodeMaxPos = 16384;
 constexpr int kDecodeMaxSplits = kDecodeMaxPos / 64;
 
-// Bytes of partial sums and arrival counters that a decode step of `rows` <=
+// Bytes of partial sums and arrival counters that a decode step of up to
 // kGemvMaxRows rows needs (the largest of its five projections').
 struct GemvNeed {
   size_t part_bytes = 0;
   int counters = 0;
 };
-inline GemvNeed gemv_need(const pallas_model_config& c, int rows) {
+inline GemvNeed gemv_need(const pallas_model_config& c) {
   const int QKV = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, QD = c.n_q_heads * c.head_dim;
   const int proj[5][3] = {{kEpiBf16, QKV, c.hidden}, {kEpiAddF32, c.hidden, QD}, {kEpiSwiGLU, c.ffn, c.hidden},
                           {kEpiAddF32, c.hidden, c.ffn}, {kEpiF32, c.vocab, c.hidden}};
   GemvNeed need;
   for (const auto& p : proj) {
-    const GemvPlan pl = gemv_plan(p[0], rows, p[1], p[2]);
+    const GemvPlan pl = gemv_plan(p[0], p[1], p[2]);
     need.part_bytes = std::max(need.part_bytes, pl.part_bytes());
     need.counters = std::max(need.counters, pl.counters());
   }
   return need;
 }
-// Sums of squares of up to 16 rows: one partial of 16 floats per 16 columns
+// Sums of squares of up to kGemvMaxRows rows: one partial per 16 columns
 // (GemvPlan, whole tiles of up to 64 columns).
-inline size_t norm_bytes(const pallas_model_config& c) { return (size_t(c.hidden) + 256) * 4; }
+inline size_t norm_bytes(const pallas_model_config& c) { return (size_t(c.hidden) / 16 + 4) * kGemvMaxRows * 4; }
 
 inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, int64_t seqs) {
   Workspace w;
@@ -97,11 +97,11 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.attn_split = take(w.attn_split_bytes);
   // Decode projections split over K: partial sums and arrival counters.
   {
-    const GemvNeed few = gemv_need(c, 8), more = gemv_need(c, kGemvMaxRows);
-    w.gemv_part_bytes = std::max(few.part_bytes, more.part_bytes);
-    w.gemv_part = take(w.gemv_part_bytes);
-    w.gemv_ctr_count = std::max(few.counters, more.counters);
-    w.gemv_ctr = take(size_t(w.gemv_ctr_count) * 4);
+    const GemvNeed need = gemv_need(c);
+    w.gemv_part_bytes = need.part_bytes;
+    w.gemv_part = take(need.part_bytes);
+    w.gemv_ctr_count = need.counters;
+    w.gemv_ctr = take(size_t(need.counters) * 4);
   }
   w.total = at;
   return w;
@@ -167,7 +167,7 @@ inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_p
   w.part_splits = max_pos / 64 + 1;
   w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.part_splits).floats * 4);
   w.ssq = take(norm_bytes(c));
-  const GemvNeed need = gemv_need(c, seqs);
+  const GemvNeed need = gemv_need(c);
   w.gemv_part_bytes = need.part_bytes;
   w.gemv_part = take(need.part_bytes);
   w.gemv_ctr_count = need.counters;

@@ -477,12 +477,12 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
   const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
   pallas::DecodeRuns runs;
   if (!pallas::plan_decode_runs(rm, Hkv, runs)) return fail(PALLAS_ERR_UNSUPPORTED, "decode: positions beyond what a split holds");
-  const int gemv_counters = B <= pallas::kGemvMaxRows ? pallas::gemv_need(c, B).counters : 0;
+  const int gemv_counters = B <= pallas::kGemvMaxRows ? pallas::gemv_need(c).counters : 0;
   // The norms inside the projections: O and down write h = r g of the norm
   // that follows, with the sums of squares of r; the next projection scales.
   // The first layer's comes normalised from the embedding kernel.
-  const int o_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, QD).norm_parts();
-  const int down_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, B, H, F).norm_parts();
+  const int o_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, H, QD).norm_parts();
+  const int down_parts = B > pallas::kGemvMaxRows ? 0 : pallas::gemv_plan(pallas::kEpiAddF32, H, F).norm_parts();
   auto norm_in = [&](int parts) { return pallas::GemvNorm{parts ? ssq : nullptr, parts, c.rms_eps, nullptr, nullptr, nullptr}; };
   auto norm_out = [&](const void* gain) { return pallas::GemvNorm{nullptr, 0, c.rms_eps, u16(gain), h, ssq}; };
   // More than kGemvMaxRows rows run the GEMM's 64-row tiles; O and down are

@@ -1,6 +1,6 @@
 """The decode projections at the row counts and shapes where their plan
 changes, against the oracle's decode layer by layer over random caches: 1, 8,
-9, 16, 17, 32, 33 and 64 rows (the streaming kernel up to 16 rows, the GEMM's
+9, 16, 17, 32, 33 and 64 rows (the streaming kernel up to 8 rows, the GEMM's
 64-row tiles above); K split over workgroups and not; more and fewer weight
 rows than the workgroups take at once; weight rows that are not multiples of a
 tile; a K that is not a multiple of 64.  Logits and residual within 1e-2 max|ref|
@@ -70,33 +70,37 @@ def test_rows(P, name, rows):
         assert e <= TOL, f"row {i} of {rows}: logits rel err {e:.3g}"
 
 
-def test_rows_do_not_depend_on_their_number(P):
-    """A row's logits and residual have the same bits in calls of 1 to 8 rows,
-    each in a workspace of just its size.  (Partial sums of a K split of gate|up
-    or down that a one-row workspace must hold too.)"""
+@pytest.mark.parametrize("counts", [[1, 2, 3, 4, 5, 7, 8], [9, 12, 16, 17, 32, 33, 64]])
+def test_rows_do_not_depend_on_their_number(P, counts):
+    """A row's logits and residual have the same bits in calls of 1 to 8 rows, and
+    in calls of 9 to 64, each in a workspace of just its size.  (O and down
+    split K in both; gate|up too in some: their partial sums set what a
+    workspace for one row must hold.)"""
     cfg = configs.TINY.replace(n_layers=2, hidden=2048, n_q_heads=16, n_kv_heads=4, head_dim=64, ffn=3072, vocab=512,
                                qk_norm=True)
     glob, layers = gen.model_weights(cfg, seed=72, gain_sigma=0.1)
     model = gpu_model(P, cfg, glob, layers)
-    pos = [5, 40, 17, 0, 33, 21, 60, 9]
+    most = max(counts)
+    pos = [(5 + 37 * i) % 67 for i in range(most)]
     pages = [n // 16 + 1 for n in pos]
     tables = gen.disjoint_block_tables(pages, sum(pages), max(pages), 72, 1)
     pool = gen.kv_pool_normal(cfg.n_layers, sum(pages), 16, cfg.n_kv_heads, cfg.head_dim, 72, DEV)
-    ids = gen.token_ids(8, cfg.vocab, seed=72)
+    ids = gen.token_ids(most, cfg.vocab, seed=72)
     err = torch.zeros(1, dtype=torch.int32, device=DEV)
 
-    def step(rows):
-        out = torch.full((len(rows), cfg.vocab), float("nan"), device=DEV)
-        ws = model.workspace(len(rows), len(rows))
+    def step(first, n):
+        rows = list(range(first, first + n))
+        out = torch.full((n, cfg.vocab), float("nan"), device=DEV)
+        ws = model.workspace(n, n)
         model.decode_step(ids[rows].to(DEV), [pos[i] for i in rows], torch.tensor(tables[rows], device=DEV), pool.clone(),
                           out, ws, err)
         torch.cuda.synchronize()
-        return out, residual_rows(ws, len(rows), cfg.hidden).clone()
+        return out, residual_rows(ws, n, cfg.hidden).clone()
 
-    alone = [step([i]) for i in range(8)]
-    for n in (2, 3, 4, 5, 7, 8):
-        out, resid = step(list(range(8 - n, 8)))
-        for k, i in enumerate(range(8 - n, 8)):
-            assert torch.equal(resid[k], alone[i][1][0]), f"residual of row {i} among {n}"
-            assert torch.equal(out[k], alone[i][0][0]), f"logits of row {i} among {n}"
+    all_out, all_resid = step(0, most)
+    for n in counts:
+        for first in {0, most - n, (most - n) // 2}:
+            out, resid = step(first, n)
+            assert torch.equal(resid, all_resid[first:first + n]), f"residuals of rows {first}, +{n}"
+            assert torch.equal(out, all_out[first:first + n]), f"logits of rows {first}, +{n}"
     assert int(err.item()) == 0
