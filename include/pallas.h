@@ -282,10 +282,9 @@ int pallas_assemble_kv(const pallas_kv_pool* dst, const int32_t* d_dst_block_tab
  * up to 8 sequences, nor on those of a call of 9 to 64 (the two differ in
  * the last bits: their projections split their sums in other ways).
  * num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
- * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention keeps one
- * partial record per 64 keys in a workspace section of fixed size), and
- * n_i + 1 <= max_pages * page (OUT_OF_RANGE).  For more than 8
- * sequences the 2 GiB operand limit of pallas_prefill_prefix applies, also to
+ * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention cuts a
+ * sequence into at most 16 splits of at most 1024 keys), and n_i + 1 <=
+ * max_pages * page (OUT_OF_RANGE).  For more than 8 sequences the 2 GiB operand limit of pallas_prefill_prefix applies, also to
  * lm_head [V][hidden].
  * Table entries outside [0, num_pages) raise PALLAS_DEVERR_PAGE (the K/V
  * store of slot n_i is skipped; keys on such pages are masked), token ids

@@ -656,14 +656,12 @@ bool plan_decode_runs(const RowMap& rm, int Hkv, DecodeRuns& runs) {
 }
 
 hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, const DecodeRuns& runs, float* part,
-                                   int part_splits, hipStream_t s) {
+                                   int max_splits, hipStream_t s) {
   if (p.Hq % p.Hkv != 0 || p.page != kPage) return hipErrorInvalidValue;
   const int G = p.Hq / p.Hkv;
   if (G > 8 || (G & (G - 1)) != 0) return hipErrorInvalidValue;
-  // Records of runs.most runs in a section sized for part_splits splits of 64
-  // keys: counters, then outputs, then maxima and sums.
-  const DecodeAttnScratch sc = decode_attn_scratch(rm.n_seqs, p.Hq, p.Hkv, p.d, part_splits);
-  if (runs.most > 1 && runs.most > sc.max_splits) return hipErrorInvalidValue;
+  if (runs.most > max_splits) return hipErrorInvalidValue;
+  const DecodeAttnScratch sc = decode_attn_scratch(rm.n_seqs, p.Hq, p.Hkv, p.d, max_splits);
   int* ctr = reinterpret_cast<int*>(part);
   float* po = part + sc.out_floats;
   float* pml = part + sc.ml_floats;

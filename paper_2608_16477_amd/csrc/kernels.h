@@ -308,22 +308,19 @@ constexpr int kDecodeMaxRunSplits = 4;  // its merges in progress are held in re
 __host__ __device__ inline int decode_split_keys(int n) {
   return (n / kDecodeSplitsPerSeq + kDecodeMinSplit) / kDecodeMinSplit * kDecodeMinSplit;
 }
-// A section of [n_seqs][Hq][part_splits][d + 2] floats, part_splits = largest
-// position / 64 + 1: arrival counters (zero on entry, left zero), outputs
-// [n_seqs][Hkv][run][G][d], then maxima and sums.  With fewer than two splits
-// nothing is used; otherwise half the records leave room for the counters.
+// The section of decode attention for up to max_splits splits per sequence:
+// arrival counters (zero on entry, left zero), outputs [n_seqs][Hkv][run][G]
+// [d], then maxima and sums.  With one split nothing is used.
 struct DecodeAttnScratch {
-  int max_splits;          // splits per sequence that fit
   int counters;            // ints to clear at the start of the section
   size_t out_floats, ml_floats, floats;
 };
-inline DecodeAttnScratch decode_attn_scratch(int n_seqs, int Hq, int Hkv, int d, int part_splits) {
+inline DecodeAttnScratch decode_attn_scratch(int n_seqs, int Hq, int Hkv, int d, int max_splits) {
   DecodeAttnScratch s;
-  s.max_splits = (part_splits + 1) / 2 < kDecodeSplitsPerSeq ? (part_splits + 1) / 2 : kDecodeSplitsPerSeq;
-  s.counters = s.max_splits > 1 ? n_seqs * Hkv : 0;
+  s.counters = max_splits > 1 ? n_seqs * Hkv : 0;
   s.out_floats = (size_t(n_seqs) * Hkv + 63) / 64 * 64;
-  s.ml_floats = s.out_floats + size_t(n_seqs) * Hq * s.max_splits * d;
-  s.floats = s.max_splits > 1 ? s.ml_floats + size_t(n_seqs) * Hq * s.max_splits * 2 : 0;
+  s.ml_floats = s.out_floats + size_t(n_seqs) * Hq * max_splits * d;
+  s.floats = max_splits > 1 ? s.ml_floats + size_t(n_seqs) * Hq * max_splits * 2 : 0;
   return s;
 }
 // Work of a call: sequence s has runs [first[s], first[s + 1]) of per_run[s]
@@ -337,7 +334,7 @@ struct DecodeRuns {
 // False where a position is outside what the kernel takes.
 bool plan_decode_runs(const RowMap& rm, int Hkv, DecodeRuns& runs);
 hipError_t launch_attention_decode(const DecodeAttnParams& p, const RowMap& rm, const DecodeRuns& runs, float* part,
-                                   int part_splits, hipStream_t s);
+                                   int max_splits, hipStream_t s);
 
 // ------------------------------------------------------------ skinny GEMM
 // C[m][n] (op) A[m] . B[n] for m < M <= 8 rows (gemv.hip); epilogues as

@@ -26,14 +26,14 @@ struct Workspace {
   size_t resid, h, qkv, q, o, act, rope, part, split, split_bytes, attn_split, attn_split_bytes;
   size_t gemv_part, gemv_part_bytes, gemv_ctr, ssq, shared;
   int gemv_ctr_count;
-  int part_splits;   // decode attention: largest position / 64 + 1 the section is sized for
+  int decode_splits;   // decode attention: splits per sequence its section holds
   size_t total;
 };
 
-// Decode positions are below this bound; decode attention keeps one partial
-// record per 64-key split.
-constexpr int kDecodeMaxPos = 16384;
-constexpr int kDecodeMaxSplits = kDecodeMaxPos / 64;
+// Decode positions are below this bound: as many splits as a sequence has, as
+// long as a workgroup takes.
+constexpr int kDecodeMaxPos = kDecodeSplitsPerSeq * kDecodeMaxRun;
+static_assert(kDecodeMaxPos == 16384, "the decode position limit");
 
 // Bytes of partial sums and arrival counters that a decode step of up to
 // kGemvMaxRows rows needs (the largest of its five projections').
@@ -70,14 +70,9 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
   w.act = take(size_t(tokens) * c.ffn * 2);
   w.rope = take(size_t(tokens) * (c.head_dim / 2) * 8);  // (cos, sin) per row and pair
   w.shared = take(size_t(seqs) * 4);                     // decode: a flag per row
-  w.part_splits = kDecodeMaxSplits;
-  const size_t part_bytes = size_t(seqs) * c.n_q_heads * kDecodeMaxSplits * (c.head_dim + 2) * 4;
-  w.part = take(part_bytes);
-  // Sums of squares of the decode norms, at the end of that section (decode
-  // attention uses a sixteenth of it) where they fit.
-  const size_t records = decode_attn_scratch(int(seqs), c.n_q_heads, c.n_kv_heads, c.head_dim, kDecodeMaxSplits).floats * 4;
-  w.ssq = align_up(w.part + records, 256);
-  if (w.ssq + norm_bytes(c) > w.part + part_bytes) w.ssq = take(norm_bytes(c));
+  w.decode_splits = kDecodeSplitsPerSeq;
+  w.part = take(decode_attn_scratch(int(seqs), c.n_q_heads, c.n_kv_heads, c.head_dim, w.decode_splits).floats * 4);
+  w.ssq = take(norm_bytes(c));   // decode: sums of squares
   // Split-K partial sums of the projections of up to 256 rows.
   {
     const int rows = static_cast<int>(tokens < 256 ? tokens : 256);
@@ -164,8 +159,8 @@ inline Workspace decode_layout(const pallas_model_config& c, int seqs, int max_p
   w.act = take(size_t(seqs) * c.ffn * 2);
   w.rope = take(size_t(seqs) * (c.head_dim / 2) * 8);
   w.shared = take(size_t(seqs) * 4);
-  w.part_splits = max_pos / 64 + 1;
-  w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.part_splits).floats * 4);
+  w.decode_splits = std::min(max_pos / kDecodeMinSplit + 1, kDecodeSplitsPerSeq);
+  w.part = take(decode_attn_scratch(seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, w.decode_splits).floats * 4);
   w.ssq = take(norm_bytes(c));
   const GemvNeed need = gemv_need(c);
   w.gemv_part_bytes = need.part_bytes;

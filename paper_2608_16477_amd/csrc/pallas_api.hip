@@ -474,7 +474,7 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
 
   const pallas::GemvScratch sc{reinterpret_cast<float*>(ws + w.gemv_part), w.gemv_part_bytes,
                                reinterpret_cast<int*>(ws + w.gemv_ctr), w.gemv_ctr_count};
-  const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.part_splits);
+  const pallas::DecodeAttnScratch as = pallas::decode_attn_scratch(B, Hq, Hkv, d, w.decode_splits);
   pallas::DecodeRuns runs;
   if (!pallas::plan_decode_runs(rm, Hkv, runs)) return fail(PALLAS_ERR_UNSUPPORTED, "decode: positions beyond what a split holds");
   const int gemv_counters = B <= pallas::kGemvMaxRows ? pallas::gemv_need(c).counters : 0;
@@ -528,7 +528,7 @@ int run_decode(const pallas_model* m, const pallas::RowMap& rm, const int32_t* t
     ap.k_gain = u16(L.k_norm);
     ap.k_plane = pl.k;
     ap.v_plane = pl.v;
-    PALLAS_TRY(PALLAS_K_DECODE_ATTN, pallas::launch_attention_decode(ap, rm, runs, part, w.part_splits, s), "decode attention");
+    PALLAS_TRY(PALLAS_K_DECODE_ATTN, pallas::launch_attention_decode(ap, rm, runs, part, w.decode_splits, s), "decode attention");
     PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiAddF32, o, u16(L.w_o), r, H, QD, norm_out(L.mlp_norm)), "o proj");
     PALLAS_TRY(PALLAS_K_DECODE_PROJ, project(pallas::kEpiSwiGLU, h, u16(L.w_gate_up), act, F, H, norm_in(o_parts)),
                "gate_up proj");

@@ -343,3 +343,21 @@ def test_static_decode_host_rejections(P):
         assert rc([-1]) == P.Status.OUT_OF_RANGE
     finally:
         h.pallas_model_destroy(model)
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(hidden=131072, n_q_heads=1, n_kv_heads=1, ffn=64, vocab=64),
+                                   dict(hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, ffn=4096, vocab=512)])
+def test_a_workspace_serves_smaller_calls(P, shape):
+    """A workspace for some tokens and sequences is large enough for calls of
+    fewer: its size never falls as either grows."""
+    from workloads import configs
+    h = P.lib()
+    model = fake_model(P, configs.TINY.replace(**shape))
+    try:
+        size = {(t, s): h.pallas_workspace_size(model, t, s) for t in (1, 8, 64, 255, 256, 257, 1000)
+                for s in range(1, min(t, 64) + 1)}
+        for (t, s), b in size.items():
+            for t2, s2 in ((t, s + 1), ({1: 8, 8: 64, 64: 255, 255: 256, 256: 257, 257: 1000}.get(t), s)):
+                assert size.get((t2, s2), b) >= b, f"{t} tokens, {s} sequences need more than {t2}, {s2}"
+    finally:
+        h.pallas_model_destroy(model)
