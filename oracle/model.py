@@ -241,12 +241,14 @@ def prefill_chunk(ids: Sequence[int], start: int, K_cache: List[np.ndarray],
 
 
 def decode(token: int, n: int, K_cache: List[np.ndarray], V_cache: List[np.ndarray],
-           glob: Dict, layers: List[Dict], shp: Shape, rnd: Rounder = bf16_round):
+           glob: Dict, layers: List[Dict], shp: Shape, rnd: Rounder = bf16_round,
+           with_residual: bool = False):
     """One decode step: token ``token`` at position ``n`` attends to the
     cached positions 0..n-1 and to itself.
 
     ``K_cache[l], V_cache[l]`` hold ``[n, Hkv, d]``.  Returns ``(logits [V],
-    k_new, v_new)`` with this token's per-layer K/V ``[1, Hkv, d]``."""
+    k_new, v_new)`` with this token's per-layer K/V ``[1, Hkv, d]``, and with
+    ``with_residual`` the residual leaving the last layer ``[H]`` too."""
     pos = np.array([n])
     r = embed([token], glob)
     k_new, v_new = [], []
@@ -254,4 +256,5 @@ def decode(token: int, n: int, K_cache: List[np.ndarray], V_cache: List[np.ndarr
         r, k, v = layer(r, pos, K_cache[l][:n], V_cache[l][:n], layers[l], shp, rnd)
         k_new.append(k)
         v_new.append(v)
-    return logits(r, glob, shp, rnd)[0], k_new, v_new
+    out = logits(r, glob, shp, rnd)[0], k_new, v_new
+    return (*out, r[0]) if with_residual else out

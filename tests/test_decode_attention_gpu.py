@@ -1,11 +1,12 @@
 """Decode attention at the sizes where its work split changes, against the
 oracle's decode over the same random caches: 32-key blocks, 128-key splits and
-their multiples, one split (no merge) and sixteen, four-wave and two-wave
-workgroups (at most / more than 256 of them), head_dim 64 and 128, groups of
-1, 2, 4 and 8 query heads.  Unwritten slots hold NaN patterns; table entries
+their multiples, one split (no merge) and sixteen, workgroups of four waves and
+of two (where more than 256 are needed), runs of one split and of several,
+head_dim 64 and 128, groups of 1, 2, 4 and 8 query heads.  Unwritten slots hold NaN patterns; table entries
 outside the pool mask their keys.  Residual and logits within
 max|gpu - ref| <= 1e-2 max|ref| per row (the bf16 bound of the other decode
-tests); the K/V written within it too."""
+tests); the K/V written within it too, and nothing else in the pool changed.
+Then what several rows of a call may share, and what a row's bits depend on."""
 import numpy as np
 import pytest
 import torch
@@ -70,12 +71,15 @@ def test_split_edges(P, d, group, hkv, pos):
         pg = tables[i][np.array(keep, dtype=int) // 16] if keep else np.zeros(0, dtype=int)
         sl = np.array(keep, dtype=int) % 16
         kv = pool[0][:, torch.as_tensor(pg, dtype=torch.long), torch.as_tensor(sl)].double().numpy()
-        ref, k_new, v_new = om.decode(int(ids[i]), n, [kv[0]], [kv[1]], g, ls, shp)
+        ref, k_new, v_new, r = om.decode(int(ids[i]), n, [kv[0]], [kv[1]], g, ls, shp, with_residual=True)
         e = rel_err(logits[i].double().cpu().numpy(), ref)
         assert e <= TOL, f"position {n}: logits rel err {e:.3g}"
-        assert np.isfinite(resid[i]).all()
+        e = rel_err(resid[i], r)
+        assert e <= TOL, f"position {n}: residual rel err {e:.3g}"
         at = got_pool[0][:, tables[i, n // 16], n % 16].double().numpy()
         assert rel_err(at[0], k_new[0]) <= TOL and rel_err(at[1], v_new[0]) <= TOL
+        got_pool[0][:, tables[i, n // 16], n % 16] = pool[0][:, tables[i, n // 16], n % 16]
+    assert torch.equal(got_pool.view(torch.int16), pool.view(torch.int16)), "slots written besides the rows' own"
 
 
 def test_slot_outside_the_pool(P):
@@ -167,11 +171,13 @@ def test_rows_of_one_sequence(P, name):
 
 
 # head_dim, group, KV heads, positions.  Alone a row runs in workgroups of four
-# waves and one split each; two and five rows in workgroups of four waves and
-# longer runs; all of them in workgroups of two waves.
+# waves and one split each.  Beside others: two waves with one split, and with
+# one, two and four; the same at head_dim 64; four waves with two and with four.
 BATCHES = [
-    (128, 2, 8, [300, 1000, 2500, 6000, 9000, 40, 127, 0]),
+    (128, 2, 16, [300, 1000, 2500, 6000, 9000, 40, 127, 0]),
     (64, 4, 4, [4095, 4096, 16383, 2047, 129, 8200, 700, 15000]),
+    (128, 1, 8, [1000, 1500, 2047, 1800, 120, 900, 511, 2000]),
+    (64, 8, 8, [1000, 1500, 2047, 1800, 120, 900, 511, 2000]),
 ]
 
 

@@ -65,9 +65,11 @@ def test_rows(P, name, rows):
         n = pos[i]
         t = np.arange(n)
         kv = pool[:, :, torch.as_tensor(tables[i][t // 16], dtype=torch.long), torch.as_tensor(t % 16)].double().numpy()
-        ref, _, _ = om.decode(int(ids[i]), n, list(kv[:, 0]), list(kv[:, 1]), g, ls, shp)
+        ref, _, _, r = om.decode(int(ids[i]), n, list(kv[:, 0]), list(kv[:, 1]), g, ls, shp, with_residual=True)
         e = rel_err(out[0][i].double().cpu().numpy(), ref)
         assert e <= TOL, f"row {i} of {rows}: logits rel err {e:.3g}"
+        e = rel_err(resid[0][i].double().cpu().numpy(), r)
+        assert e <= TOL, f"row {i} of {rows}: residual rel err {e:.3g}"
 
 
 @pytest.mark.parametrize("counts", [[1, 2, 3, 4, 5, 7, 8], [9, 12, 16, 17, 32, 33, 64]])
