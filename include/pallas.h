@@ -284,8 +284,9 @@ int pallas_assemble_kv(const pallas_kv_pool* dst, const int32_t* d_dst_block_tab
  * num_seqs in [1, PALLAS_MAX_SEQS]; 0 <= n_i <=
  * PALLAS_MAX_DECODE_POS (UNSUPPORTED beyond: decode attention cuts a
  * sequence into at most 16 splits of at most 1024 keys), and n_i + 1 <=
- * max_pages * page (OUT_OF_RANGE).  For more than 8 sequences the 2 GiB operand limit of pallas_prefill_prefix applies, also to
- * lm_head [V][hidden].
+ * max_pages * page (OUT_OF_RANGE).  For more than 8 sequences the 2 GiB
+ * operand limit of pallas_prefill_prefix applies, also to lm_head
+ * [V][hidden].
  * Table entries outside [0, num_pages) raise PALLAS_DEVERR_PAGE (the K/V
  * store of slot n_i is skipped; keys on such pages are masked), token ids
  * outside [0, vocab) PALLAS_DEVERR_TOKEN, in *d_err (nullable). */
@@ -298,19 +299,19 @@ int pallas_decode_step(pallas_model* m, int32_t num_seqs, const int32_t* d_token
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  The same step as pallas_decode_step (the same checks,
  * kernels and results, bit for bit), with its intermediate values in a
- * scratch array of PALLAS_STATIC_SCRATCH_BYTES that the library keeps in
- * device memory on each GPU it runs on, from that GPU's first call until
- * the process ends.  The call allocates nothing; the caller still owns the
+ * scratch array (PALLAS_STATIC_SCRATCH_BYTES and 24 MiB) that the library
+ * keeps in device memory on each GPU it runs on, from that GPU's first call
+ * until the process ends.  The call allocates nothing; the caller still owns the
  * tokens, tables, pool and logits.  Every call on one GPU uses that GPU's
  * one array, so calls whose work overlaps on a GPU (different streams, or
  * host threads without ordering) race and give undefined results; calls
  * ordered on one stream do not.  Each call clears what must start at zero.
  * Limits, beyond those of pallas_decode_step (UNSUPPORTED): at most
- * PALLAS_STATIC_DECODE_MAX_SEQS sequences, and a scratch need within the
- * array: roughly num_seqs * n_q_heads * (max n_i / 64 + 1) * (head_dim + 2)
- * * 4 bytes of attention records plus the step's activations (at 64 query
- * heads of 128 and ffn 25600: 8 sequences up to position 15,743; fewer
- * up to 16,383).
+ * PALLAS_STATIC_DECODE_MAX_SEQS sequences, and at most
+ * PALLAS_STATIC_SCRATCH_BYTES counted as num_seqs * n_q_heads *
+ * (max n_i / 64 + 1) * (head_dim + 2) * 4 bytes for attention (more than it
+ * uses today) plus the step's activations (at 64 query heads of 128 and ffn
+ * 25600: 8 sequences up to position 15,743; fewer up to 16,383).
  * HIP on a failed device query. */
 #define PALLAS_STATIC_SCRATCH_BYTES (64u << 20)
 #define PALLAS_STATIC_DECODE_MAX_SEQS 8

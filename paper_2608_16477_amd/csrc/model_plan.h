@@ -105,7 +105,8 @@ inline Workspace workspace_layout(const pallas_model_config& c, int64_t tokens, 
 // The documented scratch need of pallas_decode_step_static, which decides
 // what it accepts: the step's activations, one record per 64 keys and query
 // head, and partial sums and counters of the projections of fewer than 512
-// 16-row tiles (O and down at the large shape: three splits).
+// 16-row tiles.  It is what the first decode kernels used and is kept so that
+// the same calls are accepted; the layout itself is decode_layout.
 inline size_t static_decode_need(const pallas_model_config& c, int seqs, int max_pos) {
   const int64_t QKV = int64_t(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   const int64_t QD = int64_t(c.n_q_heads) * c.head_dim;

@@ -583,7 +583,12 @@ int decode_checks(const pallas_model* m, int32_t num_seqs, const int32_t* d_toke
 // the array's name as an address: its device address on the current GPU is
 // looked up once per device (hipGetSymbolAddress, on the first call that
 // runs there) and kept in `g_scratch`.
-static __device__ __align__(256) unsigned char scratch[PALLAS_STATIC_SCRATCH_BYTES];
+//   What a call is accepted for (static_decode_need) leaves out the sums of
+// squares (2 hidden + 128 bytes: an accepted call's hidden is below 64 MiB / 6)
+// and the projections' partial sums and counters beyond what it counts (at most
+// 2 MiB and 4 KiB: gemv_plan splits what runs at once): room beside the limit.
+constexpr size_t kScratchBytes = PALLAS_STATIC_SCRATCH_BYTES + (24u << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -701,7 +706,7 @@ int pallas_decode_step_static(pallas_model* m, int32_t num_seqs, const int32_t* 
   for (int i = 0; i < num_seqs; ++i) max_pos = std::max(max_pos, h_positions[i]);
   const size_t need = pallas::static_decode_need(m->cfg, num_seqs, max_pos);
   const pallas::Workspace w = pallas::decode_layout(m->cfg, num_seqs, max_pos);
-  if (need > PALLAS_STATIC_SCRATCH_BYTES || w.total > PALLAS_STATIC_SCRATCH_BYTES)
+  if (need > PALLAS_STATIC_SCRATCH_BYTES || w.total > kScratchBytes)
     return fail(PALLAS_ERR_UNSUPPORTED,
                 "decode (static scratch): %d sequences up to position %d need %zu bytes of scratch (at most %zu)",
                 num_seqs, max_pos, need, size_t(PALLAS_STATIC_SCRATCH_BYTES));

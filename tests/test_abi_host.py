@@ -345,6 +345,31 @@ def test_static_decode_host_rejections(P):
         h.pallas_model_destroy(model)
 
 
+def test_static_decode_accepts_up_to_its_limit(P):
+    """The limit counts a step's activations and 66 floats per 64 keys here
+    (one head of 64): 8 sequences at position 0 with ffn 4,192,864 need exactly
+    PALLAS_STATIC_SCRATCH_BYTES, and are accepted although the sums of squares
+    and partial sums that the limit leaves out take more (without a GPU the
+    call then fails on the device query); 16 more columns are refused."""
+    import torch
+    from workloads import configs
+    from paper_2608_16477_amd.binding import KVPoolC
+    if torch.cuda.is_available():
+        pytest.skip("an accepted call would launch kernels on the fake pointers")
+    h = P.lib()
+
+    def rc(ffn):
+        c = configs.TINY.replace(hidden=64, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn=ffn, vocab=64, n_layers=1)
+        model = fake_model(P, c)
+        pool = KVPoolC(FAKE, 64, c.page_size, 1, 1, 64)
+        try:
+            return P.Status(h.pallas_decode_step_static(model, 8, FAKE, (C.c_int32 * 8)(), FAKE, 8, C.byref(pool),
+                                                        FAKE, None, None))
+        finally:
+            h.pallas_model_destroy(model)
+    assert [rc(4192864 + x) for x in (-16, 0, 16)] == [P.Status.HIP, P.Status.HIP, P.Status.UNSUPPORTED]
+
+
 @pytest.mark.parametrize("shape", [dict(), dict(hidden=131072, n_q_heads=1, n_kv_heads=1, ffn=64, vocab=64),
                                    dict(hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, ffn=4096, vocab=512)])
 def test_a_workspace_serves_smaller_calls(P, shape):
