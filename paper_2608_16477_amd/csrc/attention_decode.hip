@@ -606,35 +606,31 @@ bool plan_decode_runs(const RowMap& rm, int Hkv, DecodeRuns& runs) {
   if (rm.n_seqs < 1 || rm.n_seqs > kMaxSeqs) return false;
   for (int i = 0; i < rm.n_seqs; ++i)
     if (rm.base_pos[i] < 0 || decode_split_keys(rm.base_pos[i]) > kDecodeMaxRun) return false;
-  auto count = [&](int i) {
-    const int splits = rm.base_pos[i] / decode_split_keys(rm.base_pos[i]) + 1;
-    return (splits + runs.per_run[i] - 1) / runs.per_run[i];
-  };
+  int split_keys[kMaxSeqs], splits[kMaxSeqs];
+  for (int i = 0; i < rm.n_seqs; ++i) {
+    split_keys[i] = decode_split_keys(rm.base_pos[i]);
+    splits[i] = rm.base_pos[i] / split_keys[i] + 1;
+  }
+  auto count = [&](int i) { return (splits[i] + runs.per_run[i] - 1) / runs.per_run[i]; };
   int64_t wgs;
   auto start = [&] {
     wgs = 0;
     for (int i = 0; i < rm.n_seqs; ++i) {
       runs.per_run[i] = 1;
-      wgs += int64_t(count(i)) * Hkv;
+      wgs += int64_t(splits[i]) * Hkv;
     }
   };
   // Doubles the shortest runs that may have up to `keys` keys until at most
-  // `most` workgroups are left.
+  // `most` workgroups are left (the shortest first: a doubled run's turn comes
+  // at its new length).
   auto grow = [&](int64_t most, int keys) {
-    while (wgs > most) {
-      int at = -1, least = 0;
-      for (int i = 0; i < rm.n_seqs; ++i) {
-        const int r = decode_split_keys(rm.base_pos[i]) * runs.per_run[i];
-        if (2 * r <= keys && 2 * runs.per_run[i] <= kDecodeMaxRunSplits && count(i) > 1 && (at < 0 || r < least)) {
-          at = i;
-          least = r;
-        }
+    for (int r = kDecodeMinSplit; 2 * r <= keys; r += kDecodeMinSplit)
+      for (int i = 0; i < rm.n_seqs && wgs > most; ++i) {
+        const int c = count(i);
+        if (split_keys[i] * runs.per_run[i] != r || 2 * runs.per_run[i] > kDecodeMaxRunSplits || c == 1) continue;
+        runs.per_run[i] *= 2;
+        wgs -= int64_t(c - count(i)) * Hkv;
       }
-      if (at < 0) break;
-      wgs -= int64_t(count(at)) * Hkv;
-      runs.per_run[at] *= 2;
-      wgs += int64_t(count(at)) * Hkv;
-    }
   };
   start();
   grow(kCus, kDecodeMaxRun / 2);
