@@ -673,7 +673,7 @@ hipError_t launch_gemm(int epi, const uint16_t* A, int lda, const uint16_t* B, i
   p.ldb = ldb;
   p.ldc = ldc;
   p.ksplit = gemm_ksplit(epi, M, N, K);
-  const bool few = M <= kGemmFewRows;
+  const bool few = gemm_few_rows(epi, M, N, p.ksplit);
   if (epi == kEpiF32 && M > 64) return hipErrorInvalidValue;   // decode only
   const GemmTile tile = few ? gemm_tile_few(epi, M, N) : gemm_tile(epi, M, N);
   const int bm = tile.bm, bn = tile.bn;

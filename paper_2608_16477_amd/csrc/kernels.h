@@ -131,6 +131,21 @@ inline GemmTile gemm_tile_few(int epi, int M, int N) {
   return {M <= 128 ? 128 : M <= 192 ? 192 : 256, bn};
 }
 
+// Which of the two tile rules a launch takes.  Without a K split (K below 2048,
+// or many columns), more than 64 rows are one M tile only where gemm_tile, too,
+// takes one, of at least 128 columns, and the columns fill a quarter of the
+// CUs.  Fewer run faster as gemm_tile's, in narrower tiles or two M tiles, and
+// with their few weights cached: the tiny model's prefill of 192 rows takes 86
+// against 121 us, one of hidden 1536 and ffn 8960 198 against 273 at 256 rows.
+// At 180 rows and 32, 64, 96 and 140 tiles of gate|up, three layers take 161,
+// 176, 186 and 192 us that way, 173, 174, 177 and 181 this way; 288 tiles of
+// 128 in 256 rows 1089 against 1022.
+inline bool gemm_few_rows(int epi, int M, int N, int ksplit) {
+  if (M > kGemmFewRows || M <= 64 || ksplit > 1) return M <= kGemmFewRows;
+  const GemmTile t = gemm_tile(epi, M, N);
+  return t.bm >= M && t.bn >= 128 && gemm_tiles_n(epi, N, 128) >= 64;
+}
+
 // K-range splits per tile.  Only launches of at most 256 rows split (their
 // few tiles would leave most of the 256 CUs idle): 128-wide tiles times
 // splits fill at most 256 workgroups, and each split keeps at least 16 K-steps
