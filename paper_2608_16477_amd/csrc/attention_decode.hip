@@ -545,8 +545,8 @@ __global__ __launch_bounds__(kBoundThreads) void attn_decode_kernel(DecodeAttnPa
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   if (*arrived != nrun - 1) return;
   if (t == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // All records of a batch of runs are in flight at once, for both of this
-  // thread's output groups.  A batch is an aligned part of the tree.
+  // All records of a batch of runs are in flight at once, for each of this
+  // thread's E output groups.  A batch is an aligned part of the tree.
   constexpr int E = (8 * D / 4 + kThreads - 1) / kThreads, U = E == 1 ? kDecodeSplitsPerSeq : kDecodeSplitsPerSeq / 2;
   const __amdgpu_buffer_rsrc_t rml = __builtin_amdgcn_make_buffer_rsrc(
       (void*)rec_ml, 0, static_cast<uint32_t>(nrun * G * 8), 0x00020000);

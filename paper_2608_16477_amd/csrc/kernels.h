@@ -44,7 +44,7 @@ enum GemmEpi : int {
   kEpiBf16 = 0,    // C bf16 [M][ldc] = A B^T
   kEpiAddF32 = 1,  // C f32 [M][ldc] += A B^T (residual add)
   kEpiSwiGLU = 2,  // C bf16 [M][ldc] = silu(A Bg^T) * (A Bu^T); B rows [0,N) gate, [N,2N) up
-  kEpiF32 = 3,     // C f32 [M][ldc] = A B^T (skinny kernels only)
+  kEpiF32 = 3,     // C f32 [M][ldc] = A B^T (decode: up to 64 rows)
 };
 
 struct GemmParams {
@@ -130,7 +130,6 @@ inline GemmTile gemm_tile_few(int epi, int M, int N) {
   if (M <= 64 && bn == 128) return {64, 128};
   return {M <= 128 ? 128 : M <= 192 ? 192 : 256, bn};
 }
-
 // Which of the two tile rules a launch takes.  Without a K split (K below 2048,
 // or many columns), more than 64 rows are one M tile only where gemm_tile, too,
 // takes one, of at least 128 columns, and the columns fill a quarter of the
@@ -368,14 +367,16 @@ struct GemvPlan {
   int norm_parts() const { return tiles * tn; }
 };
 // The plan of least modelled time, from the shape alone (so a row's arithmetic
-// does not depend on the rows beside it).  A
-// CU holds r workgroups (their LDS stages decide), and a full round of 256 r
-// of them takes K / S u r + c0: u = the time 256 CUs need for one k of tn
-// blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split adds 1 us +
-// 0.3 us per part (count, partial sums) and the partials' traffic.  Fitted to
-// (us, tn / S): Q|K|V of the mid model at M = 1 11.8 (1 / 2), 12.7 (2 / 1),
-// 14.2 (2 / 4 at M = 8), of the large one 19.7 (4 / 3), 20.2 (1 / 1), 21.6
-// (1 / 2); large O 17.6 (2 / 3), down 43.2 (2 / 3) and 45 (1 / 3).
+// does not depend on the rows beside it; X, a small part of the loads, is not
+// counted).  A CU holds r workgroups (their LDS stages decide), and a full
+// round of 256 r of them takes K / S u r + c0: u = the time 256 CUs need for
+// one k of tn blocks at 5.5 TB/s, c0 = 3 us of start and epilogue.  A split
+// adds 1 us + 0.3 us per part (count, partial sums) and the partials' traffic.
+//   It ranks plans and predicts no times: modelled against measured (us, tn /
+// S), Q|K|V of the mid model 1 / 2 14.1, 11.8; 2 / 1 15.2, 12.7; 2 / 4 15.1,
+// 14.2 (8 rows); of the large one 4 / 3 26.2, 19.7; 1 / 1 25.9, 20.2; large O
+// 2 / 3 21.7, 17.6; down 2 / 3 56.2, 43.2; 1 / 3 56.2, 45.  Equal ones keep the
+// narrower tile: at the large down and Q|K|V that is 4% and 3% off the best.
 inline GemvPlan gemv_plan(int epi, int N, int K) {
   GemvPlan best{};
   const int64_t rows = epi == kEpiSwiGLU ? 2 * int64_t(N) : N;

@@ -1,8 +1,7 @@
 """Decode parity against the oracle at long contexts and full vocabulary.
 
-From position 1024 on, decode attention runs more than 16 splits of 64 keys
-and its combine pass reads the split records in several batches of 16;
-from 4000 on, more than 62.  The lm_head of the 151936-token vocabulary has
+At 1100 decode attention cuts the keys into nine splits, at 4000 and 8000 into
+sixteen, of 256 and 512 keys there.  The lm_head of the 151936-token vocabulary has
 9496 weight tiles.  Logits within max|gpu - ref| <= 1e-2 max|ref| per row.
 
 * Tiny decoder (2 layers, vocab 151936), the oracle end to end: it prefills

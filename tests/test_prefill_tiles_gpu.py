@@ -1,7 +1,8 @@
 """Prefill at the row counts where the GEMMs change their tile or K split,
 against the oracle end to end: the limits of the 64-, 128-, 192- and 256-row
 tiles of launches of at most 256 rows (gate|up with 128- and with 256-wide
-tiles, O and down with and without a K split), and a few hundred rows, which
+tiles, O and down with and without a K split; few columns without a split, which
+take narrower tiles or two M tiles from 65 rows on), and a few hundred rows, which
 take 128-row tiles above 256.  K/V of both layers within 1e-2 max|ref| (the
 bf16 bound of the other prefill tests).  Lengths on one side of 256 rows agree bit for bit: above it in
 everything, up to it in layer 0, which the projection alone decides (attention
