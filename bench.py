@@ -47,8 +47,8 @@ NOMINAL_SCLK_GHZ = 2.4      # clock the MFMA peak is quoted at
 # only for the GEMM source it was measured on: a different csrc/gemm.hip
 # reports null.
 GEMM_TRAFFIC = {
-    "gemm_source_sha256_16": "cee46dc046faea20",
-    "fetch_kib": 1.38511e6, "fetch_scale": 2.0,
+    "gemm_source_sha256_16": "0833f3d23c47e323",
+    "fetch_kib": 1.40882e6, "fetch_scale": 2.0,
     "write_kib": 1.94010e5, "write_scale": 1.0,
 }
 
